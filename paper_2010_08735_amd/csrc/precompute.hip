@@ -3,7 +3,7 @@
 // record, at the Appendix A texel centres k/(N-1):
 //   D(e, u)   = phi - atan2(u, du/dphi) on the incoming branch   (Algorithm 1, Precompute)
 //   U(e, phi) = u for 0 <= phi < pi, 1 once the ray has fallen in (Section 3.3.3).
-// One thread integrates one e column with classic RK4 in phi.  Precision: FP64 while
+// Classic RK4 in phi, one e column per workgroup.  Precision: FP64 while
 // |u - 2/3| < band (near the photon sphere, where the deflection diverges and errors grow
 // exponentially with each turn), FP32 elsewhere with Kahan-compensated state updates.
 // Values between steps come from cubic Hermite interpolation (u and du/dphi are both
@@ -33,79 +33,90 @@ __device__ __forceinline__ void kahan_add(float& s, float& c, float x) {
   s = t;
 }
 
-// State of one column integration, switching between FP64 and compensated FP32.
+// The serial part of a column: u and w = du/dphi by RK4, in FP64 or compensated FP32.  The
+// regularised time is no part of this chain: its increments depend only on each step's
+// start, so the reading wave forms them in parallel (tau_step).
 struct Integrator {
   double e2;            // the column's conserved (du/dphi)^2 + u^2 (1 - u)
-  double e;             // its square root
-  double u, w, tau;     // FP64 state (valid when in64)
+  double u, w;          // FP64 state (valid when in64)
   float uf, wf, cu, cw; // FP32 state, true value = uf - cu (Kahan)
-  float tf, ct;         // FP32 regularised time, true value = tf - ct
   bool in64;
   int mode;
   double band;
 
-  __device__ bool want64(double uu) const {
+  __device__ __forceinline__ bool want64(double uu) const {
     return mode == kTabAll || (mode == kTabBand && fabs(uu - 2.0 / 3.0) < band);
   }
-  __device__ void init(double u0, double w0) {
+  __device__ __forceinline__ void init(double u0, double w0) {
     u = u0;
     w = w0;
-    tau = 0.0;
     uf = (float)u0;
     wf = (float)w0;
     cu = (float)((double)uf - u0);
     cw = (float)((double)wf - w0);
-    tf = 0.0f;
-    ct = 0.0f;
     in64 = want64(u0);
   }
-  __device__ double get_u() const { return in64 ? u : (double)uf - (double)cu; }
-  __device__ double get_w() const { return in64 ? w : (double)wf - (double)cw; }
-  __device__ double get_tau() const { return in64 ? tau : (double)tf - (double)ct; }
-  __device__ void step(double h) {
-    double uc = get_u();
-    bool w64 = want64(uc);
-    if (w64 != in64) {
-      if (w64) {
-        // entering the FP64 band: keep u and re-derive |du/dphi| from the exact invariant,
-        // so FP32 rounding of e^2 is not amplified by the unstable orbit near u = 2/3
-        u = uc;
-        double wc = get_w();
-        tau = get_tau();
-        double w2 = e2 - uc * uc * (1.0 - uc);
-        w = w2 > 0.0 ? copysign(sqrt(w2), wc) : 0.0;
-      } else {
-        uf = (float)u;
-        cu = (float)((double)uf - u);
-        wf = (float)w;
-        cw = (float)((double)wf - w);
-        tf = (float)tau;
-        ct = (float)((double)tf - tau);
-      }
-      in64 = w64;
-    }
-    if (in64) {
-      double k1u = w, k1w = accel64(u);
-      double k2u = w + 0.5 * h * k1w, k2w = accel64(u + 0.5 * h * k1u);
-      double k3u = w + 0.5 * h * k2w, k3w = accel64(u + 0.5 * h * k2u);
-      double k4u = w + h * k3w, k4w = accel64(u + h * k3u);
-      tau += h / 6.0 * (1.0 / (e + k1u) + 2.0 / (e + k2u) + 2.0 / (e + k3u) + 1.0 / (e + k4u));
-      u += h / 6.0 * (k1u + 2.0 * k2u + 2.0 * k3u + k4u);
-      w += h / 6.0 * (k1w + 2.0 * k2w + 2.0 * k3w + k4w);
+  __device__ __forceinline__ double get_u() const {
+    return in64 ? u : (double)uf - (double)cu;
+  }
+  __device__ __forceinline__ double get_w() const {
+    return in64 ? w : (double)wf - (double)cw;
+  }
+  // the precision of the next step
+  __device__ __forceinline__ void select() {
+    const double uc = get_u();
+    const bool w64 = want64(uc);
+    if (w64 == in64) return;
+    if (w64) {
+      // entering the FP64 band: keep u and re-derive |du/dphi| from the exact invariant,
+      // so FP32 rounding of e^2 is not amplified by the unstable orbit near u = 2/3
+      const double wc = get_w();
+      u = uc;
+      const double w2 = e2 - uc * uc * (1.0 - uc);
+      w = w2 > 0.0 ? copysign(sqrt(w2), wc) : 0.0;
     } else {
-      float hf = (float)h;
-      float k1u = wf, k1w = accel32(uf);
-      float k2u = wf + 0.5f * hf * k1w, k2w = accel32(uf + 0.5f * hf * k1u);
-      float k3u = wf + 0.5f * hf * k2w, k3w = accel32(uf + 0.5f * hf * k2u);
-      float k4u = wf + hf * k3w, k4w = accel32(uf + hf * k3u);
-      float ef = (float)e;
-      kahan_add(tf, ct, hf / 6.0f * (1.0f / (ef + k1u) + 2.0f / (ef + k2u) + 2.0f / (ef + k3u) +
-                                     1.0f / (ef + k4u)));
-      kahan_add(uf, cu, hf / 6.0f * (k1u + 2.0f * k2u + 2.0f * k3u + k4u));
-      kahan_add(wf, cw, hf / 6.0f * (k1w + 2.0f * k2w + 2.0f * k3w + k4w));
+      uf = (float)u;
+      cu = (float)((double)uf - u);
+      wf = (float)w;
+      cw = (float)((double)wf - w);
     }
+    in64 = w64;
+  }
+  __device__ __forceinline__ void step64(double h) {
+    double k1u = w, k1w = accel64(u);
+    double k2u = w + 0.5 * h * k1w, k2w = accel64(u + 0.5 * h * k1u);
+    double k3u = w + 0.5 * h * k2w, k3w = accel64(u + 0.5 * h * k2u);
+    double k4u = w + h * k3w, k4w = accel64(u + h * k3u);
+    u += h / 6.0 * (k1u + 2.0 * k2u + 2.0 * k3u + k4u);
+    w += h / 6.0 * (k1w + 2.0 * k2w + 2.0 * k3w + k4w);
+  }
+  __device__ __forceinline__ void step32(float hf) {
+    float k1u = wf, k1w = accel32(uf);
+    float k2u = wf + 0.5f * hf * k1w, k2w = accel32(uf + 0.5f * hf * k1u);
+    float k3u = wf + 0.5f * hf * k2w, k3w = accel32(uf + 0.5f * hf * k2u);
+    float k4u = wf + hf * k3w, k4w = accel32(uf + hf * k3u);
+    kahan_add(uf, cu, hf / 6.0f * (k1u + 2.0f * k2u + 2.0f * k3u + k4u));
+    kahan_add(wf, cw, hf / 6.0f * (k1w + 2.0f * k2w + 2.0f * k3w + k4w));
   }
 };
+
+// Increment of the regularised time over the step that starts at (u, w): RK4 on
+// dtau/dphi = 1 / (e + du/dphi), the stages of step64 and step32 formed again.
+__device__ __forceinline__ double tau_step64(double e, double u, double w, double h) {
+  double k1u = w, k1w = accel64(u);
+  double k2u = w + 0.5 * h * k1w, k2w = accel64(u + 0.5 * h * k1u);
+  double k3u = w + 0.5 * h * k2w, k3w = accel64(u + 0.5 * h * k2u);
+  double k4u = w + h * k3w;
+  return h / 6.0 * (1.0 / (e + k1u) + 2.0 / (e + k2u) + 2.0 / (e + k3u) + 1.0 / (e + k4u));
+}
+__device__ __forceinline__ float tau_step32(float ef, float uf, float wf, float hf) {
+  float k1u = wf, k1w = accel32(uf);
+  float k2u = wf + 0.5f * hf * k1w, k2w = accel32(uf + 0.5f * hf * k1u);
+  float k3u = wf + 0.5f * hf * k2w, k3w = accel32(uf + 0.5f * hf * k2u);
+  float k4u = wf + hf * k3w;
+  return hf / 6.0f *
+         (1.0f / (ef + k1u) + 2.0f / (ef + k2u) + 2.0f / (ef + k3u) + 1.0f / (ef + k4u));
+}
 
 __device__ __forceinline__ double hermite(double t, double f0, double d0, double f1, double d1,
                                           double hh) {
@@ -132,82 +143,345 @@ __device__ double d_col_e2(int n, int i) {
 
 constexpr int kMaxSteps = 4000000;
 
-__global__ void __launch_bounds__(64) k_precompute_D(float* __restrict__ D,
-                                                     float* __restrict__ Dt, int n, int mode,
-                                                     double band, double step) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const double e2 = d_col_e2(n, i);
-  const double e = sqrt(e2);
-  const double h = step / (1.0 + e);
-  Integrator I;
-  I.mode = mode;
-  I.band = band;
-  I.e2 = e2;
-  I.e = e;
-  I.init(0.0, e);
-  D[i] = 0.0f;  // u = 0 at phi = 0: D = 0 - atan2(0, e)
-  Dt[i] = 0.0f;
-  int j = 1;
-  if (i < n / 2) {
-    // roots u_a < u_2 of u^3 - u^2 + e^2 (u_3 < 0): closed form and sum/product of roots
-    double ua = 1.0 / 3.0 + 2.0 / 3.0 * sin(asin(fmin(2.0 * e2 / kMuD - 1.0, 1.0)) / 3.0);
-    double ssum = 1.0 - ua, prod = -e2 / ua;
-    double disc = sqrt(ssum * ssum - 4.0 * prod);
-    double u2 = 0.5 * (ssum + disc), u3 = 0.5 * (ssum - disc);
-    double yp = 0.0, fp = 0.0, dp, tp = 0.0, dtp;
-    {
-      // derivatives at the start (u = 0, w = e): s = w / g, g(0) = e
-      double g = e, gp = ua * (u2 + u3) / (2.0 * g);
-      double dsdphi = (0.0 * g - e * e * gp) / (g * g);  // accel(0) = 0
-      double dDdphi = 1.0 - (e * e) / (e * e);            // = 0 at u = 0
-      dp = dDdphi / (-dsdphi);
-      dtp = (0.5 / e) / (-dsdphi);                         // dtau/dphi = 1 / (2e) at u = 0
-    }
-    for (int k = 1; k < kMaxSteps && j < n; ++k) {
-      I.step(h);
-      double u = I.get_u(), w = I.get_w(), phi = k * h;
-      double g2 = ua * (u2 - u) * (u - u3);
-      double g = sqrt(fmax(g2, 1e-300));
-      double y = 1.0 - w / g;
-      double acc = accel64(u);
-      double gp = ua * (u2 + u3 - 2.0 * u) / (2.0 * g);
-      double dydphi = -(acc * g - w * w * gp) / g2;
-      double f = phi - atan2(u, w);
-      double dfdphi = 1.0 - (w * w - u * acc) / (u * u + w * w);
-      double d = dfdphi / dydphi;
-      double tv = I.get_tau(), dtv = (1.0 / (e + w)) / dydphi;
-      while (j < n) {
-        double yj = (double)j / (n - 1);
-        if (yj > y) break;
-        double hh = y - yp;
-        double t = hh > 0.0 ? (yj - yp) / hh : 1.0;
-        D[(size_t)j * n + i] = (float)hermite(t, fp, dp, f, d, hh);
-        Dt[(size_t)j * n + i] = (float)(e * hermite(t, tp, dtp, tv, dtv, hh));
-        ++j;
+// ---- one workgroup per column ------------------------------------------------------------
+// A column is a serial chain of up to ~10^4 RK4 steps (the columns next to mu), and the chip
+// has far more lanes than columns, so what counts is the length of one step's dependent
+// chain.  Two waves share the column: wave 0 only integrates (u, w), every lane the same
+// values (a wave of few active lanes issues each instruction several times slower than a full
+// one), and writes the state after each step to LDS; wave 1 reads the chunk before it: the
+// time increments (64 lanes, then a prefix sum in FP64) and one lane per table row, which
+// finds its step by bisection.  One barrier per chunk.  512 x 512 with 64 x 32, FP64 band,
+// with the download and 100 003 traced rays: 18.5 ms as one thread per column, integration
+// and readout in turn, 0.96 ms so.
+constexpr int kChunk = 256;
+
+struct ChunkInfo {
+  int n, first, in64, last;  // steps, index of the state before them, precision, last chunk
+};
+struct ColumnLds {
+  float4 st[2][kChunk + 1];  // (uf, cu, wf, cw), or u and w in FP64
+  float4 dump[64];           // where the copies of wave 0's other lanes go
+  double val[kChunk + 1];    // the row coordinate after each step (y, or u)
+  double tau[kChunk + 1];
+  ChunkInfo info[2];
+};
+
+union State16 {
+  float4 f;
+  double d[2];
+};
+
+__device__ __forceinline__ void state_at(const float4& s, bool in64, double* u, double* w) {
+  State16 x;
+  x.f = s;
+  *u = in64 ? x.d[0] : (double)x.f.x - (double)x.f.y;
+  *w = in64 ? x.d[1] : (double)x.f.z - (double)x.f.w;
+}
+
+// orders this wave's LDS writes before its other lanes' reads
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// A column ends where its last row is passed: kApsis at w <= 0, kHorizon at u >= 1, kPhi after
+// `max_steps` steps or at u >= 1 (the ray has fallen in).
+enum { kApsis = 0, kHorizon = 1, kPhi = 2 };
+
+// a condition that is the same on every lane, as a scalar
+__device__ __forceinline__ bool uniform(bool c) {
+  return __builtin_amdgcn_readfirstlane((int)c) != 0;
+}
+
+// Wave 0: up to kChunk steps of one precision into st (st[0] = the state they start from).
+// Steps go in blocks of kBlock, looked at once: u rises until w changes its sign, so a block
+// that ends inside its precision's range and before the column's end was inside all along; one
+// that does not is taken back and stepped singly.  (Tests and branches after every step took
+// more than half of the step: 2.05 against 0.96 ms for the pass above.)
+constexpr int kBlock = 8;
+
+template <int END>
+__device__ __forceinline__ ChunkInfo integrate_chunk(Integrator& I, double h, int done,
+                                                     int max_steps, float4* st, float4* dump) {
+  const int lane = threadIdx.x & 63;
+  float4* dst = lane == 0 ? st : dump + lane;
+  const int inc = lane == 0 ? 1 : 0;
+  I.select();
+  ChunkInfo c;
+  c.first = done;
+  c.in64 = uniform(I.in64);
+  c.last = 0;
+  const int most = min(kChunk, max_steps - done);
+  int n = 0;
+  if (c.in64) {
+    const auto put = [&] {
+      State16 x;
+      x.d[0] = I.u;
+      x.d[1] = I.w;
+      *dst = x.f;
+    };
+    const auto ended = [&] { return END == kApsis ? !(I.w > 0.0) : !(I.u < 1.0); };
+    const auto left = [&] {
+      return I.mode == kTabBand && !(fabs(I.u - 2.0 / 3.0) < I.band);
+    };
+    put();
+    while (n + kBlock <= most) {
+      const double u0 = I.u, w0 = I.w;
+#pragma unroll
+      for (int q = 0; q < kBlock; ++q) {
+        I.step64(h);
+        dst += inc;
+        put();
       }
-      yp = y;
-      fp = f;
-      dp = d;
-      tp = tv;
-      dtp = dtv;
+      if (uniform(ended() || left())) {
+        I.u = u0;
+        I.w = w0;
+        dst -= kBlock * inc;
+        break;
+      }
+      n += kBlock;
     }
-    for (; j < n; ++j) {  // not reached in practice
-      D[(size_t)j * n + i] = (float)fp;
-      Dt[(size_t)j * n + i] = (float)(e * tp);
+#pragma unroll 1
+    while (n < most) {
+      I.step64(h);
+      ++n;
+      dst += inc;
+      put();
+      if (uniform(ended())) {
+        c.last = 1;
+        break;
+      }
+      if (uniform(left())) break;
     }
   } else {
-    const double a = sqrt(2.0 / 3.0), b = sqrt(1.0 / 3.0);
-    double phip = 0.0, up = 0.0, wp = e, taup = 0.0;
-    for (int k = 1; k < kMaxSteps && j < n; ++k) {
-      I.step(h);
-      double u = I.get_u(), w = I.get_w(), phi = k * h, tau = I.get_tau();
-      while (j < n) {
-        double z = (double)j / (n - 1) * (a + b) - a;
-        double uj = 2.0 / 3.0 + (z >= 0 ? z * z : -z * z);
-        if (j == n - 1) uj = 1.0;
-        if (uj > u) break;
-        double hh = phi - phip;
+    const float hf = (float)h;
+    const auto put = [&] { *dst = make_float4(I.uf, I.cu, I.wf, I.cw); };
+    // u within a rounding of the FP64 band (never, when there is none) or of the end
+    const float near_lo = I.mode == kTabBand ? (float)(2.0 / 3.0 - I.band) - 1e-6f : 2.0f;
+    const float near_hi = I.mode == kTabBand ? (float)(2.0 / 3.0 + I.band) + 1e-6f : 2.0f;
+    const auto near_band = [&] { return I.uf > near_lo && I.uf < near_hi; };
+    const auto near_end = [&] {
+      return END == kApsis ? !(I.wf - I.cw > 0.0f) : !(I.uf < 0.999999f);
+    };
+    put();
+    while (n + kBlock <= most) {
+      const float u0 = I.uf, w0 = I.wf, cu0 = I.cu, cw0 = I.cw;
+#pragma unroll
+      for (int q = 0; q < kBlock; ++q) {
+        I.step32(hf);
+        dst += inc;
+        put();
+      }
+      // a block may not pass the whole band either (a narrow one, wide steps)
+      if (uniform(near_end() || near_band() || (u0 <= near_lo) != (I.uf <= near_lo))) {
+        I.uf = u0;
+        I.wf = w0;
+        I.cu = cu0;
+        I.cw = cw0;
+        dst -= kBlock * inc;
+        break;
+      }
+      n += kBlock;
+    }
+#pragma unroll 1
+    while (n < most) {
+      I.step32(hf);
+      ++n;
+      dst += inc;
+      put();
+      if (uniform(near_end())) {
+        if (END == kApsis || uniform(!(I.get_u() < 1.0))) {
+          c.last = 1;
+          break;
+        }
+      }
+      if (uniform(near_band())) {
+        if (uniform(I.want64(I.get_u()))) break;
+      }
+    }
+  }
+  c.n = n;
+  if (done + n >= max_steps) c.last = 1;
+  return c;
+}
+
+// Wave 1: tau after each step of the chunk (tau0 before the first); returns the last.
+__device__ __forceinline__ double chunk_tau(const float4* st, const ChunkInfo& c, double e,
+                                            double h, double tau0, double* tau) {
+  constexpr int kPer = kChunk / 64;
+  const int lane = threadIdx.x & 63;
+  double inc[kPer], sum = 0.0;
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    const int k = kPer * lane + q;
+    inc[q] = 0.0;
+    if (k < c.n) {
+      State16 x;
+      x.f = st[k];
+      inc[q] = c.in64 ? tau_step64(e, x.d[0], x.d[1], h)
+                      : (double)tau_step32((float)e, x.f.x, x.f.z, (float)h);
+    }
+    sum += inc[q];
+    inc[q] = sum;
+  }
+  double before = sum;  // inclusive sum over the lanes below and this one
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const double up = __shfl_up(before, o);
+    if (lane >= o) before += up;
+  }
+  const double total = __shfl(before, 63);
+  before += tau0 - sum;
+  if (lane == 0) tau[0] = tau0;
+#pragma unroll
+  for (int q = 0; q < kPer; ++q)
+    if (kPer * lane + q < c.n) tau[kPer * lane + q + 1] = before + inc[q];
+  return tau0 + total;
+}
+
+// smallest k in [1, n] with val[k] >= v, given val[n] >= v
+__device__ __forceinline__ int first_step(const double* val, int n, double v) {
+  int lo = 1, hi = n;
+  while (lo < hi) {
+    const int mid = (lo + hi) >> 1;
+    if (val[mid] >= v)
+      hi = mid;
+    else
+      lo = mid + 1;
+  }
+  return lo;
+}
+
+struct TableOut {
+  float* D;
+  float* Dt;
+  float* U;
+  float* Ut;
+  int n, ne, nphi;
+};
+
+// Wave 0's loop and the chunk hand-over; `read(chunk, states)` runs on wave 1 for each chunk
+// in turn.  Both waves leave after the iteration that read the last chunk.
+template <int END, class Read>
+__device__ __forceinline__ void run_column(ColumnLds& L, Integrator& I, double h, int max_steps,
+                                           Read read) {
+  const bool integrates = threadIdx.x < 64;
+  int done = 0;
+  bool ended = false;  // wave 0: the chunk before this iteration was the last
+  for (int c = 0;; ++c) {
+    bool stop = false;
+    if (integrates) {
+      stop = ended;
+      if (!ended) {
+        const ChunkInfo ci =
+            integrate_chunk<END>(I, h, done, max_steps, L.st[c & 1], L.dump);
+        done += ci.n;
+        ended = __builtin_amdgcn_readfirstlane(ci.last) != 0;
+        if ((threadIdx.x & 63) == 0) L.info[c & 1] = ci;
+      }
+    } else if (c > 0) {
+      ChunkInfo ci = L.info[(c - 1) & 1];
+      ci.n = __builtin_amdgcn_readfirstlane(ci.n);
+      ci.first = __builtin_amdgcn_readfirstlane(ci.first);
+      ci.in64 = __builtin_amdgcn_readfirstlane(ci.in64);
+      ci.last = __builtin_amdgcn_readfirstlane(ci.last);
+      read(ci, L.st[(c - 1) & 1]);
+      stop = ci.last != 0;
+    }
+    __syncthreads();
+    if (stop) break;
+  }
+}
+
+__device__ void column_D_low(ColumnLds& L, Integrator& I, const TableOut& O, int i, double e2,
+                             double e, double h) {
+  const int lane = threadIdx.x & 63, n = O.n;
+  // roots u_a < u_2 of u^3 - u^2 + e^2 (u_3 < 0): closed form and sum/product of roots
+  const double ua = 1.0 / 3.0 + 2.0 / 3.0 * sin(asin(fmin(2.0 * e2 / kMuD - 1.0, 1.0)) / 3.0);
+  const double ssum = 1.0 - ua, prod = -e2 / ua;
+  const double disc = sqrt(ssum * ssum - 4.0 * prod);
+  const double u2 = 0.5 * (ssum + disc), u3 = 0.5 * (ssum - disc);
+  int j0 = 1;
+  double tau0 = 0.0;
+  run_column<kApsis>(L, I, h, kMaxSteps - 1, [&](const ChunkInfo& c, const float4* st) {
+    tau0 = chunk_tau(st, c, e, h, tau0, L.tau);
+    for (int k = lane; k <= c.n; k += 64) {
+      double u, w;
+      state_at(st[k], c.in64, &u, &w);
+      const double g = sqrt(fmax(ua * (u2 - u) * (u - u3), 1e-300));
+      L.val[k] = c.first + k == 0 ? 0.0 : 1.0 - w / g;
+    }
+    wave_sync();
+    const double yend = L.val[c.n];
+    // D, its slope in y and the time's slope in y after step k
+    auto at = [&](int k, double* f, double* d, double* dt) {
+      double u, w;
+      state_at(st[k], c.in64, &u, &w);
+      const double g2 = ua * (u2 - u) * (u - u3), g = sqrt(fmax(g2, 1e-300));
+      const double acc = accel64(u), gp = ua * (u2 + u3 - 2.0 * u) / (2.0 * g);
+      const double dydphi = -(acc * g - w * w * gp) / g2;
+      *f = (c.first + k) * h - atan2(u, w);
+      *d = (1.0 - (w * w - u * acc) / (u * u + w * w)) / dydphi;
+      *dt = (1.0 / (e + w)) / dydphi;
+    };
+    for (;;) {
+      const int j = j0 + lane;
+      const double yj = (double)j / (n - 1);
+      const bool in = j < n && yj <= yend;
+      if (in) {
+        const int k = first_step(L.val, c.n, yj);
+        double fp, dp, dtp, f, d, dt;
+        at(k - 1, &fp, &dp, &dtp);
+        at(k, &f, &d, &dt);
+        const double yp = L.val[k - 1], hh = L.val[k] - yp;
+        const double t = hh > 0.0 ? (yj - yp) / hh : 1.0;
+        O.D[(size_t)j * n + i] = (float)hermite(t, fp, dp, f, d, hh);
+        O.Dt[(size_t)j * n + i] =
+            (float)(e * hermite(t, L.tau[k - 1], dtp, L.tau[k], dt, hh));
+      }
+      const int got = __popcll(__ballot(in));
+      j0 += got;
+      if (got < 64) break;
+    }
+    if (c.last) {  // rows past the step limit (not reached in practice)
+      double f, d, dt;
+      at(c.n, &f, &d, &dt);
+      for (int j = j0 + lane; j < n; j += 64) {
+        O.D[(size_t)j * n + i] = (float)f;
+        O.Dt[(size_t)j * n + i] = (float)(e * L.tau[c.n]);
+      }
+    }
+    wave_sync();  // the next chunk writes val and tau again
+  });
+}
+
+__device__ void column_D_high(ColumnLds& L, Integrator& I, const TableOut& O, int i, double e2,
+                              double e, double h) {
+  const int lane = threadIdx.x & 63, n = O.n;
+  const double a = sqrt(2.0 / 3.0), b = sqrt(1.0 / 3.0);
+  int j0 = 1;
+  double tau0 = 0.0;
+  run_column<kHorizon>(L, I, h, kMaxSteps - 1, [&](const ChunkInfo& c, const float4* st) {
+    tau0 = chunk_tau(st, c, e, h, tau0, L.tau);
+    for (int k = lane; k <= c.n; k += 64) {
+      double u, w;
+      state_at(st[k], c.in64, &u, &w);
+      L.val[k] = u;
+    }
+    wave_sync();
+    const double uend = L.val[c.n];
+    for (;;) {
+      const int j = j0 + lane;
+      const double z = (double)j / (n - 1) * (a + b) - a;
+      double uj = 2.0 / 3.0 + (z >= 0 ? z * z : -z * z);
+      if (j == n - 1) uj = 1.0;
+      const bool in = j < n && uj <= uend;
+      if (in) {
+        const int k = first_step(L.val, c.n, uj);
+        double up, wp, u, w;
+        state_at(st[k - 1], c.in64, &up, &wp);
+        state_at(st[k], c.in64, &u, &w);
+        const double phi = (c.first + k) * h, phip = (c.first + k - 1) * h, hh = phi - phip;
         double t = (u > up) ? (uj - up) / (u - up) : 1.0;
         for (int it = 0; it < 8; ++it) {
           double r = hermite(t, up, wp, u, w, hh) - uj;
@@ -217,96 +491,127 @@ __global__ void __launch_bounds__(64) k_precompute_D(float* __restrict__ D,
         }
         double ph = phip + t * hh;
         double wj = sqrt(fmax(e2 - uj * uj * (1.0 - uj), 0.0));
-        D[(size_t)j * n + i] = (float)(ph - atan2(uj, wj));
-        Dt[(size_t)j * n + i] =
-            (float)(e * hermite(t, taup, 1.0 / (e + wp), tau, 1.0 / (e + w), hh));
-        ++j;
+        O.D[(size_t)j * n + i] = (float)(ph - atan2(uj, wj));
+        O.Dt[(size_t)j * n + i] = (float)(e * hermite(t, L.tau[k - 1], 1.0 / (e + wp),
+                                                      L.tau[k], 1.0 / (e + w), hh));
       }
-      phip = phi;
-      up = u;
-      wp = w;
-      taup = tau;
+      const int got = __popcll(__ballot(in));
+      j0 += got;
+      if (got < 64) break;
     }
-  }
+    wave_sync();
+  });
 }
 
-__global__ void __launch_bounds__(64) k_precompute_U(float* __restrict__ U,
-                                                     float* __restrict__ Ut, int ne, int nphi,
-                                                     int mode, double band, double step) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= ne) return;
+__device__ void column_U(ColumnLds& L, Integrator& I, const TableOut& O, int i, double e2,
+                         double e, double h) {
+  const int lane = threadIdx.x & 63, ne = O.ne, nphi = O.nphi;
+  const double scale = 3.0 * (1.0 + e2) / (1.0 + 6.0 * e2 * e);  // phi_j = scale * y_j
+  const double phi_last = scale * (double)(nphi - 1) / (nphi - 1);
+  // steps to the first multiple of h at or past the last row
+  const double want = fmin(ceil(phi_last / h), (double)(kMaxSteps - 2));
+  int steps = __builtin_amdgcn_readfirstlane(max((int)want, 1));
+  if (uniform(steps * h < phi_last)) ++steps;
+  int j0 = 1;
+  double tau0 = 0.0;
+  run_column<kPhi>(L, I, h, min(steps, kMaxSteps - 1), [&](const ChunkInfo& c, const float4* st) {
+    tau0 = chunk_tau(st, c, e, h, tau0, L.tau);
+    wave_sync();
+    for (;;) {
+      const int j = j0 + lane;
+      const double phij = scale * (double)j / (nphi - 1);
+      const bool in = j < nphi && phij <= (c.first + c.n) * h;
+      if (in) {
+        int lo = 1, hi = c.n;  // first step whose phi reaches the row
+        while (lo < hi) {
+          const int mid = (lo + hi) >> 1;
+          if ((c.first + mid) * h >= phij)
+            hi = mid;
+          else
+            lo = mid + 1;
+        }
+        double up, wp, u, w;
+        state_at(st[lo - 1], c.in64, &up, &wp);
+        state_at(st[lo], c.in64, &u, &w);
+        const double phi = (c.first + lo) * h, phip = (c.first + lo - 1) * h, hh = phi - phip;
+        const double t = (phij - phip) / hh;
+        const double v = hermite(t, up, wp, u, w, hh);
+        O.U[(size_t)j * ne + i] = (float)fmin(fmax(v, 0.0), 1.0);
+        O.Ut[(size_t)j * ne + i] = (float)(e * hermite(t, L.tau[lo - 1], 1.0 / (e + wp),
+                                                       L.tau[lo], 1.0 / (e + w), hh));
+      }
+      const int got = __popcll(__ballot(in));
+      j0 += got;
+      if (got < 64) break;
+    }
+    double u, w;
+    state_at(st[c.n], c.in64, &u, &w);
+    if (c.last && u >= 1.0)  // fallen in: every later row
+      for (int j = j0 + lane; j < nphi; j += 64) {
+        O.U[(size_t)j * ne + i] = 1.0f;
+        O.Ut[(size_t)j * ne + i] = 0.0f;
+      }
+    wave_sync();
+  });
+}
+
+// Columns 0 .. n - 1 of D, then the ne columns of U, one workgroup each.
+__global__ void __launch_bounds__(128)
+    k_precompute(TableOut O, int mode, double band, double step) {
+  __shared__ ColumnLds L;
+  const int lane = threadIdx.x & 63;
+  const bool reads = threadIdx.x >= 64;
+  Integrator I;
+  I.mode = mode;
+  I.band = band;
+  if ((int)blockIdx.x < O.n) {
+    const int i = blockIdx.x;
+    const double e2 = d_col_e2(O.n, i), e = sqrt(e2);
+    if (reads && lane == 0) {
+      O.D[i] = 0.0f;  // u = 0 at phi = 0: D = 0 - atan2(0, e)
+      O.Dt[i] = 0.0f;
+    }
+    I.e2 = e2;
+    I.init(0.0, e);
+    if (i < O.n / 2)
+      column_D_low(L, I, O, i, e2, e, step / (1.0 + e));
+    else
+      column_D_high(L, I, O, i, e2, e, step / (1.0 + e));
+    return;
+  }
+  const int i = blockIdx.x - O.n, ne = O.ne, nphi = O.nphi;
   if (i == 0) {  // e -> infinity: u = e phi along phi = y / (2e), i.e. u = y / 2; e tau -> 0
-    for (int j = 0; j < nphi; ++j) {
-      U[(size_t)j * ne] = 0.5f * (float)j / (float)(nphi - 1);
-      Ut[(size_t)j * ne] = 0.0f;
+    for (int j = threadIdx.x; j < nphi; j += 128) {
+      O.U[(size_t)j * ne] = 0.5f * (float)j / (float)(nphi - 1);
+      O.Ut[(size_t)j * ne] = 0.0f;
     }
     return;
   }
   if (i == ne - 1) {
     // e = 0: the ray stays at infinity (u = 0) along phi = 3y; e tau tends to tan(phi/2)
     // on a straight ray before its closest point (phi = pi/2), 2/sin(phi) - cot(phi/2) after
-    for (int j = 0; j < nphi; ++j) {
+    for (int j = threadIdx.x; j < nphi; j += 128) {
       double phi = 3.0 * (double)j / (nphi - 1);
-      U[(size_t)j * ne + i] = 0.0f;
-      Ut[(size_t)j * ne + i] =
+      O.U[(size_t)j * ne + i] = 0.0f;
+      O.Ut[(size_t)j * ne + i] =
           (float)(phi <= 0.5 * M_PI ? tan(0.5 * phi) : 2.0 / sin(phi) - 1.0 / tan(0.5 * phi));
     }
     return;
   }
-  double x = (double)i / (ne - 1);
-  double e2 = (1.0 / x - 1.0) / 6.0;
-  double e = sqrt(e2);
-  double scale = 3.0 * (1.0 + e2) / (1.0 + 6.0 * e2 * e);  // phi_j = scale * y_j
-  double h = step / (1.0 + e);
-  Integrator I;
-  I.mode = mode;
-  I.band = band;
-  I.e2 = e2;
-  I.e = e;
-  I.init(0.0, e);
-  U[i] = 0.0f;
-  Ut[i] = 0.0f;
-  int j = 1;
-  double phip = 0.0, up = 0.0, wp = e, taup = 0.0;
-  bool fallen = false;
-  for (int k = 1; k < kMaxSteps && j < nphi; ++k) {
-    I.step(h);
-    double u = I.get_u(), w = I.get_w(), phi = k * h, tau = I.get_tau();
-    while (j < nphi) {
-      double phij = scale * (double)j / (nphi - 1);
-      if (phij > phi) break;
-      double hh = phi - phip;
-      double t = (phij - phip) / hh;
-      double v = hermite(t, up, wp, u, w, hh);
-      U[(size_t)j * ne + i] = (float)fmin(fmax(v, 0.0), 1.0);
-      Ut[(size_t)j * ne + i] =
-          (float)(e * hermite(t, taup, 1.0 / (e + wp), tau, 1.0 / (e + w), hh));
-      ++j;
-    }
-    if (u >= 1.0) {
-      fallen = true;
-      break;
-    }
-    phip = phi;
-    up = u;
-    wp = w;
-    taup = tau;
+  const double x = (double)i / (ne - 1), e2 = (1.0 / x - 1.0) / 6.0, e = sqrt(e2);
+  if (reads && lane == 0) {
+    O.U[i] = 0.0f;
+    O.Ut[i] = 0.0f;
   }
-  if (fallen)
-    for (; j < nphi; ++j) {
-      U[(size_t)j * ne + i] = 1.0f;
-      Ut[(size_t)j * ne + i] = 0.0f;
-    }
+  I.e2 = e2;
+  I.init(0.0, e);
+  column_U(L, I, O, i, e2, e, step / (1.0 + e));
 }
 
 hipError_t launch_precompute(float* D, float* Dt, int d_n, float* U, float* Ut, int u_ne,
                              int u_nphi, int mode, double band, double step, hipStream_t s) {
-  hipLaunchKernelGGL(k_precompute_D, dim3((d_n + 63) / 64), dim3(64), 0, s, D, Dt, d_n, mode,
-                     band, step);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_precompute_U, dim3((u_ne + 63) / 64), dim3(64), 0, s, U, Ut, u_ne,
-                     u_nphi, mode, band, step);
+  const TableOut O{D, Dt, U, Ut, d_n, u_ne, u_nphi};
+  hipLaunchKernelGGL(k_precompute, dim3(d_n + u_ne), dim3(128), 0, s, O, mode, band, step);
   return hipGetLastError();
 }
 
