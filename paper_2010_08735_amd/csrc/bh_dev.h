@@ -53,6 +53,29 @@ struct StarsDev {
 };
 static_assert(sizeof(StarsDev) == 72, "the star-map record keeps the view record's layout");
 
+// One star-map build (stars.hip).  Levels 0 .. tl lie inside 2^tl x 2^tl tiles, the later ones
+// are formed from the tiles' topmost texels in `tail` (levels tl, tl + 1, ... back to back).
+constexpr int kStarMaxLevels = 14;  // face sizes to 8192
+struct StarBuild {
+  const float* dirs;
+  const float* inten;    // intensities, or (R, G, B) of a band map
+  const float* temp;     // (I, T) maps only
+  int* order;            // star indices in tile order
+  int* start;            // first slot of each tile in `order`, then their end
+  int* next;             // star lists beyond the stars kept in LDS
+  float* tilemax;        // the tiles' maxima per level
+  float* tail;
+  unsigned* maxbits;     // per level, zero before
+  void* out;
+  float* scale;
+  uint32_t* occ;
+  uint32_t* level_off_dev;
+  uint32_t* occ_off_dev;
+  int64_t occ_words, tail_texels;  // tail_texels: levels tl + 1 and later
+  int n0, levels, tl, tiles, fp16;
+  uint32_t off[kStarMaxLevels + 1], ooff[kStarMaxLevels + 1];  // texels, occupancy words
+};
+
 // ---- area-source map (nebulae, galaxies) ----------------------------------------------
 // (I, I T) per texel: radiance and radiance-weighted colour temperature; level L (size
 // n0 >> L, n0 a power of two) starts at texel 8 (n0^2 - nL^2), within it face-major rows.

@@ -30,27 +30,17 @@ hipError_t launch_precompute(float* D, float* Dt, int d_n, float* U, float* Ut, 
 hipError_t launch_band_lut(float4* lut, int n, float x0, float dx, hipStream_t s);
 hipError_t launch_band_eval(const LutDev& L, const float* temps, int64_t n, float* out,
                             hipStream_t s);
-hipError_t launch_star_build(const float* dirs, const float* inten, const float* temp, int64_t n,
-                             int n0, int levels, const uint32_t* level_off_host, int* head,
-                             int* next, float2* pos, float4* master, unsigned* maxbits,
-                             float* scale, int fp16, void* out, hipStream_t s);
+int star_tile_log(int n0);
+size_t star_tail_texel_bytes(int bands);
+size_t star_tile_max_bytes();
+hipError_t launch_star_count(const float* dirs, const float* inten, const float* temp, int64_t n,
+                             int n0, int bands, unsigned long long* acc, int* bad, int* count,
+                             hipStream_t s);
+hipError_t launch_star_build(const StarBuild& B, int* count, int64_t n, int bands,
+                             hipStream_t s);
 hipError_t launch_fill_int(int* p, int64_t n, int v, hipStream_t s);
-hipError_t launch_star_hash(const float* dirs, const float* inten, const float* temp, int64_t n,
-                            unsigned long long* acc, hipStream_t s);
-hipError_t launch_star_occupancy(const void* tex, int n0, int levels, const uint32_t* level_off,
-                                 const uint32_t* occ_off, int fp16, uint32_t* occ,
-                                 hipStream_t s);
 hipError_t launch_star_unpack(const void* in, int64_t count, float scale, int fp16, float4* out,
                               hipStream_t s);
-hipError_t launch_star_build_bands(const float* dirs, const float* rgb, int64_t n, int n0,
-                                   int levels, const uint32_t* level_off_host, int* head,
-                                   int* next, float2* pos, float4* master, unsigned* maxbits,
-                                   float* scale, int fp16, void* out, int* bad, hipStream_t s);
-hipError_t launch_star_hash_bands(const float* dirs, const float* rgb, int64_t n,
-                                  unsigned long long* acc, hipStream_t s);
-hipError_t launch_star_occupancy_bands(const void* tex, int n0, int levels,
-                                       const uint32_t* level_off, const uint32_t* occ_off,
-                                       int fp16, uint32_t* occ, hipStream_t s);
 hipError_t launch_star_unpack_bands(const void* in, int64_t count, float scale, int fp16,
                                     float4* out, hipStream_t s);
 hipError_t launch_render(int cfg, const ViewDev& v, const TablesDev& T, const LutDev& L,
@@ -742,31 +732,73 @@ static bh_status build_stars(bh_ctx* c, const float* dir_xyz_dev, const float* i
     bh_status st = ensure_cshift(c, hs);  // band maps are received through the table
     if (st) return st;
   }
-  // content hash of the arrays (ordered after the caller's work on the stream)
-  uint64_t hash = 0;
+  StarBuild B{};
+  B.dirs = dir_xyz_dev;
+  B.inten = intensity_dev;
+  B.temp = temperature_dev;
+  B.n0 = n0;
+  B.tl = star_tile_log(n0);
+  B.tiles = 6 * (n0 >> B.tl) * (n0 >> B.tl);
+  // scratch of the build, one allocation: the hash, the bad-value flag and the level maxima
+  // (cleared together with the tile counts), the tile starts, the star order and lists, the
+  // tiles' maxima and topmost texels
+  uint64_t tail_all = 0;
+  for (int l = B.tl; (n0 >> l) >= 1; ++l) tail_all += 6ull * (n0 >> l) * (n0 >> l);
+  const size_t nstars = (size_t)std::max<int64_t>(n, 1);
+  size_t bytes = 0;
+  auto take = [&](size_t b) {
+    const size_t at = bytes;
+    bytes += (b + 15) & ~(size_t)15;
+    return at;
+  };
+  const size_t o_acc = take(16), o_max = take(sizeof(unsigned) * 16);
+  const size_t o_count = take(sizeof(int) * (size_t)B.tiles), cleared = bytes;
+  const size_t o_start = take(sizeof(int) * ((size_t)B.tiles + 1));
+  const size_t o_order = take(sizeof(int) * nstars), o_next = take(sizeof(int) * nstars);
+  const size_t o_tmax = take(star_tile_max_bytes() * (size_t)B.tiles);
+  const size_t o_tail = take(star_tail_texel_bytes(bands) * (size_t)tail_all);
+  char* scratch = nullptr;
+  bh_status st = dev_alloc(c, bytes, (void**)&scratch);
+  // no room to build: the hash alone, since a resident map needs no scratch
+  const bool only_hash = st != BH_OK;
+  const std::string no_room = g_err;
+  if (only_hash) {
+    bytes = 16;
+    st = dev_alloc(c, bytes, (void**)&scratch);
+    if (st) return st;
+  }
+  struct Guard {  // gives the scratch back on every way out
+    bh_ctx* c;
+    char* p;
+    size_t bytes;
+    ~Guard() { dev_free(c, p, bytes); }
+  } guard{c, scratch, bytes};
+  unsigned long long* acc = (unsigned long long*)(scratch + o_acc);
+  int* count = (int*)(scratch + o_count);
+  // content hash and tile counts of the arrays (ordered after the caller's work on the stream)
+  struct {
+    unsigned long long hash;
+    int bad, pad;
+  } first = {0, 0, 0};
   {
-    unsigned long long* acc = nullptr;
-    bh_status hst = dev_alloc(c, sizeof(unsigned long long), (void**)&acc);
-    if (hst) return hst;
-    hipError_t e = hipMemsetAsync(acc, 0, sizeof(unsigned long long), hs);
+    hipError_t e = launch_fill_int((int*)scratch,
+                                   (int64_t)(std::min(cleared, bytes) / sizeof(int)), 0, hs);
     if (e == hipSuccess)
-      e = bands ? launch_star_hash_bands(dir_xyz_dev, intensity_dev, n, acc, hs)
-                : launch_star_hash(dir_xyz_dev, intensity_dev, temperature_dev, n, acc, hs);
-    unsigned long long h = 0;
-    if (e == hipSuccess) e = hipMemcpyAsync(&h, acc, sizeof(h), hipMemcpyDeviceToHost, hs);
+      e = launch_star_count(dir_xyz_dev, intensity_dev, temperature_dev, n, n0, bands, acc,
+                            (int*)(acc + 1), only_hash ? nullptr : count, hs);
+    if (e == hipSuccess) e = hipMemcpyAsync(&first, acc, 16, hipMemcpyDeviceToHost, hs);
     if (e == hipSuccess) e = hipStreamSynchronize(hs);
-    dev_free(c, acc, sizeof(unsigned long long));
     if (e != hipSuccess) return fail(BH_EDEVICE, std::string("star hash: ") + hipGetErrorString(e));
-    hash = h;
   }
   std::lock_guard<std::mutex> g(c->mu);
-  StarKey key{hash, n, n0, texel_format, bands};
+  StarKey key{first.hash, n, n0, texel_format, bands};
   auto found = c->stars.find(key);
   if (found != c->stars.end()) {
     found->second->refs++;
     *out = found->second;
     return BH_OK;
   }
+  if (only_hash) return fail(BH_ENOMEM, no_room);
   int levels = 0;
   while ((n0 >> levels) >= 1) ++levels;
   std::vector<uint32_t> off(levels), ooff(levels);
@@ -791,61 +823,38 @@ static bh_status build_stars(bh_ctx* c, const float* dir_xyz_dev, const float* i
   s->occ_off = ooff;
   size_t btex = tsz * total, bsc = sizeof(float) * levels, boff = sizeof(uint32_t) * levels;
   size_t bocc = sizeof(uint32_t) * owords;
-  bh_status st = dev_alloc(c, btex, &s->tex);
+  st = dev_alloc(c, btex, &s->tex);
   if (!st) st = dev_alloc(c, bsc, (void**)&s->scale);
   if (!st) st = dev_alloc(c, boff, (void**)&s->level_off_dev);
   if (!st) st = dev_alloc(c, bocc, (void**)&s->occ);
   if (!st) st = dev_alloc(c, boff, (void**)&s->occ_off_dev);
   s->occ_bytes = bocc;
-  // build scratch (freed below)
-  int64_t ntex0 = 6ll * n0 * n0;
-  size_t bhead = sizeof(int) * ntex0, bnext = sizeof(int) * std::max<int64_t>(n, 1),
-         bpos = sizeof(float2) * std::max<int64_t>(n, 1),
-         bmaster = sizeof(float4) * total * (bands ? 2 : 1), bmax = sizeof(unsigned) * 64;
-  int* head = nullptr;
-  int* next = nullptr;
-  float2* pos = nullptr;
-  float4* master = nullptr;
-  unsigned* maxbits = nullptr;
-  int* bad = nullptr;
-  if (!st) st = dev_alloc(c, bhead, (void**)&head);
-  if (!st) st = dev_alloc(c, bnext, (void**)&next);
-  if (!st) st = dev_alloc(c, bpos, (void**)&pos);
-  if (!st) st = dev_alloc(c, bmaster, (void**)&master);
-  if (!st) st = dev_alloc(c, bmax, (void**)&maxbits);
-  if (!st && bands) st = dev_alloc(c, sizeof(int), (void**)&bad);
   hipError_t e = hipSuccess;
-  int hbad = 0;
-  if (!st) {
-    e = hipMemcpyAsync(s->level_off_dev, off.data(), boff, hipMemcpyHostToDevice, hs);
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(s->occ_off_dev, ooff.data(), boff, hipMemcpyHostToDevice, hs);
-    if (e == hipSuccess) e = launch_fill_int(head, ntex0, -1, hs);
-    if (e == hipSuccess) e = launch_fill_int((int*)maxbits, 64, 0, hs);
-    if (e == hipSuccess && bands) e = launch_fill_int(bad, 1, 0, hs);
-    if (e == hipSuccess)
-      e = bands ? launch_star_build_bands(dir_xyz_dev, intensity_dev, n, n0, levels, off.data(),
-                                          head, next, pos, master, maxbits, s->scale, fp16,
-                                          s->tex, bad, hs)
-                : launch_star_build(dir_xyz_dev, intensity_dev, temperature_dev, n, n0, levels,
-                                    off.data(), head, next, pos, master, maxbits, s->scale, fp16,
-                                    s->tex, hs);
-    if (e == hipSuccess)
-      e = bands ? launch_star_occupancy_bands(s->tex, n0, levels, off.data(), ooff.data(), fp16,
-                                              s->occ, hs)
-                : launch_star_occupancy(s->tex, n0, levels, off.data(), ooff.data(), fp16,
-                                        s->occ, hs);
-    if (e == hipSuccess && bands)
-      e = hipMemcpyAsync(&hbad, bad, sizeof(int), hipMemcpyDeviceToHost, hs);
+  if (!st && !first.bad) {
+    B.order = (int*)(scratch + o_order);
+    B.start = (int*)(scratch + o_start);
+    B.next = (int*)(scratch + o_next);
+    B.tilemax = (float*)(scratch + o_tmax);
+    B.tail = (float*)(scratch + o_tail);
+    B.maxbits = (unsigned*)(scratch + o_max);
+    B.out = s->tex;
+    B.scale = s->scale;
+    B.occ = s->occ;
+    B.level_off_dev = s->level_off_dev;
+    B.occ_off_dev = s->occ_off_dev;
+    B.occ_words = (int64_t)owords;
+    B.levels = levels;
+    B.fp16 = fp16;
+    for (int l = 0; l < levels; ++l) {
+      B.off[l] = off[l];
+      B.ooff[l] = ooff[l];
+    }
+    B.off[levels] = (uint32_t)total;
+    B.tail_texels = (int64_t)total - B.off[B.tl + 1];
+    e = launch_star_build(B, count, n, bands, hs);
     if (e == hipSuccess) e = hipStreamSynchronize(hs);
   }
-  dev_free(c, head, head ? bhead : 0);
-  dev_free(c, next, next ? bnext : 0);
-  dev_free(c, pos, pos ? bpos : 0);
-  dev_free(c, master, master ? bmaster : 0);
-  dev_free(c, maxbits, maxbits ? bmax : 0);
-  dev_free(c, bad, bad ? sizeof(int) : 0);
-  if (st || e != hipSuccess || hbad) {
+  if (st || e != hipSuccess || first.bad) {
     dev_free(c, s->tex, s->tex ? btex : 0);
     dev_free(c, s->scale, s->scale ? bsc : 0);
     dev_free(c, s->level_off_dev, s->level_off_dev ? boff : 0);

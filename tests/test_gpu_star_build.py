@@ -1,0 +1,129 @@
+"""Star maps at the edges of the build's tiling, against the same merge in numpy: faces smaller
+than a tile, one tile a face and many, occupancy words shared by tiles, tiles with more stars
+than fit in LDS, many stars in one texel, unlit stars, and an empty field."""
+import numpy as np
+import pytest
+
+from paper_2010_08735_amd import bh, scenes
+
+pytestmark = pytest.mark.gpu
+
+
+def _place(dirs, n0):
+    """Level-0 texel and position of each direction, in float32 as the map's definition."""
+    a = np.abs(dirs)
+    k = np.where(a[:, 1] > a[:, 0], 1, 0)
+    k = np.where(a[:, 2] > np.maximum(a[:, 0], a[:, 1]), 2, k)
+    i = np.arange(len(dirs))
+    m = a[i, k]
+    face = 2 * k + (dirs[i, k] < 0)
+    g = [np.float32(0.5) * (dirs[i, (k + j) % 3] / m + np.float32(1)) * np.float32(n0)
+         for j in (1, 2)]
+    c = [np.clip(np.floor(x).astype(np.int64), 0, n0 - 1) for x in g]
+    return (face * n0 + c[1]) * n0 + c[0], g[0] - c[0].astype(np.float32), \
+        g[1] - c[1].astype(np.float32)
+
+
+def _levels(dirs, channels, weight, n0):
+    """(texels, channels + 2) sums per level: channels, weight u, weight v."""
+    key, pu, pv = _place(dirs, n0)
+    lev = np.zeros((6 * n0 * n0, channels.shape[1] + 2))
+    np.add.at(lev, key, np.concatenate([channels, (weight * pu)[:, None],
+                                        (weight * pv)[:, None]], 1))
+    return lev
+
+
+def _field(n, n0, kind, seed):
+    rng = np.random.default_rng(seed)
+    f = scenes.star_field(max(n, 1), seed)
+    d, inten, temp = f.dirs[:n].copy(), f.intensity[:n].copy(), f.temperature[:n].copy()
+    if kind == "clustered" and n:
+        d[: n // 2] = d[0] + rng.normal(0, 0.02, (n // 2, 3)).astype(np.float32)
+        d[: n // 40] = d[1]  # many stars in one texel
+        inten[::17] = 0.0    # unlit
+        d[3] = 0.0           # no direction
+    return d, inten, temp
+
+
+CASES = [(1, 50, "plain"), (2, 50, "plain"), (4, 300, "plain"), (16, 3000, "plain"),
+         (32, 3000, "clustered"), (64, 30000, "clustered"), (512, 20000, "clustered"),
+         (1024, 40000, "clustered"), (2048, 5000, "plain"), (64, 0, "plain")]
+
+
+@pytest.mark.parametrize("n0,n,kind", CASES)
+@pytest.mark.parametrize("bands", [False, True])
+def test_star_map_levels_match_numpy(gpu_ctx, n0, n, kind, bands):
+    import torch
+    d, inten, temp = _field(n, n0, kind, 5)
+    one = np.zeros((1, 3), np.float32)
+    dd = torch.from_numpy(d if n else one).cuda()
+    if bands:
+        col = np.random.default_rng(3).uniform(0.1, 1.0, (n, 3)).astype(np.float32)
+        rgb = (inten[:, None] * col).astype(np.float32)
+        tt = torch.from_numpy(rgb if n else one).cuda()
+        h = bh.bh_build_star_bands(gpu_ctx, dd.data_ptr(), tt.data_ptr(), n, n0,
+                                   bh.BH_TEXEL_FP32, bh.current_stream())
+        ch, w = rgb.astype(np.float64), rgb.astype(np.float64).sum(1)
+    else:
+        ii, tt = (torch.from_numpy(x if n else one[0]).cuda() for x in (inten, temp))
+        h = bh.bh_build_stars(gpu_ctx, dd.data_ptr(), ii.data_ptr(), tt.data_ptr(), n, n0,
+                              bh.BH_TEXEL_FP32, bh.current_stream())
+        w = inten.astype(np.float64)
+        ch = np.stack([w, w * temp], 1)
+    ok = (w > 0) & (np.abs(d).max(1, initial=0) > 0)
+    lev = _levels(d[ok], ch[ok], w[ok], n0)
+    nl, level, per = n0, 0, 8 if bands else 4
+    while True:
+        got = np.full((6 * nl * nl, per), np.nan, np.float32)
+        bh.bh_stars_download(h, level, got.ctypes.data)
+        S = lev[:, :3].sum(1) if bands else lev[:, 0]
+        lit, s = S > 0, np.where(S > 0, S, 1.0)
+        want = np.concatenate([lev[:, :3] if bands else np.stack([S, lev[:, 1] / s], 1),
+                               lev[:, -2:] / s[:, None]], 1)
+        assert not got[~lit].any() and not got[:, want.shape[1]:].any()
+        # each level rounds its texels to FP32 (2^-24 relative) from the level below's
+        np.testing.assert_allclose(got[:, :want.shape[1]][lit], want[lit],
+                                   rtol=2.0 ** -23 * (level + 1), atol=2.0 ** -23 * (level + 1))
+        if nl == 1:
+            break
+        q = lev.reshape(6, nl // 2, 2, nl // 2, 2, -1)
+        up = 0.0
+        for y in (0, 1):
+            for x in (0, 1):
+                c = q[:, :, y, :, x].copy()
+                cs = c[..., :3].sum(-1) if bands else c[..., 0]
+                c[..., -2] = 0.5 * (x * cs + c[..., -2])
+                c[..., -1] = 0.5 * (y * cs + c[..., -1])
+                up = up + c
+        nl, level = nl // 2, level + 1
+        lev = up.reshape(6 * nl * nl, -1)
+    bh.bh_release_stars(h)
+
+
+@pytest.mark.parametrize("n0", [2, 16, 32, 64, 256])
+@pytest.mark.parametrize("fmt", [bh.BH_TEXEL_FP16, bh.BH_TEXEL_FP32])
+def test_every_star_is_found_by_a_frame(gpu_ctx, gpu_tables, orc, orc_tables, n0, fmt):
+    """The occupancy bits (words that tiles share, guard words, paired rows): a frame of the
+    whole map's stars against the oracle."""
+    import torch
+    field = scenes.star_field(6 * n0 * n0 // 3 + 4, 11)
+    d, i, t = (torch.from_numpy(a).cuda() for a in (field.dirs, field.intensity,
+                                                    field.temperature))
+    h = bh.bh_build_stars(gpu_ctx, d.data_ptr(), i.data_ptr(), t.data_ptr(), len(field), n0,
+                          fmt, bh.current_stream())
+    cube = orc.cubemap(field, n0)
+    for aim in ((0.3, 1.0), (2.6, 4.1)):
+        v = scenes.small_static_view()
+        v.width, v.height, v.fov_y = 61, 47, 1.9
+        v.cam_rot = scenes.look_rotation(scenes.spherical_position(1.0, *aim))
+        out = torch.full((47, 61, 4), -1.0, device="cuda")
+        bh.bh_render(gpu_ctx, gpu_tables, bh.make_view(v, h), out.data_ptr(), None,
+                     bh.current_stream())
+        px = orc.render_quads(v, scenes.all_quads(61, 47), cube=cube, n0=n0, tables=orc_tables)
+        px = px[(px["x"] < 61) & (px["y"] < 47) & (px["n_cross"] == 0) & (px["star_zeroed"] == 0)]
+        g, o = out.cpu().numpy()[px["y"], px["x"], :3], px["rgb"]
+        # the escape angle is FP32 (~2e-6 rad, pixels are 4e-2 rad) and FP16 positions are
+        # within 2^-12 texel: tent weights move by less than 1e-3 of the brightest neighbour
+        err = np.abs(g - o).max(1) / np.maximum(o.max(1), 1e-2 * o.max())
+        assert np.percentile(err, 98) < 5e-3, float(np.percentile(err, 98))
+    bh.bh_release_stars(h)
