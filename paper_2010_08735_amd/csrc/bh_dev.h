@@ -60,8 +60,9 @@ struct StarBuild {
   const float* dirs;
   const float* inten;    // intensities, or (R, G, B) of a band map
   const float* temp;     // (I, T) maps only
-  int* order;            // star indices in tile order
-  int* start;            // first slot of each tile in `order`, then their end
+  int* order;            // star indices in bin order
+  uint32_t* where;       // their texels inside the bin
+  int* start;            // first slot of each bin in `order`, then their end
   int* next;             // star lists beyond the stars kept in LDS
   float* tilemax;        // the tiles' maxima per level
   float* tail;
@@ -72,7 +73,7 @@ struct StarBuild {
   uint32_t* level_off_dev;
   uint32_t* occ_off_dev;
   int64_t occ_words, tail_texels;  // tail_texels: levels tl + 1 and later
-  int n0, levels, tl, tiles, fp16;
+  int n0, levels, tl, tiles, bl, bins, fp16;  // a bin: a square of 2^(bl - tl) tiles an edge
   uint32_t off[kStarMaxLevels + 1], ooff[kStarMaxLevels + 1];  // texels, occupancy words
 };
 

@@ -31,6 +31,7 @@ hipError_t launch_band_lut(float4* lut, int n, float x0, float dx, hipStream_t s
 hipError_t launch_band_eval(const LutDev& L, const float* temps, int64_t n, float* out,
                             hipStream_t s);
 int star_tile_log(int n0);
+int star_bin_log(int n0);
 size_t star_tail_texel_bytes(int bands);
 size_t star_tile_max_bytes();
 hipError_t launch_star_count(const float* dirs, const float* inten, const float* temp, int64_t n,
@@ -739,8 +740,10 @@ static bh_status build_stars(bh_ctx* c, const float* dir_xyz_dev, const float* i
   B.n0 = n0;
   B.tl = star_tile_log(n0);
   B.tiles = 6 * (n0 >> B.tl) * (n0 >> B.tl);
+  B.bl = star_bin_log(n0);
+  B.bins = 6 * (n0 >> B.bl) * (n0 >> B.bl);
   // scratch of the build, one allocation: the hash, the bad-value flag and the level maxima
-  // (cleared together with the tile counts), the tile starts, the star order and lists, the
+  // (cleared together with the bin counts), the bin starts, the star order and lists, the
   // tiles' maxima and topmost texels
   uint64_t tail_all = 0;
   for (int l = B.tl; (n0 >> l) >= 1; ++l) tail_all += 6ull * (n0 >> l) * (n0 >> l);
@@ -752,9 +755,10 @@ static bh_status build_stars(bh_ctx* c, const float* dir_xyz_dev, const float* i
     return at;
   };
   const size_t o_acc = take(16), o_max = take(sizeof(unsigned) * 16);
-  const size_t o_count = take(sizeof(int) * (size_t)B.tiles), cleared = bytes;
-  const size_t o_start = take(sizeof(int) * ((size_t)B.tiles + 1));
-  const size_t o_order = take(sizeof(int) * nstars), o_next = take(sizeof(int) * nstars);
+  const size_t o_count = take(sizeof(int) * (size_t)B.bins), cleared = bytes;
+  const size_t o_start = take(sizeof(int) * ((size_t)B.bins + 1));
+  const size_t o_order = take(sizeof(int) * nstars), o_where = take(sizeof(uint32_t) * nstars);
+  const size_t o_next = take(sizeof(int) * nstars);
   const size_t o_tmax = take(star_tile_max_bytes() * (size_t)B.tiles);
   const size_t o_tail = take(star_tail_texel_bytes(bands) * (size_t)tail_all);
   char* scratch = nullptr;
@@ -775,7 +779,7 @@ static bh_status build_stars(bh_ctx* c, const float* dir_xyz_dev, const float* i
   } guard{c, scratch, bytes};
   unsigned long long* acc = (unsigned long long*)(scratch + o_acc);
   int* count = (int*)(scratch + o_count);
-  // content hash and tile counts of the arrays (ordered after the caller's work on the stream)
+  // content hash and bin counts of the arrays (ordered after the caller's work on the stream)
   struct {
     unsigned long long hash;
     int bad, pad;
@@ -832,6 +836,7 @@ static bh_status build_stars(bh_ctx* c, const float* dir_xyz_dev, const float* i
   hipError_t e = hipSuccess;
   if (!st && !first.bad) {
     B.order = (int*)(scratch + o_order);
+    B.where = (uint32_t*)(scratch + o_where);
     B.start = (int*)(scratch + o_start);
     B.next = (int*)(scratch + o_next);
     B.tilemax = (float*)(scratch + o_tmax);

@@ -16,8 +16,8 @@
 // from the level's largest band value, or the same eight values in FP32.
 //
 // Build.  The level-0 map is cut into square tiles (64 x 64 texels, 32 x 32 on small maps) and
-// the stars are sorted by tile (count, scan, scatter).  One workgroup then owns a tile: it
-// lists its stars per texel in LDS, merges them, and forms every mip level that fits inside
+// the stars are sorted into bins of one or more tiles (count, scan, scatter).  One workgroup
+// then owns a tile: it picks its stars from the bin, lists them per texel in LDS, merges them, and forms every mip level that fits inside
 // the tile, so no level ever goes through memory.  The FP16 scales need each level's maximum
 // first: a first pass over the tiles only finds the maxima and the tiles' topmost texels, from
 // which k_star_tail forms the remaining levels; a second pass merges again (the stars are few
@@ -82,12 +82,17 @@ __device__ __forceinline__ Place place_star(const float* __restrict__ dirs,
   return p;
 }
 
-__device__ __forceinline__ int tile_of(const Place& p, int n0, int tl) {
-  const int nt = n0 >> tl;
-  return (p.face * nt + (p.iy >> tl)) * nt + (p.ix >> tl);
+// bin of a star, and its texel inside the bin (column low, row high)
+__device__ __forceinline__ int bin_of(const Place& p, int n0, int bl) {
+  const int nb = n0 >> bl;
+  return (p.face * nb + (p.iy >> bl)) * nb + (p.ix >> bl);
+}
+__device__ __forceinline__ uint32_t bin_texel(const Place& p, int bl) {
+  const int mask = (1 << bl) - 1;
+  return (uint32_t)(p.ix & mask) | ((uint32_t)(p.iy & mask) << 16);
 }
 
-// ---- content hash and tile counts -----------------------------------------------------------
+// ---- content hash and bin counts ------------------------------------------------------------
 
 // Content hash of a star field, the key under which its maps are shared: every star
 // contributes a 64-bit mix of its index and the bit patterns of its values, and the
@@ -119,35 +124,34 @@ __device__ __forceinline__ uint64_t star_hash(const float* __restrict__ dirs,
   return h;
 }
 
-// Stars per workgroup of the sorting kernels (16 per thread), and the most tiles whose counts
-// they keep in LDS first: one global atomic per tile and workgroup instead of one per star.
-// With more tiles (6 x 2048^2 has 6144) a tile gets few stars and the counters do not
-// contend; with 96 tiles and 10^6 stars 10^4 atomics would queue on each (~12 ns apart).
-constexpr int kSortThreads = 256, kSortPer = 16, kSortStars = kSortThreads * kSortPer;
-constexpr int kLdsTiles = 2048;
+// The sorting kernels keep their counts in LDS and add them to the bins' with one global
+// atomic per bin and workgroup.  Few large workgroups (16 stars a thread, 16 384 each) and at
+// most kMaxBins bins keep those few: 10^6 stars straight onto the 6144 tiles of 6 x 2048^2
+// were 10^6 scattered device atomics, 65 us a pass; onto the 96 of 6 x 256^2, 10^4 queued on
+// each counter.
+constexpr int kSortThreads = 1024, kSortPer = 16, kSortStars = kSortThreads * kSortPer;
+constexpr int kMaxBins = 1536;
 
-// Hash of the field, stars per tile (unless `count` is null), and whether a band value is
+// Hash of the field, stars per bin (unless `count` is null), and whether a band value is
 // negative, infinite or NaN (which fails the whole build).  One 64-bit atomic per workgroup:
 // one per wave queued 15 600 of them on the same address, 192 us for 10^6 stars.
 template <bool BANDS>
 __global__ void __launch_bounds__(kSortThreads)
     k_star_count(const float* __restrict__ dirs, const float* __restrict__ inten,
-                 const float* __restrict__ temp, int64_t n, int n0, int tl, int tiles,
+                 const float* __restrict__ temp, int64_t n, int n0, int bl, int bins,
                  unsigned long long* __restrict__ acc, int* __restrict__ bad,
                  int* __restrict__ count) {
-  __shared__ int hist[kLdsTiles];
+  __shared__ int hist[kMaxBins];
   __shared__ unsigned long long wsum[kSortThreads / 64];
-  const bool lds = count && tiles <= kLdsTiles;
-  if (lds) {
-    for (int b = threadIdx.x; b < tiles; b += kSortThreads) hist[b] = 0;
-    __syncthreads();
-  }
+  for (int b = threadIdx.x; b < bins; b += kSortThreads) hist[b] = 0;
+  __syncthreads();
   const int64_t first = (int64_t)blockIdx.x * kSortStars + threadIdx.x;
   uint64_t h = 0;
   bool any_bad = false;
+#pragma unroll 4
   for (int q = 0; q < kSortPer; ++q) {
     const int64_t s = first + q * kSortThreads;
-    if (s >= n) break;
+    if (s >= n) continue;
     h += star_hash<BANDS>(dirs, inten, temp, s);
     if constexpr (BANDS) {
       const float r = inten[3 * s], g = inten[3 * s + 1], b = inten[3 * s + 2];
@@ -156,7 +160,7 @@ __global__ void __launch_bounds__(kSortThreads)
     }
     if (!count) continue;
     const Place p = place_star<BANDS>(dirs, inten, s, n0);
-    if (p.lit) atomicAdd(lds ? &hist[tile_of(p, n0, tl)] : &count[tile_of(p, n0, tl)], 1);
+    if (p.lit) atomicAdd(&hist[bin_of(p, n0, bl)], 1);
   }
   if (any_bad) atomicOr(bad, 1);
   for (int o = 32; o > 0; o >>= 1) h += __shfl_xor(h, o);
@@ -167,21 +171,19 @@ __global__ void __launch_bounds__(kSortThreads)
     for (int w = 0; w < kSortThreads / 64; ++w) t += wsum[w];
     atomicAdd(acc, t);
   }
-  if (lds)
-    for (int b = threadIdx.x; b < tiles; b += kSortThreads)
+  if (count)
+    for (int b = threadIdx.x; b < bins; b += kSortThreads)
       if (hist[b]) atomicAdd(&count[b], hist[b]);
 }
 
-// start[b] = stars in the tiles before b (start[tiles] = all); `count` becomes the scatter's
-// cursors, the same values.  One workgroup (at most 98 304 tiles).
+// start[b] = stars in the bins before b (start[bins] = all); `count` becomes the scatter's
+// cursors, the same values.  One workgroup, at most 2 bins a thread.
 __global__ void __launch_bounds__(1024)
-    k_star_scan(int* __restrict__ count, int* __restrict__ start, int tiles) {
+    k_star_scan(int* __restrict__ count, int* __restrict__ start, int bins) {
   __shared__ int part[1024];
-  const int t = threadIdx.x, per = (tiles + 1023) / 1024;
-  const int b0 = min(t * per, tiles), b1 = min(b0 + per, tiles);
-  int sum = 0;
-  for (int b = b0; b < b1; ++b) sum += count[b];
-  part[t] = sum;
+  const int t = threadIdx.x, b = 2 * t;
+  const int c0 = b < bins ? count[b] : 0, c1 = b + 1 < bins ? count[b + 1] : 0;
+  part[t] = c0 + c1;
   __syncthreads();
   for (int o = 1; o < 1024; o <<= 1) {
     const int v = t >= o ? part[t - o] : 0;
@@ -189,56 +191,48 @@ __global__ void __launch_bounds__(1024)
     part[t] += v;
     __syncthreads();
   }
-  int at = part[t] - sum;
-  for (int b = b0; b < b1; ++b) {
-    const int c = count[b];
-    start[b] = at;
-    count[b] = at;
-    at += c;
-  }
-  if (t == 1023) start[tiles] = part[1023];
+  const int at = part[t] - c0 - c1;
+  if (b < bins) start[b] = count[b] = at;
+  if (b + 1 < bins) start[b + 1] = count[b + 1] = at + c0;
+  if (t == 1023) start[bins] = part[1023];
 }
 
-// star indices in tile order (any order inside a tile: the merge sorts)
+// star indices and their texels in bin order (any order inside a bin: the merge sorts)
 template <bool BANDS>
 __global__ void __launch_bounds__(kSortThreads)
     k_star_scatter(const float* __restrict__ dirs, const float* __restrict__ inten, int64_t n,
-                   int n0, int tl, int tiles, int* __restrict__ cursor,
-                   int* __restrict__ order) {
-  __shared__ int hist[kLdsTiles];
-  const bool lds = tiles <= kLdsTiles;
+                   int n0, int bl, int bins, int* __restrict__ cursor, int* __restrict__ order,
+                   uint32_t* __restrict__ where) {
+  __shared__ int hist[kMaxBins];
   const int64_t first = (int64_t)blockIdx.x * kSortStars + threadIdx.x;
-  if (!lds) {
-    for (int q = 0; q < kSortPer; ++q) {
-      const int64_t s = first + q * kSortThreads;
-      if (s >= n) break;
-      const Place p = place_star<BANDS>(dirs, inten, s, n0);
-      if (p.lit) order[atomicAdd(&cursor[tile_of(p, n0, tl)], 1)] = (int)s;
-    }
-    return;
-  }
-  for (int b = threadIdx.x; b < tiles; b += kSortThreads) hist[b] = 0;
+  for (int b = threadIdx.x; b < bins; b += kSortThreads) hist[b] = 0;
   __syncthreads();
-  int tile[kSortPer], rank[kSortPer];
+  int bin[kSortPer], rank[kSortPer];
+  uint32_t texel[kSortPer];
 #pragma unroll
   for (int q = 0; q < kSortPer; ++q) {
     const int64_t s = first + q * kSortThreads;
-    tile[q] = -1;
+    bin[q] = -1;
     if (s >= n) continue;
     const Place p = place_star<BANDS>(dirs, inten, s, n0);
     if (!p.lit) continue;
-    tile[q] = tile_of(p, n0, tl);
-    rank[q] = atomicAdd(&hist[tile[q]], 1);
+    bin[q] = bin_of(p, n0, bl);
+    texel[q] = bin_texel(p, bl);
+    rank[q] = atomicAdd(&hist[bin[q]], 1);
   }
   __syncthreads();
-  for (int b = threadIdx.x; b < tiles; b += kSortThreads) {
+  for (int b = threadIdx.x; b < bins; b += kSortThreads) {
     const int c = hist[b];
     if (c) hist[b] = atomicAdd(&cursor[b], c);
   }
   __syncthreads();
 #pragma unroll
-  for (int q = 0; q < kSortPer; ++q)
-    if (tile[q] >= 0) order[hist[tile[q]] + rank[q]] = (int)(first + q * kSortThreads);
+  for (int q = 0; q < kSortPer; ++q) {
+    if (bin[q] < 0) continue;
+    const int at = hist[bin[q]] + rank[q];
+    order[at] = (int)(first + q * kSortThreads);
+    where[at] = texel[q];
+  }
 }
 
 // ---- texels -----------------------------------------------------------------------------------
@@ -415,8 +409,11 @@ __device__ __forceinline__ void put_occupancy(uint32_t* occ, int nl, int face, i
 constexpr int kMaxTileLog = 6, kTileThreads = 256;
 constexpr int kMipTexels = 1365;    // levels 1 .. 6 of a 64 x 64 tile
 constexpr int kTileMaxima = 8;      // per tile: the maxima of levels 0 .. 6
-// Stars of a tile kept in LDS; the others' values are read again when they are merged.  10^6
-// stars on 6 x 2048^2 are 163 per tile.
+// Stars of a tile kept in LDS.  While they all fit (10^6 stars on 6 x 2048^2 are 163 per tile),
+// levels 0 and 1 are formed from lists: one lane per star merges the texels whose list it
+// heads, then one lane per parent that has a child.  Every texel of the tile in turn ran the
+// FP64 merge for the few lanes of each wave that had anything (230 us a pass, of issue alone).
+// A tile with more stars does that; the values that do not fit are read again.
 constexpr int kStash = 512;
 
 // value and position of star s
@@ -449,6 +446,9 @@ __global__ void __launch_bounds__(kTileThreads) k_star_tiles(StarBuild B) {
   __shared__ M mip[kMipTexels];
   __shared__ M stash[kStash];
   __shared__ int stash_id[kStash], stash_next[kStash];
+  __shared__ short stash_at[kStash], parents[kStash];
+  __shared__ unsigned seen[32];           // parents already listed
+  __shared__ int own, listed;             // stars of this tile, parents with a child
   __shared__ unsigned word[2 * 64 + 64];  // PACK: occupancy words of levels 0 .. 6
   __shared__ unsigned top[kTileMaxima];
   const int t = threadIdx.x, tl = B.tl, T = 1 << tl, n0 = B.n0, nt = n0 >> tl;
@@ -469,7 +469,11 @@ __global__ void __launch_bounds__(kTileThreads) k_star_tiles(StarBuild B) {
   }
   const int tile = blockIdx.x, face = tile / (nt * nt);
   const int ty = (tile / nt) % nt, tx = tile % nt;
-  const int base = B.start[tile], cnt = B.start[tile + 1] - base;
+  // the tile's bin, and the tile's first texel inside it
+  const int bl = B.bl, nb = n0 >> bl, sub = bl - tl;
+  const int bin = (face * nb + (ty >> sub)) * nb + (tx >> sub);
+  const int base = B.start[bin], cnt = B.start[bin + 1] - base;
+  const int bx = (tx & ((1 << sub) - 1)) << tl, by = (ty & ((1 << sub) - 1)) << tl;
   if (PACK) {
     if (tile == 0 && t < B.levels) B.scale[t] = level_scale(B.maxbits, t, B.fp16);
   } else {
@@ -477,7 +481,35 @@ __global__ void __launch_bounds__(kTileThreads) k_star_tiles(StarBuild B) {
     const int64_t w0 = B.occ_words * tile / B.tiles, w1 = B.occ_words * (tile + 1) / B.tiles;
     for (int64_t w = w0 + t; w < w1; w += kTileThreads) B.occ[w] = 0u;
   }
-  if (cnt == 0) {  // uniform
+  for (int q = t; q < T * T; q += kTileThreads) head[q] = -1;
+  if (PACK)
+    for (int q = t; q < 192; q += kTileThreads) word[q] = 0u;
+  else if (t < kTileMaxima)
+    top[t] = 0u;
+  for (int q = t; q < T * T / 4; q += kTileThreads) mip[q] = no_star<BANDS>();
+  if (t < 32) seen[t] = 0u;
+  if (t == 0) own = listed = 0;
+  __syncthreads();
+  // pick the tile's stars from the bin and list them per texel: star i < kStash in LDS, any
+  // other by its slot in the bin
+  for (int q = t; q < cnt; q += kTileThreads) {
+    const uint32_t w = B.where[base + q];
+    const int lx = (int)(w & 0xffffu) - bx, ly = (int)(w >> 16) - by;
+    if ((unsigned)lx >= (unsigned)T || (unsigned)ly >= (unsigned)T) continue;
+    const int i = atomicAdd(&own, 1), e = i < kStash ? i : kStash + q, at = ly * T + lx;
+    const int before = atomicExch(&head[at], e);
+    if (i >= kStash) {
+      B.next[base + q] = before;
+      continue;
+    }
+    const int s = B.order[base + q];
+    stash[i] = star_value<BANDS>(B, s, place_star<BANDS>(B.dirs, B.inten, s, n0));
+    stash_id[i] = s;
+    stash_at[i] = (short)at;
+    stash_next[i] = before;
+  }
+  __syncthreads();
+  if (own == 0) {  // uniform
     const M zero = no_star<BANDS>();
     if (PACK) {
       for (int l = 0; l <= tl; ++l) {
@@ -497,29 +529,10 @@ __global__ void __launch_bounds__(kTileThreads) k_star_tiles(StarBuild B) {
     }
     return;
   }
-  for (int q = t; q < T * T; q += kTileThreads) head[q] = -1;
-  if (PACK)
-    for (int q = t; q < 192; q += kTileThreads) word[q] = 0u;
-  else if (t < kTileMaxima)
-    top[t] = 0u;
-  __syncthreads();
-  // list the stars of each texel
-  for (int i = t; i < cnt; i += kTileThreads) {
-    const int s = B.order[base + i];
-    const Place p = place_star<BANDS>(B.dirs, B.inten, s, n0);
-    if (i < kStash) {
-      stash[i] = star_value<BANDS>(B, s, p);
-      stash_id[i] = s;
-    }
-    const int before = atomicExch(&head[(p.iy - ty * T) * T + (p.ix - tx * T)], i);
-    if (i < kStash)
-      stash_next[i] = before;
-    else
-      B.next[base + i] = before;
-  }
-  __syncthreads();
-  const auto id_of = [&](int i) { return i < kStash ? stash_id[i] : B.order[base + i]; };
-  const auto next_of = [&](int i) { return i < kStash ? stash_next[i] : B.next[base + i]; };
+  const auto id_of = [&](int e) { return e < kStash ? stash_id[e] : B.order[base + e - kStash]; };
+  const auto next_of = [&](int e) {
+    return e < kStash ? stash_next[e] : B.next[base + e - kStash];
+  };
   // level-0 texel: its stars in increasing star index
   const auto merge = [&](int h) {
     if (h < 0) return no_star<BANDS>();
@@ -527,11 +540,11 @@ __global__ void __launch_bounds__(kTileThreads) k_star_tiles(StarBuild B) {
     int last = -1;
     for (;;) {
       int best = 0x7fffffff, at = -1;
-      for (int c = h; c >= 0; c = next_of(c)) {
-        const int id = id_of(c);
+      for (int e = h; e >= 0; e = next_of(e)) {
+        const int id = id_of(e);
         if (id > last && id < best) {
           best = id;
-          at = c;
+          at = e;
         }
       }
       if (at < 0) break;
@@ -555,6 +568,11 @@ __global__ void __launch_bounds__(kTileThreads) k_star_tiles(StarBuild B) {
     for (int k = 0; k < l; ++k) w += (T >> k) * max(1, (T >> k) >> 5);
     return w;
   };
+  // stores texels (x, y), (x + 1, y) of level l, x even, and their occupancy bits
+  const auto put_pair = [&](int l, int wb, int x, int y, const M& c0, const M& c1, float inv) {
+    const unsigned o = store_pair<BANDS>(B.out, texel_at(l, x, y), c0, c1, inv, B.fp16);
+    if (o) atomicOr(&word[wb + y * max(1, (T >> l) >> 5) + (x >> 5)], o << (x & 31));
+  };
   if (tl == 0) {  // a 1 x 1 face: its texel is also the topmost
     if (t == 0) {
       const M m = merge(head[0]);
@@ -569,42 +587,54 @@ __global__ void __launch_bounds__(kTileThreads) k_star_tiles(StarBuild B) {
     }
     return;
   }
-  // levels 0 and 1, a thread per 2 x 2 texels
+  // levels 0 and 1
   float max0 = 0.0f, max1 = 0.0f;
   const int half = T >> 1;
   const float inv0 = PACK ? 1.0f / level_scale(B.maxbits, 0, B.fp16) : 1.0f;
-  const float inv1 = PACK ? 1.0f / level_scale(B.maxbits, 1, B.fp16) : 1.0f;
-  const int wp0 = max(1, T >> 5), base1 = word_base(1), wp1 = max(1, half >> 5);
-  for (int q = t; q < half * half; q += kTileThreads) {
-    const int qx = q & (half - 1), qy = q >> (tl - 1);
-    const int2 h0 = *(const int2*)&head[(2 * qy) * T + 2 * qx];
-    const int2 h1 = *(const int2*)&head[(2 * qy + 1) * T + 2 * qx];
-    const bool none = (h0.x & h0.y & h1.x & h1.y) < 0;  // list heads are -1 or >= 0
-    M c[4];
-    if (none) {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) c[k] = no_star<BANDS>();
-    } else {
-      c[0] = merge(h0.x);
-      c[1] = merge(h0.y);
-      c[2] = merge(h1.x);
-      c[3] = merge(h1.y);
+  const int mine = own;
+  if (mine <= kStash) {
+    for (int i = t; i < mine; i += kTileThreads) {
+      const int at = stash_at[i];
+      if (head[at] != i) continue;
+      const M m = merge(i);  // the list's other stars are read here only
+      stash[i] = m;
+      max0 = fmaxf(max0, brightest(m));
+      const int q = (at >> (tl + 1)) * half + ((at & (T - 1)) >> 1);
+      const unsigned bit = 1u << (q & 31);
+      if (!(atomicOr(&seen[q >> 5], bit) & bit)) parents[atomicAdd(&listed, 1)] = (short)q;
     }
-    const M m = none ? no_star<BANDS>() : parent_texel<BANDS>([&](int k) { return c[k]; });
-    mip[q] = m;
-    if (PACK) {
-      const unsigned o0 = store_pair<BANDS>(B.out, texel_at(0, 2 * qx, 2 * qy), c[0], c[1], inv0,
-                                            B.fp16);
-      const unsigned o1 = store_pair<BANDS>(B.out, texel_at(0, 2 * qx, 2 * qy + 1), c[2], c[3],
-                                            inv0, B.fp16);
-      if (o0) atomicOr(&word[(2 * qy) * wp0 + (2 * qx >> 5)], o0 << (2 * qx & 31));
-      if (o1) atomicOr(&word[(2 * qy + 1) * wp0 + (2 * qx >> 5)], o1 << (2 * qx & 31));
-      if (store_texel<BANDS>(B.out, texel_at(1, qx, qy), m, inv1, B.fp16))
-        atomicOr(&word[base1 + qy * wp1 + (qx >> 5)], 1u << (qx & 31));
-    } else {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) max0 = fmaxf(max0, brightest(c[k]));
+    __syncthreads();
+    const auto texel0 = [&](int h) { return h < 0 ? no_star<BANDS>() : stash[h]; };
+    for (int a = t; a < listed; a += kTileThreads) {
+      const int q = parents[a], at = 2 * (q >> (tl - 1)) * T + 2 * (q & (half - 1));
+      const M m = parent_texel<BANDS>(
+          [&](int k) { return texel0(head[at + (k >> 1) * T + (k & 1)]); });
+      mip[q] = m;
       max1 = fmaxf(max1, brightest(m));
+    }
+    if (PACK) {
+      for (int q = t; q < T * half; q += kTileThreads) {
+        const int x = 2 * (q & (half - 1)), y = q >> (tl - 1);
+        const int2 h = *(const int2*)&head[y * T + x];
+        put_pair(0, 0, x, y, texel0(h.x), texel0(h.y), inv0);
+      }
+    }
+  } else {
+    for (int q = t; q < half * half; q += kTileThreads) {
+      const int x = 2 * (q & (half - 1)), y = 2 * (q >> (tl - 1));
+      M c[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        c[k] = merge(head[(y + (k >> 1)) * T + x + (k & 1)]);
+        max0 = fmaxf(max0, brightest(c[k]));
+      }
+      const M m = parent_texel<BANDS>([&](int k) { return c[k]; });
+      mip[q] = m;
+      max1 = fmaxf(max1, brightest(m));
+      if (PACK) {
+        put_pair(0, 0, x, y, c[0], c[1], inv0);
+        put_pair(0, 0, x, y + 1, c[2], c[3], inv0);
+      }
     }
   }
   if (!PACK) {
@@ -618,6 +648,16 @@ __global__ void __launch_bounds__(kTileThreads) k_star_tiles(StarBuild B) {
     }
   }
   __syncthreads();
+  if (PACK) {
+    const float inv1 = 1.0f / level_scale(B.maxbits, 1, B.fp16);
+    const int wb = word_base(1);
+    if (half > 1) {
+      for (int q = t; q < half * half / 2; q += kTileThreads)
+        put_pair(1, wb, 2 * q & (half - 1), 2 * q >> (tl - 1), mip[2 * q], mip[2 * q + 1], inv1);
+    } else if (t == 0 && store_texel<BANDS>(B.out, texel_at(1, 0, 0), mip[0], inv1, B.fp16)) {
+      word[wb] = 1u;
+    }
+  }
   // levels 2 .. tl
   const M* prev = mip;
   for (int l = 2; l <= tl; ++l) {
@@ -722,28 +762,35 @@ size_t star_tail_texel_bytes(int bands) {
 }
 size_t star_tile_max_bytes() { return kTileMaxima * sizeof(float); }
 
-// hash (*acc), *bad and the stars per tile (`count`, or null); all zero before
+// Bins: one tile each while there are at most kMaxBins of them, else squares of tiles.
+int star_bin_log(int n0) {
+  int bl = star_tile_log(n0);
+  while (6 * (n0 >> bl) * (n0 >> bl) > kMaxBins) ++bl;
+  return bl;
+}
+
+// hash (*acc), *bad and the stars per bin (`count`, or null); all zero before
 hipError_t launch_star_count(const float* dirs, const float* inten, const float* temp, int64_t n,
                              int n0, int bands, unsigned long long* acc, int* bad, int* count,
                              hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  const int tl = star_tile_log(n0), nt = n0 >> tl;
+  const int bl = star_bin_log(n0), nb = n0 >> bl;
   const dim3 grid(blocks_for(n, kSortStars));
   if (bands)
     hipLaunchKernelGGL(k_star_count<true>, grid, dim3(kSortThreads), 0, s, dirs, inten, temp, n,
-                       n0, tl, 6 * nt * nt, acc, bad, count);
+                       n0, bl, 6 * nb * nb, acc, bad, count);
   else
     hipLaunchKernelGGL(k_star_count<false>, grid, dim3(kSortThreads), 0, s, dirs, inten, temp, n,
-                       n0, tl, 6 * nt * nt, acc, bad, count);
+                       n0, bl, 6 * nb * nb, acc, bad, count);
   return hipGetLastError();
 }
 
 template <bool BANDS>
 static hipError_t build(const StarBuild& B, int* count, int64_t n, hipStream_t s) {
-  hipLaunchKernelGGL(k_star_scan, dim3(1), dim3(1024), 0, s, count, B.start, B.tiles);
+  hipLaunchKernelGGL(k_star_scan, dim3(1), dim3(1024), 0, s, count, B.start, B.bins);
   if (n > 0)
     hipLaunchKernelGGL(k_star_scatter<BANDS>, dim3(blocks_for(n, kSortStars)), dim3(kSortThreads),
-                       0, s, B.dirs, B.inten, n, B.n0, B.tl, B.tiles, count, B.order);
+                       0, s, B.dirs, B.inten, n, B.n0, B.bl, B.bins, count, B.order, B.where);
   hipLaunchKernelGGL((k_star_tiles<BANDS, false>), dim3(B.tiles), dim3(kTileThreads), 0, s, B);
   hipLaunchKernelGGL(k_star_tail<BANDS>, dim3(6), dim3(kTileThreads), 0, s, B);
   hipLaunchKernelGGL((k_star_tiles<BANDS, true>),
@@ -752,7 +799,7 @@ static hipError_t build(const StarBuild& B, int* count, int64_t n, hipStream_t s
   return hipGetLastError();
 }
 
-// Every level, its scale and its occupancy bits, from the tile counts of launch_star_count.
+// Every level, its scale and its occupancy bits, from the bin counts of launch_star_count.
 hipError_t launch_star_build(const StarBuild& B, int* count, int64_t n, int bands,
                              hipStream_t s) {
   return bands ? build<true>(B, count, n, s) : build<false>(B, count, n, s);
