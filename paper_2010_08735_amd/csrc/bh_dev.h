@@ -62,6 +62,7 @@ struct StarBuild {
   const float* temp;     // (I, T) maps only
   int* order;            // star indices in bin order
   uint32_t* where;       // their texels inside the bin
+  float4* val;           // their values, or null: read through `order` (stars.hip)
   int* start;            // first slot of each bin in `order`, then their end
   int* next;             // star lists beyond the stars kept in LDS
   float* tilemax;        // the tiles' maxima per level
@@ -72,6 +73,7 @@ struct StarBuild {
   uint32_t* occ;
   uint32_t* level_off_dev;
   uint32_t* occ_off_dev;
+  int64_t n;             // stars
   int64_t occ_words, tail_texels;  // tail_texels: levels tl + 1 and later
   int n0, levels, tl, tiles, bl, bins, fp16;  // a bin: a square of 2^(bl - tl) tiles an edge
   uint32_t off[kStarMaxLevels + 1], ooff[kStarMaxLevels + 1];  // texels, occupancy words

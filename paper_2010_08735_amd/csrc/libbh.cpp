@@ -759,6 +759,12 @@ static bh_status build_stars(bh_ctx* c, const float* dir_xyz_dev, const float* i
   const size_t o_start = take(sizeof(int) * ((size_t)B.bins + 1));
   const size_t o_order = take(sizeof(int) * nstars), o_where = take(sizeof(uint32_t) * nstars);
   const size_t o_next = take(sizeof(int) * nstars);
+  // Star values in bin order save a gather of three cache lines a star in each pass over the
+  // tiles (10^6 stars on 6 x 2048^2: 131 + 167 -> 121 + 150 us, the scatter 32 -> 39 us), but not
+  // on maps denser than 9 n0^2 stars, where 28 or 32 bytes of scratch a star would exceed what
+  // a build needed when it kept every level's FP32 texels (152 n0^2 bytes and 12 a star).
+  const bool values = n <= 9ll * n0 * n0;
+  const size_t o_val = take(values ? (bands ? 20 : 16) * nstars : 0);
   const size_t o_tmax = take(star_tile_max_bytes() * (size_t)B.tiles);
   const size_t o_tail = take(star_tail_texel_bytes(bands) * (size_t)tail_all);
   char* scratch = nullptr;
@@ -837,6 +843,8 @@ static bh_status build_stars(bh_ctx* c, const float* dir_xyz_dev, const float* i
   if (!st && !first.bad) {
     B.order = (int*)(scratch + o_order);
     B.where = (uint32_t*)(scratch + o_where);
+    B.val = values ? (float4*)(scratch + o_val) : nullptr;
+    B.n = n;
     B.start = (int*)(scratch + o_start);
     B.next = (int*)(scratch + o_next);
     B.tilemax = (float*)(scratch + o_tmax);

@@ -22,9 +22,11 @@
 // first: a first pass over the tiles only finds the maxima and the tiles' topmost texels, from
 // which k_star_tail forms the remaining levels; a second pass merges again (the stars are few
 // against the texels) and writes the stored texels and the occupancy bits, each byte once.
-// The first version linked stars through a texel-sized head array and passed every level
-// through FP32 masters: 0.9 GB of scratch and 60 launches, 1.55 ms of kernels for 10^6 stars
-// on 6 x 2048^2.  The bound is the 277 MB the map itself takes.
+// 10^6 stars on 6 x 2048^2: 350 us of kernels (count 19, scatter 39, tiles 121 and 150, tail 13),
+// where linking the stars through a texel-sized head array and passing every level through
+// FP32 texels in memory took 1550 us, 60 launches and 0.9 GB of scratch.  The map's own 277 MB
+// are 45 us; the tile passes wait on their chains of LDS and FP64 latency (a wave lives for 13
+// us and issues 450 vector instructions; LDS fits three workgroups a CU).
 #include <algorithm>
 
 #include "bh_dev.h"
@@ -42,6 +44,11 @@ struct __align__(16) Half8 {
 };
 
 static inline unsigned blocks_for(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
+
+__global__ void k_fill_int(int* p, int64_t n, int v) {
+  int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (t < n) p[t] = v;
+}
 
 // ---- where a star lands -------------------------------------------------------------------
 
@@ -125,11 +132,11 @@ __device__ __forceinline__ uint64_t star_hash(const float* __restrict__ dirs,
 }
 
 // The sorting kernels keep their counts in LDS and add them to the bins' with one global
-// atomic per bin and workgroup.  Few large workgroups (16 stars a thread, 16 384 each) and at
-// most kMaxBins bins keep those few: 10^6 stars straight onto the 6144 tiles of 6 x 2048^2
+// atomic per bin and workgroup.  Large workgroups (8192 stars) and at most
+// kMaxBins bins keep those few: 10^6 stars straight onto the 6144 tiles of 6 x 2048^2
 // were 10^6 scattered device atomics, 65 us a pass; onto the 96 of 6 x 256^2, 10^4 queued on
 // each counter.
-constexpr int kSortThreads = 1024, kSortPer = 16, kSortStars = kSortThreads * kSortPer;
+constexpr int kSortThreads = 1024, kSortPer = 8, kSortStars = kSortThreads * kSortPer;
 constexpr int kMaxBins = 1536;
 
 // Hash of the field, stars per bin (unless `count` is null), and whether a band value is
@@ -197,44 +204,6 @@ __global__ void __launch_bounds__(1024)
   if (t == 1023) start[bins] = part[1023];
 }
 
-// star indices and their texels in bin order (any order inside a bin: the merge sorts)
-template <bool BANDS>
-__global__ void __launch_bounds__(kSortThreads)
-    k_star_scatter(const float* __restrict__ dirs, const float* __restrict__ inten, int64_t n,
-                   int n0, int bl, int bins, int* __restrict__ cursor, int* __restrict__ order,
-                   uint32_t* __restrict__ where) {
-  __shared__ int hist[kMaxBins];
-  const int64_t first = (int64_t)blockIdx.x * kSortStars + threadIdx.x;
-  for (int b = threadIdx.x; b < bins; b += kSortThreads) hist[b] = 0;
-  __syncthreads();
-  int bin[kSortPer], rank[kSortPer];
-  uint32_t texel[kSortPer];
-#pragma unroll
-  for (int q = 0; q < kSortPer; ++q) {
-    const int64_t s = first + q * kSortThreads;
-    bin[q] = -1;
-    if (s >= n) continue;
-    const Place p = place_star<BANDS>(dirs, inten, s, n0);
-    if (!p.lit) continue;
-    bin[q] = bin_of(p, n0, bl);
-    texel[q] = bin_texel(p, bl);
-    rank[q] = atomicAdd(&hist[bin[q]], 1);
-  }
-  __syncthreads();
-  for (int b = threadIdx.x; b < bins; b += kSortThreads) {
-    const int c = hist[b];
-    if (c) hist[b] = atomicAdd(&cursor[b], c);
-  }
-  __syncthreads();
-#pragma unroll
-  for (int q = 0; q < kSortPer; ++q) {
-    if (bin[q] < 0) continue;
-    const int at = hist[bin[q]] + rank[q];
-    order[at] = (int)(first + q * kSortThreads);
-    where[at] = texel[q];
-  }
-}
-
 // ---- texels -----------------------------------------------------------------------------------
 
 // (I, T, p_u, p_v) or (R, G, B, p_u, p_v); all zero when nothing lands in the texel
@@ -257,6 +226,26 @@ template <bool BANDS>
 __device__ __forceinline__ float brightest(const Master<BANDS>& m) {
   return BANDS ? fmaxf(m.v[0], fmaxf(m.v[1], m.v[2])) : m.v[0];
 }
+
+// Quotients by one divisor d > 0: a reciprocal by Newton's iteration, then each quotient
+// corrected once by its own remainder (within an ulp of FP64, exact where the quotient is; it is
+// rounded to FP32 next).  Outside the range where nothing can overflow or vanish the plain
+// division is used.
+struct Divider {
+  double d, r;
+  bool plain;
+  __device__ __forceinline__ explicit Divider(double x) : d(x) {
+    plain = !(x > 0x1p-500 && x < 0x1p500);
+    r = __builtin_amdgcn_rcp(x);
+    r = fma(fma(-x, r, 1.0), r, r);
+    r = fma(fma(-x, r, 1.0), r, r);
+  }
+  __device__ __forceinline__ float operator()(double n) const {
+    if (plain) return (float)(n / d);
+    const double q = n * r;
+    return (float)fma(fma(-d, q, n), r, q);
+  }
+};
 
 // Running sums of a texel in FP64, in the order the stars or children are added
 template <bool BANDS>
@@ -283,21 +272,107 @@ struct Sums {
     if constexpr (BANDS) {
       const double S = s[0] + s[1] + s[2];
       if (S > 0.0) {
+        const Divider over(S);
         m.v[0] = (float)s[0];
         m.v[1] = (float)s[1];
         m.v[2] = (float)s[2];
-        m.v[3] = (float)(s[3] / S);
-        m.v[4] = (float)(s[4] / S);
+        m.v[3] = over(s[3]);
+        m.v[4] = over(s[4]);
       }
     } else if (s[0] > 0.0) {
+      const Divider over(s[0]);
       m.v[0] = (float)s[0];
-      m.v[1] = (float)(s[1] / s[0]);
-      m.v[2] = (float)(s[2] / s[0]);
-      m.v[3] = (float)(s[3] / s[0]);
+      m.v[1] = over(s[1]);
+      m.v[2] = over(s[2]);
+      m.v[3] = over(s[3]);
     }
     return m;
   }
 };
+
+// value and position of star s
+template <bool BANDS>
+__device__ __forceinline__ Master<BANDS> star_value(const StarBuild& B, int64_t s,
+                                                    const Place& p) {
+  Master<BANDS> m;
+  if constexpr (BANDS) {
+    m.v[0] = B.inten[3 * s];
+    m.v[1] = B.inten[3 * s + 1];
+    m.v[2] = B.inten[3 * s + 2];
+    m.v[3] = p.pu;
+    m.v[4] = p.pv;
+  } else {
+    m.v[0] = B.inten[s];
+    m.v[1] = B.temp[s];
+    m.v[2] = p.pu;
+    m.v[3] = p.pv;
+  }
+  return m;
+}
+
+// Star values in bin order (4 floats a star, or 4 and then, after all of them, 1): the tiles
+// read their stars in a row instead of gathering three cache lines for each.
+template <bool BANDS>
+__device__ __forceinline__ void put_value(const StarBuild& B, int64_t at, const Master<BANDS>& m) {
+  B.val[at] = make_float4(m.v[0], m.v[1], m.v[2], m.v[3]);
+  if constexpr (BANDS) ((float*)(B.val + B.n))[at] = m.v[4];
+}
+
+// value of the star at slot `at` of the bin order
+template <bool BANDS>
+__device__ __forceinline__ Master<BANDS> value_at(const StarBuild& B, int64_t at) {
+  if (!B.val) {
+    const int64_t s = B.order[at];
+    return star_value<BANDS>(B, s, place_star<BANDS>(B.dirs, B.inten, s, B.n0));
+  }
+  const float4 v = B.val[at];
+  Master<BANDS> m;
+  m.v[0] = v.x;
+  m.v[1] = v.y;
+  m.v[2] = v.z;
+  m.v[3] = v.w;
+  if constexpr (BANDS) m.v[4] = ((const float*)(B.val + B.n))[at];
+  return m;
+}
+
+// star indices, texels and values in bin order (any order inside a bin: the merge sorts)
+template <bool BANDS>
+__global__ void __launch_bounds__(kSortThreads)
+    k_star_scatter(StarBuild B, int* __restrict__ cursor) {
+  __shared__ int hist[kMaxBins];
+  const int64_t first = (int64_t)blockIdx.x * kSortStars + threadIdx.x;
+  for (int b = threadIdx.x; b < B.bins; b += kSortThreads) hist[b] = 0;
+  __syncthreads();
+  int bin[kSortPer], rank[kSortPer];
+  uint32_t texel[kSortPer];
+  Master<BANDS> m[kSortPer];
+#pragma unroll
+  for (int q = 0; q < kSortPer; ++q) {
+    const int64_t s = first + q * kSortThreads;
+    bin[q] = -1;
+    if (s >= B.n) continue;
+    const Place p = place_star<BANDS>(B.dirs, B.inten, s, B.n0);
+    if (!p.lit) continue;
+    bin[q] = bin_of(p, B.n0, B.bl);
+    texel[q] = bin_texel(p, B.bl);
+    m[q] = star_value<BANDS>(B, s, p);
+    rank[q] = atomicAdd(&hist[bin[q]], 1);
+  }
+  __syncthreads();
+  for (int b = threadIdx.x; b < B.bins; b += kSortThreads) {
+    const int c = hist[b];
+    if (c) hist[b] = atomicAdd(&cursor[b], c);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < kSortPer; ++q) {
+    if (bin[q] < 0) continue;
+    const int at = hist[bin[q]] + rank[q];
+    B.order[at] = (int)(first + q * kSortThreads);
+    B.where[at] = texel[q];
+    if (B.val) put_value<BANDS>(B, at, m[q]);
+  }
+}
 
 // parent texel from children (0,0), (1,0), (0,1), (1,1)
 template <bool BANDS, class Child>
@@ -406,7 +481,7 @@ __device__ __forceinline__ void put_occupancy(uint32_t* occ, int nl, int face, i
   }
 }
 
-constexpr int kMaxTileLog = 6, kTileThreads = 256;
+constexpr int kMaxTileLog = 6, kTileThreads = 512;
 constexpr int kMipTexels = 1365;    // levels 1 .. 6 of a 64 x 64 tile
 constexpr int kTileMaxima = 8;      // per tile: the maxima of levels 0 .. 6
 // Stars of a tile kept in LDS.  While they all fit (10^6 stars on 6 x 2048^2 are 163 per tile),
@@ -415,26 +490,6 @@ constexpr int kTileMaxima = 8;      // per tile: the maxima of levels 0 .. 6
 // FP64 merge for the few lanes of each wave that had anything (230 us a pass, of issue alone).
 // A tile with more stars does that; the values that do not fit are read again.
 constexpr int kStash = 512;
-
-// value and position of star s
-template <bool BANDS>
-__device__ __forceinline__ Master<BANDS> star_value(const StarBuild& B, int64_t s,
-                                                    const Place& p) {
-  Master<BANDS> m;
-  if constexpr (BANDS) {
-    m.v[0] = B.inten[3 * s];
-    m.v[1] = B.inten[3 * s + 1];
-    m.v[2] = B.inten[3 * s + 2];
-    m.v[3] = p.pu;
-    m.v[4] = p.pv;
-  } else {
-    m.v[0] = B.inten[s];
-    m.v[1] = B.temp[s];
-    m.v[2] = p.pu;
-    m.v[3] = p.pv;
-  }
-  return m;
-}
 
 // PACK: write the tile's stored texels and occupancy bits; otherwise only its levels' maxima
 // and its topmost texel (level tl) for the tail.
@@ -451,24 +506,25 @@ __global__ void __launch_bounds__(kTileThreads) k_star_tiles(StarBuild B) {
   __shared__ int own, listed;             // stars of this tile, parents with a child
   __shared__ unsigned word[2 * 64 + 64];  // PACK: occupancy words of levels 0 .. 6
   __shared__ unsigned top[kTileMaxima];
-  const int t = threadIdx.x, tl = B.tl, T = 1 << tl, n0 = B.n0, nt = n0 >> tl;
+  const int t = threadIdx.x, tl = B.tl, T = 1 << tl, n0 = B.n0;
+  const int lnt = B.levels - 1 - tl, nt = 1 << lnt;  // tiles of a face edge
   if (PACK && (int)blockIdx.x >= B.tiles) {  // the tail's levels, one thread per texel
     const int64_t q = (int64_t)(blockIdx.x - B.tiles) * kTileThreads + t;
     const int64_t k = q + (B.off[tl + 1] - B.off[tl]);  // in B.tail
     if (q >= B.tail_texels) return;
     int l = tl + 1;
     while (l + 1 < B.levels && k >= (int64_t)(B.off[l + 1] - B.off[tl])) ++l;
-    const int nl = n0 >> l;
+    const int nl = n0 >> l, ll = B.levels - 1 - l;
     const int e = (int)(k - (B.off[l] - B.off[tl]));
-    const int x = e % nl, y = (e / nl) % nl, face = e / (nl * nl);
+    const int x = e & (nl - 1), y = (e >> ll) & (nl - 1), face = e >> (2 * ll);
     const M m = ((const M*)B.tail)[k];
     if (store_texel<BANDS>(B.out, (int64_t)B.off[l] + e, m,
                            1.0f / level_scale(B.maxbits, l, B.fp16), B.fp16))
       put_occupancy(B.occ + B.ooff[l], nl, face, y, x >> 5, 1u << (x & 31), false);
     return;
   }
-  const int tile = blockIdx.x, face = tile / (nt * nt);
-  const int ty = (tile / nt) % nt, tx = tile % nt;
+  const int tile = blockIdx.x, face = tile >> (2 * lnt);
+  const int ty = (tile >> lnt) & (nt - 1), tx = tile & (nt - 1);
   // the tile's bin, and the tile's first texel inside it
   const int bl = B.bl, nb = n0 >> bl, sub = bl - tl;
   const int bin = (face * nb + (ty >> sub)) * nb + (tx >> sub);
@@ -476,10 +532,6 @@ __global__ void __launch_bounds__(kTileThreads) k_star_tiles(StarBuild B) {
   const int bx = (tx & ((1 << sub) - 1)) << tl, by = (ty & ((1 << sub) - 1)) << tl;
   if (PACK) {
     if (tile == 0 && t < B.levels) B.scale[t] = level_scale(B.maxbits, t, B.fp16);
-  } else {
-    // this workgroup's share of the cleared occupancy words
-    const int64_t w0 = B.occ_words * tile / B.tiles, w1 = B.occ_words * (tile + 1) / B.tiles;
-    for (int64_t w = w0 + t; w < w1; w += kTileThreads) B.occ[w] = 0u;
   }
   for (int q = t; q < T * T; q += kTileThreads) head[q] = -1;
   if (PACK)
@@ -492,21 +544,30 @@ __global__ void __launch_bounds__(kTileThreads) k_star_tiles(StarBuild B) {
   __syncthreads();
   // pick the tile's stars from the bin and list them per texel: star i < kStash in LDS, any
   // other by its slot in the bin
-  for (int q = t; q < cnt; q += kTileThreads) {
-    const uint32_t w = B.where[base + q];
-    const int lx = (int)(w & 0xffffu) - bx, ly = (int)(w >> 16) - by;
-    if ((unsigned)lx >= (unsigned)T || (unsigned)ly >= (unsigned)T) continue;
-    const int i = atomicAdd(&own, 1), e = i < kStash ? i : kStash + q, at = ly * T + lx;
-    const int before = atomicExch(&head[at], e);
-    if (i >= kStash) {
-      B.next[base + q] = before;
-      continue;
+  constexpr int kScan = 4;  // loads in flight: a bin holds several tiles' stars
+  for (int q0 = t; q0 < cnt; q0 += kScan * kTileThreads) {
+    uint32_t w[kScan];
+#pragma unroll
+    for (int k = 0; k < kScan; ++k) {
+      const int q = q0 + k * kTileThreads;
+      w[k] = B.where[base + min(q, cnt - 1)];
     }
-    const int s = B.order[base + q];
-    stash[i] = star_value<BANDS>(B, s, place_star<BANDS>(B.dirs, B.inten, s, n0));
-    stash_id[i] = s;
-    stash_at[i] = (short)at;
-    stash_next[i] = before;
+#pragma unroll
+    for (int k = 0; k < kScan; ++k) {
+      const int q = q0 + k * kTileThreads;
+      const int lx = (int)(w[k] & 0xffffu) - bx, ly = (int)(w[k] >> 16) - by;
+      if (q >= cnt || (unsigned)lx >= (unsigned)T || (unsigned)ly >= (unsigned)T) continue;
+      const int i = atomicAdd(&own, 1), e = i < kStash ? i : kStash + q, at = ly * T + lx;
+      const int before = atomicExch(&head[at], e);
+      if (i >= kStash) {
+        B.next[base + q] = before;
+        continue;
+      }
+      stash[i] = value_at<BANDS>(B, base + q);
+      stash_id[i] = B.order[base + q];
+      stash_at[i] = (short)at;
+      stash_next[i] = before;
+    }
   }
   __syncthreads();
   if (own == 0) {  // uniform
@@ -517,8 +578,9 @@ __global__ void __launch_bounds__(kTileThreads) k_star_tiles(StarBuild B) {
         const int64_t at = (int64_t)B.off[l] + ((int64_t)face * nl + ty * s) * nl + tx * s;
         if (s > 1) {
           for (int q = t; q < s * s / 2; q += kTileThreads)
-            store_pair<BANDS>(B.out, at + (int64_t)(q / (s / 2)) * nl + 2 * (q % (s / 2)), zero,
-                              zero, 1.0f, B.fp16);
+            store_pair<BANDS>(B.out,
+                              at + (int64_t)(q >> (tl - l - 1)) * nl + 2 * (q & (s / 2 - 1)),
+                              zero, zero, 1.0f, B.fp16);
         } else if (t == 0) {
           store_texel<BANDS>(B.out, at, zero, 1.0f, B.fp16);
         }
@@ -552,7 +614,7 @@ __global__ void __launch_bounds__(kTileThreads) k_star_tiles(StarBuild B) {
       if (at < kStash)
         m = stash[at];
       else
-        m = star_value<BANDS>(B, best, place_star<BANDS>(B.dirs, B.inten, best, n0));
+        m = value_at<BANDS>(B, base + at - kStash);
       sum.add(m, (double)m.v[P], (double)m.v[P + 1]);
       last = best;
     }
@@ -689,7 +751,7 @@ __global__ void __launch_bounds__(kTileThreads) k_star_tiles(StarBuild B) {
   for (int l = 0, wb = 0; l <= tl; ++l) {
     const int s = T >> l, wp = max(1, s >> 5);
     for (int q = t; q < s * wp; q += kTileThreads) {
-      const int y = q / wp, gx = tx * s + 32 * (q % wp);
+      const int y = wp == 2 ? q >> 1 : q, gx = tx * s + (wp == 2 ? 32 * (q & 1) : 0);
       put_occupancy(B.occ + B.ooff[l], n0 >> l, face, ty * s + y, gx >> 5,
                     word[wb + q] << (gx & 31), s >= 32);
     }
@@ -733,7 +795,7 @@ __global__ void __launch_bounds__(kTileThreads) k_star_tail(StarBuild B) {
     M* cur = tail + (B.off[l] - B.off[tl]) + (int64_t)face * nl * nl;
     float v = 0.0f;
     for (int q = t; q < nl * nl; q += kTileThreads) {
-      const int x = q % nl, y = q / nl;
+      const int x = q & (nl - 1), y = q >> (B.levels - 1 - l);
       const M m = parent_texel<BANDS>(
           [&](int k) { return prev[(2 * y + (k >> 1)) * np + 2 * x + (k & 1)]; });
       cur[q] = m;
@@ -787,10 +849,12 @@ hipError_t launch_star_count(const float* dirs, const float* inten, const float*
 
 template <bool BANDS>
 static hipError_t build(const StarBuild& B, int* count, int64_t n, hipStream_t s) {
+  hipLaunchKernelGGL(k_fill_int, dim3(blocks_for(B.occ_words, 256)), dim3(256), 0, s,
+                     (int*)B.occ, B.occ_words, 0);
   hipLaunchKernelGGL(k_star_scan, dim3(1), dim3(1024), 0, s, count, B.start, B.bins);
   if (n > 0)
     hipLaunchKernelGGL(k_star_scatter<BANDS>, dim3(blocks_for(n, kSortStars)), dim3(kSortThreads),
-                       0, s, B.dirs, B.inten, n, B.n0, B.bl, B.bins, count, B.order, B.where);
+                       0, s, B, count);
   hipLaunchKernelGGL((k_star_tiles<BANDS, false>), dim3(B.tiles), dim3(kTileThreads), 0, s, B);
   hipLaunchKernelGGL(k_star_tail<BANDS>, dim3(6), dim3(kTileThreads), 0, s, B);
   hipLaunchKernelGGL((k_star_tiles<BANDS, true>),
@@ -840,11 +904,6 @@ hipError_t launch_star_unpack_bands(const void* in, int64_t count, float scale, 
   hipLaunchKernelGGL(k_star_unpack_bands, dim3(blocks_for(count, 256)), dim3(256), 0, s, in,
                      count, scale, fp16, out);
   return hipGetLastError();
-}
-
-__global__ void k_fill_int(int* p, int64_t n, int v) {
-  int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (t < n) p[t] = v;
 }
 
 hipError_t launch_fill_int(int* p, int64_t n, int v, hipStream_t s) {

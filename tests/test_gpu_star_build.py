@@ -46,7 +46,7 @@ def _field(n, n0, kind, seed):
 
 
 CASES = [(1, 50, "plain"), (2, 50, "plain"), (4, 300, "plain"), (16, 3000, "plain"),
-         (32, 3000, "clustered"), (64, 30000, "clustered"), (512, 20000, "clustered"),
+         (32, 3000, "clustered"), (64, 30000, "clustered"), (64, 60000, "clustered"), (512, 20000, "clustered"),
          (1024, 40000, "clustered"), (2048, 5000, "plain"), (64, 0, "plain")]
 
 
