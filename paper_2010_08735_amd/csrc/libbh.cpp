@@ -191,6 +191,11 @@ struct bh_ctx {
   int device = 0;
   uint64_t budget = 0;
   std::atomic<uint64_t> used{0};
+  // blocks of released handles and finished builds, kept for the next ones (dev_recycle)
+  std::mutex kept_mu;
+  std::multimap<size_t, void*> kept;  // by size
+  size_t kept_bytes = 0;
+  std::set<void*> unrounded;          // blocks smaller than their size step, never kept
   int cus = 256;
   std::mutex mu;  // resources, tile config, batch staging
   std::map<std::string, bh_tables*> tables;
@@ -237,6 +242,30 @@ static double now_s() {
       .count();
 }
 
+// Blocks kept for reuse.  Fresh device memory is cleared before a process gets it, and a build
+// that allocates and frees a 268 MB map waits for that: a new 6 x 2048^2 star map took 4.5 ms
+// of which its kernels are 0.35.  A context without a budget therefore keeps idle blocks of at
+// least kKeepLeast, at most kKeepMost in all, and hands them out again by size; they are freed
+// when an allocation fails and with the context.  Sizes are rounded up to eight steps an octave so
+// that nearly equal builds share blocks.  With a budget, which counts what is allocated, nothing is
+// kept or rounded.
+constexpr size_t kKeepLeast = (size_t)1 << 20, kKeepMost = (size_t)1 << 30;
+
+static size_t block_size(const bh_ctx* c, size_t bytes) {
+  if (c->budget || bytes < kKeepLeast) return bytes;
+  size_t step = kKeepLeast >> 3;
+  while ((step << 4) <= bytes) step <<= 1;
+  return (bytes + step - 1) / step * step;
+}
+
+// frees every kept block (with the context's device current)
+static void drop_kept(bh_ctx* c) {
+  std::lock_guard<std::mutex> g(c->kept_mu);
+  for (auto& kv : c->kept) (void)hipFree(kv.second);
+  c->kept.clear();
+  c->kept_bytes = 0;
+}
+
 // Reserves the bytes in the budget first (one atomic add, so concurrent callers cannot both
 // pass the check), then allocates; both steps are undone on failure.
 static bh_status dev_alloc(bh_ctx* c, size_t bytes, void** p) {
@@ -246,7 +275,31 @@ static bh_status dev_alloc(bh_ctx* c, size_t bytes, void** p) {
     return fail(BH_ENOMEM, "HBM budget exceeded: " + std::to_string(before + bytes) + " > " +
                                std::to_string(c->budget));
   }
-  hipError_t e = hipMalloc(p, bytes);
+  const size_t block = block_size(c, bytes);
+  if (block >= kKeepLeast) {
+    std::lock_guard<std::mutex> g(c->kept_mu);
+    auto it = c->kept.find(block);
+    if (it != c->kept.end()) {
+      *p = it->second;
+      c->kept.erase(it);
+      c->kept_bytes -= block;
+      return BH_OK;
+    }
+  }
+  hipError_t e = hipMalloc(p, block);
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    drop_kept(c);
+    e = hipMalloc(p, block);
+    if (e != hipSuccess && block != bytes) {
+      (void)hipGetLastError();
+      e = hipMalloc(p, bytes);
+      if (e == hipSuccess) {
+        std::lock_guard<std::mutex> g(c->kept_mu);
+        c->unrounded.insert(*p);
+      }
+    }
+  }
   if (e != hipSuccess) {
     c->used -= bytes;
     *p = nullptr;
@@ -259,6 +312,23 @@ static void dev_free(bh_ctx* c, void* p, size_t bytes) {
   if (!p) return;
   (void)hipFree(p);
   c->used -= bytes;
+}
+
+// dev_free of a block (of `bytes` when it was allocated) that no queued or running work uses,
+// on any stream: it may be handed out again at once.
+static void dev_recycle(bh_ctx* c, void* p, size_t bytes) {
+  if (!p) return;
+  const size_t block = block_size(c, bytes);
+  if (!c->budget && block >= kKeepLeast) {
+    std::lock_guard<std::mutex> g(c->kept_mu);
+    if (!c->unrounded.erase(p) && c->kept_bytes + block <= kKeepMost) {
+      c->kept.emplace(block, p);
+      c->kept_bytes += block;
+      c->used -= bytes;
+      return;
+    }
+  }
+  dev_free(c, p, bytes);
 }
 
 static bh_status ensure_staging(Staging& s, size_t bytes) {
@@ -378,6 +448,7 @@ extern "C" void bh_destroy(bh_ctx* c) {
     handle_drop(p);
     delete p;
   }
+  drop_kept(c);
   dev_free(c, c->lut, 0);
   dev_free(c, c->ctab, 0);
   dev_free(c, c->b_counter, 0);
@@ -494,10 +565,10 @@ extern "C" bh_status bh_release_tables(bh_tables* t) {
     }
   }
   c->tables.erase(t->key);
-  dev_free(c, t->D, sizeof(float) * (size_t)t->p.d_n * t->p.d_n);
-  dev_free(c, t->U, sizeof(float) * (size_t)t->p.u_ne * t->p.u_nphi);
-  dev_free(c, t->Dt, sizeof(float) * (size_t)t->p.d_n * t->p.d_n);
-  dev_free(c, t->Ut, sizeof(float) * (size_t)t->p.u_ne * t->p.u_nphi);
+  dev_recycle(c, t->D, sizeof(float) * (size_t)t->p.d_n * t->p.d_n);
+  dev_recycle(c, t->U, sizeof(float) * (size_t)t->p.u_ne * t->p.u_nphi);
+  dev_recycle(c, t->Dt, sizeof(float) * (size_t)t->p.d_n * t->p.d_n);
+  dev_recycle(c, t->Ut, sizeof(float) * (size_t)t->p.u_ne * t->p.u_nphi);
   handle_drop(t);
   delete t;
   return BH_OK;
@@ -703,8 +774,8 @@ extern "C" bh_status bh_bloom_release(bh_bloom* b) {
   if (!c->blooms.erase(b)) return fail(BH_ENOTFOUND, "unknown bloom");
   (void)hipSetDevice(c->device);
   (void)hipDeviceSynchronize();  // launches may still use the pyramid
-  dev_free(c, b->P, sizeof(float4) * b->elems);
-  dev_free(c, b->U, sizeof(float4) * b->elems);
+  dev_recycle(c, b->P, sizeof(float4) * b->elems);
+  dev_recycle(c, b->U, sizeof(float4) * b->elems);
   handle_drop(b);
   delete b;
   return BH_OK;
@@ -781,8 +852,9 @@ static bh_status build_stars(bh_ctx* c, const float* dir_xyz_dev, const float* i
     bh_ctx* c;
     char* p;
     size_t bytes;
-    ~Guard() { dev_free(c, p, bytes); }
-  } guard{c, scratch, bytes};
+    bool idle;  // nothing that uses it is queued or running
+    ~Guard() { idle ? dev_recycle(c, p, bytes) : dev_free(c, p, bytes); }
+  } guard{c, scratch, bytes, false};
   unsigned long long* acc = (unsigned long long*)(scratch + o_acc);
   int* count = (int*)(scratch + o_count);
   // content hash and bin counts of the arrays (ordered after the caller's work on the stream)
@@ -800,6 +872,7 @@ static bh_status build_stars(bh_ctx* c, const float* dir_xyz_dev, const float* i
     if (e == hipSuccess) e = hipStreamSynchronize(hs);
     if (e != hipSuccess) return fail(BH_EDEVICE, std::string("star hash: ") + hipGetErrorString(e));
   }
+  guard.idle = true;
   std::lock_guard<std::mutex> g(c->mu);
   StarKey key{first.hash, n, n0, texel_format, bands};
   auto found = c->stars.find(key);
@@ -864,8 +937,10 @@ static bh_status build_stars(bh_ctx* c, const float* dir_xyz_dev, const float* i
     }
     B.off[levels] = (uint32_t)total;
     B.tail_texels = (int64_t)total - B.off[B.tl + 1];
+    guard.idle = false;
     e = launch_star_build(B, count, n, bands, hs);
     if (e == hipSuccess) e = hipStreamSynchronize(hs);
+    guard.idle = e == hipSuccess;
   }
   if (st || e != hipSuccess || first.bad) {
     dev_free(c, s->tex, s->tex ? btex : 0);
@@ -934,11 +1009,11 @@ extern "C" bh_status bh_release_stars(bh_stars* s) {
   const size_t tsz = (s->fp16 ? 8 : 16) * (s->bands ? 2 : 1);
   uint64_t total = 0;
   for (int l = 0; l < s->levels; ++l) total += 6ull * (s->n0 >> l) * (s->n0 >> l);
-  dev_free(c, s->tex, tsz * total);
-  dev_free(c, s->scale, sizeof(float) * s->levels);
-  dev_free(c, s->level_off_dev, sizeof(uint32_t) * s->levels);
-  dev_free(c, s->occ, s->occ_bytes);
-  dev_free(c, s->occ_off_dev, sizeof(uint32_t) * s->levels);
+  dev_recycle(c, s->tex, tsz * total);
+  dev_recycle(c, s->scale, sizeof(float) * s->levels);
+  dev_recycle(c, s->level_off_dev, sizeof(uint32_t) * s->levels);
+  dev_recycle(c, s->occ, s->occ_bytes);
+  dev_recycle(c, s->occ_off_dev, sizeof(uint32_t) * s->levels);
   handle_drop(s);
   delete s;
   return BH_OK;
@@ -1089,7 +1164,7 @@ extern "C" bh_status bh_release_area(bh_area* a) {
   if (!c->areas.erase(a)) return fail(BH_EINVAL, "unknown area map");
   (void)hipSetDevice(c->device);
   (void)hipDeviceSynchronize();
-  dev_free(c, a->tex, a->bytes);
+  dev_recycle(c, a->tex, a->bytes);
   handle_drop(a);
   delete a;
   return BH_OK;

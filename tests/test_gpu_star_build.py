@@ -127,3 +127,50 @@ def test_every_star_is_found_by_a_frame(gpu_ctx, gpu_tables, orc, orc_tables, n0
         err = np.abs(g - o).max(1) / np.maximum(o.max(1), 1e-2 * o.max())
         assert np.percentile(err, 98) < 5e-3, float(np.percentile(err, 98))
     bh.bh_release_stars(h)
+
+
+def _level0(h, n0):
+    g = np.empty((6 * n0 * n0, 4), np.float32)
+    bh.bh_stars_download(h, 0, g.ctypes.data)
+    return g
+
+
+@pytest.mark.parametrize("budget", [0, 4 << 30])
+def test_maps_built_in_released_blocks(budget):
+    """Maps built and released in turn by two threads on streams of their own, in blocks that
+    earlier maps of other contents held, against maps of a fresh context; nothing stays counted."""
+    import threading
+    import torch
+    n0, fields = 512, [scenes.star_field(n, 30 + n % 7) for n in (40000, 41000, 300, 39500)]
+    dev = [[torch.from_numpy(a).cuda() for a in (f.dirs, f.intensity, f.temperature)]
+           for f in fields]
+    torch.cuda.synchronize()
+
+    def build(ctx, k, stream):
+        d, i, t = dev[k]
+        return bh.bh_build_stars(ctx, d.data_ptr(), i.data_ptr(), t.data_ptr(), len(d), n0,
+                                 bh.BH_TEXEL_FP16, stream.cuda_stream)
+    ref = []
+    for k in range(len(fields)):
+        ctx = bh.bh_create(0, 0)
+        ref.append(_level0(build(ctx, k, torch.cuda.Stream()), n0))
+        bh.bh_destroy(ctx)
+    ctx = bh.bh_create(0, budget)
+    base, bad = bh.bh_bytes_in_use(ctx), []
+
+    def work(first):
+        s = torch.cuda.Stream()
+        for r in range(12):
+            k = (first + r) % len(fields)
+            h = build(ctx, k, s)
+            if not np.array_equal(_level0(h, n0), ref[k]):
+                bad.append((first, r, k))
+            bh.bh_release_stars(h)
+    threads = [threading.Thread(target=work, args=(q,)) for q in (0, 2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not bad
+    assert bh.bh_bytes_in_use(ctx) == base
+    bh.bh_destroy(ctx)
