@@ -15,7 +15,7 @@
 //   k_bloom_tail  one workgroup builds the coarse levels 7..K and their U chain, which are
 //                 small (at most 120 x 68 pixels at 7680 x 4320), only when K > 7 (for
 //                 K = 7 the output pass forms the U_7 values it needs from level 6);
-//   k_bloom_up    one workgroup per 64x64 output tile (32x32 when encoding for display)
+//   k_bloom_up    one workgroup per 64x64 or 32x32 output tile (launch_bloom_up says which)
 //                 runs the U chain for levels 6..1 over the tile plus the one-pixel halo each
 //                 bilinear doubling needs, in LDS, then writes O (HBM-bound: reads the image
 //                 once more, writes O), or O's display encoding (below) in place of O.
@@ -40,16 +40,16 @@ __device__ __forceinline__ float4 box4(float4 a, float4 b, float4 c, float4 d) {
 }
 
 // bilinear blend of the four coarse neighbours of a fine pixel (fx, fy: weights of the
-// second column / row, 1/4 or 3/4)
+// second column / row, 1/4 or 3/4): two rows across, then the rows
+__device__ __forceinline__ float4 across(float4 v0, float4 v1, float fx) {
+  const float gx = 1.0f - fx;
+  return make_float4(gx * v0.x + fx * v1.x, gx * v0.y + fx * v1.y, gx * v0.z + fx * v1.z,
+                     gx * v0.w + fx * v1.w);
+}
+__device__ __forceinline__ float4 down(float4 a, float4 b, float fy) { return across(a, b, fy); }
 __device__ __forceinline__ float4 blend(float4 v00, float4 v10, float4 v01, float4 v11, float fx,
                                         float fy) {
-  const float gx = 1.0f - fx, gy = 1.0f - fy;
-  float4 a = make_float4(gx * v00.x + fx * v10.x, gx * v00.y + fx * v10.y, gx * v00.z + fx * v10.z,
-                         gx * v00.w + fx * v10.w);
-  float4 b = make_float4(gx * v01.x + fx * v11.x, gx * v01.y + fx * v11.y, gx * v01.z + fx * v11.z,
-                         gx * v01.w + fx * v11.w);
-  return make_float4(gy * a.x + fy * b.x, gy * a.y + fy * b.y, gy * a.z + fy * b.z,
-                     gy * a.w + fy * b.w);
+  return down(across(v00, v10, fx), across(v01, v11, fx), fy);
 }
 
 // ---- display encoding ------------------------------------------------------------------------
@@ -98,7 +98,9 @@ __global__ void __launch_bounds__(256)
 // LDS holds level k of the tile at local index l for every l in [0, 64 / 2^k), also beyond
 // the level's last pixel: an entry past it holds the last pixel's value (its index clamped),
 // so the next level's 2x2 averages need no clamping of their own.
-__global__ void __launch_bounds__(256)
+constexpr int kDownThreads = 512;
+
+__global__ void __launch_bounds__(kDownThreads)
     k_bloom_down(const float4* __restrict__ img, float4* __restrict__ P, BloomDev B) {
   __shared__ float4 s1[32 * 32];
   __shared__ float4 s2[16 * 16];
@@ -107,19 +109,29 @@ __global__ void __launch_bounds__(256)
   const int t = threadIdx.x;
   float4* cur = s1;
   float4* nxt = s2;
-  // level 1 from the image
+  // level 1 from the image, every load in flight before the first average
   {
+    constexpr int kEach = 32 * 32 / kDownThreads;
     const int n1x = B.w[1], n1y = B.h[1];
-    for (int l = t; l < 32 * 32; l += 256) {
-      const int lx = l & 31, ly = l >> 5;
-      const int gx = tx * 32 + lx, gy = ty * 32 + ly;
-      const int cx = min(gx, n1x - 1), cy = min(gy, n1y - 1);
-      const int x0 = 2 * cx, y0 = 2 * cy;
-      const int x1 = min(x0 + 1, B.w[0] - 1), y1 = min(y0 + 1, B.h[0] - 1);
-      const float4 v = box4(img[(size_t)y0 * B.w[0] + x0], img[(size_t)y0 * B.w[0] + x1],
-                            img[(size_t)y1 * B.w[0] + x0], img[(size_t)y1 * B.w[0] + x1]);
-      cur[l] = v;
-      if (gx < n1x && gy < n1y) P[B.off[1] + (size_t)gy * n1x + gx] = v;
+    const int lx = t & 31, gx = tx * 32 + lx, cx = min(gx, n1x - 1);
+    const int x0 = 2 * cx, x1 = min(x0 + 1, B.w[0] - 1);
+    float4 v[kEach][4];
+#pragma unroll
+    for (int j = 0; j < kEach; ++j) {
+      const int cy = min(ty * 32 + (t >> 5) + j * (kDownThreads / 32), n1y - 1);
+      const float4* r0 = img + (size_t)(2 * cy) * B.w[0];
+      const float4* r1 = img + (size_t)min(2 * cy + 1, B.h[0] - 1) * B.w[0];
+      v[j][0] = r0[x0];
+      v[j][1] = r0[x1];
+      v[j][2] = r1[x0];
+      v[j][3] = r1[x1];
+    }
+#pragma unroll
+    for (int j = 0; j < kEach; ++j) {
+      const int ly = (t >> 5) + j * (kDownThreads / 32), gy = ty * 32 + ly;
+      const float4 p = box4(v[j][0], v[j][1], v[j][2], v[j][3]);
+      cur[ly * 32 + lx] = p;
+      if (gx < n1x && gy < n1y) P[B.off[1] + (size_t)gy * n1x + gx] = p;
     }
   }
   __syncthreads();
@@ -128,7 +140,7 @@ __global__ void __launch_bounds__(256)
     const int lside = 6 - k, side = 1 << lside, pside = side * 2;
     const int nx = B.w[k], ny = B.h[k];
     const int sx = tx * side, sy = ty * side;  // the tile's first level-k pixel
-    for (int l = t; l < side * side; l += 256) {
+    for (int l = t; l < side * side; l += kDownThreads) {
       const int lx = l & (side - 1), ly = l >> lside;
       const int cx = min(sx + lx, nx - 1) - sx, cy = min(sy + ly, ny - 1) - sy;
       const float4 v = box4(cur[(2 * cy) * pside + 2 * cx], cur[(2 * cy) * pside + 2 * cx + 1],
@@ -202,38 +214,63 @@ __global__ void __launch_bounds__(256)
   }
 }
 
-// ---- the U chain and the output, per T x T output tile ------------------------------------------
+// ---- the U chain and the output, per T x T output tile -------------------------------------------
 //
-// A tile reads level-1 pixels T t / 2 - 1 .. T t / 2 + T / 2 (T / 2 + 2 per axis), level-2
-// pixels T / 4 + 2 per axis, and so on down to 3 at level 6.  Odd levels are kept in LDS
-// buffer `sa` (row stride SA), even levels in `sb` (stride SB).  Every P value a tile needs is
-// loaded into registers first, so the chain of levels waits on LDS only.
-template <int T, int K>
-struct UpLevel {
-  static constexpr int S = (K & 1) ? T / 2 + 2 : T / 4 + 2;  // LDS row stride
-  // rows of the region, at most: T / 2^K + 2 while that is at least 3, then 3
-  static constexpr int ROWS = T / (1 << K) + 2 < 3 ? 3 : T / (1 << K) + 2;
-  static constexpr int N = (S * ROWS + 255) / 256;           // slots per thread
-  static_assert(ROWS <= S, "a region's rows and columns fit the LDS row stride");
-};
-
+// A 64 x 64 tile reads level-1 pixels 32 t - 1 .. 32 t + 32 (34 per axis), level-2 pixels 18 per
+// axis, then 10, 6, 4 and 3 at level 6.  Levels 2 .. 6 together are 485 pixels, so each thread
+// owns at most one of them (and its share of level 1): its P value is loaded first, together with
+// the thread's image pixels, and the chain of levels then waits on LDS only.  A wave computes
+// only the levels it owns elements of, and two output rows at a time come from the same three
+// rows of U_1.  With every level's elements spread over all threads and one output row at a
+// time, the display form issued 829 vector instructions a wave for 4 pixels a lane: 18.4 us at
+// 1920 x 1080, now 16.2 (whole pass 26.5 -> 23.7; linear 3839 x 2158 93.7 -> 90.3).  At 1920 x
+// 1080 every workgroup is resident at once, so the phases add up instead of overlapping: about
+// 3 us each for the image's loads, the chain and the encoding.
 struct Region {
   int lox, hix, loy, hiy;
 };
 
-// P_k over the region, slot j of this thread = element threadIdx.x + 256 j of the region in
-// row-major order with row stride S (entries outside the region are not loaded)
-template <int T, int K>
-__device__ __forceinline__ void load_p(const BloomDev& B, const float4* __restrict__ P,
-                                       const Region& R, float4 (&p)[UpLevel<T, K>::N]) {
-  using L = UpLevel<T, K>;
-#pragma unroll
-  for (int j = 0; j < L::N; ++j) {
-    const int l = threadIdx.x + 256 * j;
-    const int r = l / L::S, c = l - r * L::S;
-    if (c <= R.hix - R.lox && r <= R.hiy - R.loy)
-      p[j] = P[B.off[K] + (size_t)(R.loy + r) * B.w[K] + R.lox + c];
+// Shape of the output pass: T x T tiles of TH threads.  side(k): the most pixels an axis that a
+// tile reads of level k, which is also that level's LDS row stride (T / 2^k + 2, at least 3).
+template <int T_, int TH_>
+struct UpShape {
+  static constexpr int T = T_, TH = TH_;
+  static constexpr int side(int k) { return T / (1 << k) + 2 < 3 ? 3 : T / (1 << k) + 2; }
+  // first thread that owns an element of level k >= 2
+  static constexpr int first(int k) {
+    int n = 0;
+    for (int j = 2; j < k; ++j) n += side(j) * side(j);
+    return n;
   }
+  static constexpr int kRest = first(kBloomTileLevels + 1);
+  static_assert(kRest <= TH, "one element of levels 2 .. 6 a thread");
+  static_assert(TH % T == 0 && T % (2 * (TH / T)) == 0, "whole row pairs per pass");
+};
+
+template <class S>
+struct UpLds {
+  float4 l1[S::side(1) * S::side(1)];
+  float4 rest[S::kRest];  // levels 2 .. 6, level k from S::first(k)
+  float4 u7[16];          // the level-7 neighbourhood of level 6's region (row stride 4)
+};
+
+// the thread's element of level K (>= 2): true when it owns one inside the region
+template <class S, int K>
+__device__ __forceinline__ bool up_element(const Region& R, int* r, int* c) {
+  constexpr int N = S::side(K);
+  const int e = (int)threadIdx.x - S::first(K);
+  if (e < 0 || e >= N * N) return false;
+  *r = e / N;
+  *c = e - *r * N;
+  return *c <= R.hix - R.lox && *r <= R.hiy - R.loy;
+}
+
+template <class S, int K>
+__device__ __forceinline__ void load_p(const BloomDev& B, const float4* __restrict__ P,
+                                       const Region& R, float4* p) {
+  int r, c;
+  if (up_element<S, K>(R, &r, &c))
+    *p = P[B.off[K] + (size_t)(R.loy + r) * B.w[K] + R.lox + c];
 }
 
 // U_7 = w_7 P_7 at level-7 pixel (x, y) of a pyramid of exactly 7 levels, from level 6: the
@@ -255,111 +292,58 @@ __device__ __forceinline__ Region coarse_region(const BloomDev& B, const Region&
   return Region{max((R.lox - 1) >> 1, 0), min((R.hix + 1) >> 1, B.w[K] - 1),
                 max((R.loy - 1) >> 1, 0), min((R.hiy + 1) >> 1, B.h[K] - 1)};
 }
-constexpr int kU7Max = 16;  // >= 3 x 3
 
-// U_7 over the coarse region C of a 7-level pyramid, one value per thread, into LDS `su7`
-// (row stride 4)
+// U_7 over the region C, one value per thread, into LDS `su7` (row stride 4): with exactly 7
+// levels formed from level 6, with more from the global U array the tail kernel wrote
 __device__ __forceinline__ void fill_u7(const BloomDev& B, const float4* __restrict__ P,
-                                        const Region& C, float4* su7) {
-  const int t = threadIdx.x, w = C.hix - C.lox + 1, h = C.hiy - C.loy + 1;
-  if (t < w * h) {
-    const int x = t % w, y = t / w;
-    su7[y * 4 + x] = u7_from_p6(B, P, C.lox + x, C.loy + y);
-  }
+                                        const float4* __restrict__ U, const Region& C,
+                                        float4* su7) {
+  constexpr int K = kBloomTileLevels + 1;
+  const int x = threadIdx.x & 3, y = threadIdx.x >> 2;
+  if (x > C.hix - C.lox || y > C.hiy - C.loy) return;
+  su7[threadIdx.x] = B.levels == K
+                         ? u7_from_p6(B, P, C.lox + x, C.loy + y)
+                         : U[B.off[K] + (size_t)(C.loy + y) * B.w[K] + C.lox + x];
 }
 
-// U_7 at the four coarse neighbours of every level-6 element of the region (only when the
-// pyramid has more than 6 levels): with exactly 7, from `su7` (fill_u7, region C); with
-// more, from the global U array the tail kernel wrote
-template <int T>
-__device__ __forceinline__ void load_u_coarse(const BloomDev& B, const float4* __restrict__ U,
-                                              const Region& R, const float4* su7,
-                                              const Region& C,
-                                              float4 (&q)[UpLevel<T, kBloomTileLevels>::N][4]) {
-  using L = UpLevel<T, kBloomTileLevels>;
-  constexpr int K = kBloomTileLevels;
-  const int cnx = B.w[K + 1], cny = B.h[K + 1];
-  const float4* cu = U + B.off[K + 1];
-  const bool direct = B.levels == K + 1;
-#pragma unroll
-  for (int j = 0; j < L::N; ++j) {
-    // slots outside the region load a neighbour of its last element, unused: loads that
-    // every lane issues keep the chain's waits on earlier loads exact
-    const int l = threadIdx.x + 256 * j;
-    const int r = l / L::S, c = l - r * L::S;
-    const int x = R.lox + min(c, R.hix - R.lox), y = R.loy + min(r, R.hiy - R.loy);
-    const int xa = max((x - 1) >> 1, 0), xb = min((x + 1) >> 1, cnx - 1);
-    const int ya = max((y - 1) >> 1, 0), yb = min((y + 1) >> 1, cny - 1);
-    if (direct) {
-      q[j][0] = su7[(ya - C.loy) * 4 + xa - C.lox];
-      q[j][1] = su7[(ya - C.loy) * 4 + xb - C.lox];
-      q[j][2] = su7[(yb - C.loy) * 4 + xa - C.lox];
-      q[j][3] = su7[(yb - C.loy) * 4 + xb - C.lox];
-    } else {
-      q[j][0] = cu[(size_t)ya * cnx + xa];
-      q[j][1] = cu[(size_t)ya * cnx + xb];
-      q[j][2] = cu[(size_t)yb * cnx + xa];
-      q[j][3] = cu[(size_t)yb * cnx + xb];
-    }
+// U_K = w_K P_K + up(U_{K+1}) at element (r, c) of level K's region R; `src` holds U_{K+1} over
+// the region Rs (row stride SS), absent for K = levels
+template <int K, int SS>
+__device__ __forceinline__ float4 u_value(const BloomDev& B, float4 p, const Region& R, int r,
+                                          int c, const float4* src, const Region& Rs) {
+  float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (K < B.levels) {
+    const int x = R.lox + c, y = R.loy + r, cnx = B.w[K + 1], cny = B.h[K + 1];
+    const int xa = max((x - 1) >> 1, 0) - Rs.lox, xb = min((x + 1) >> 1, cnx - 1) - Rs.lox;
+    const int ya = (max((y - 1) >> 1, 0) - Rs.loy) * SS;
+    const int yb = (min((y + 1) >> 1, cny - 1) - Rs.loy) * SS;
+    v = blend(src[ya + xa], src[ya + xb], src[yb + xa], src[yb + xb], (x & 1) ? 0.25f : 0.75f,
+              (y & 1) ? 0.25f : 0.75f);
   }
+  return f4_fma(B.wt[K], p, v);
 }
 
-// U_K = w_K P_K + up(U_{K+1}) over the region, into `dst`.  U_{K+1} comes from LDS (`src`,
-// region Rs, stride of level K + 1) for K < 6, from the preloaded values `q` for K = 6, and
-// is absent for K = levels.  The chain itself reads no global memory, so its waits cover
-// only the loads it uses.
-template <int T, int K>
-__device__ __forceinline__ void u_level(const BloomDev& B, const float4 (&p)[UpLevel<T, K>::N],
-                                        const float4 (*q)[4], const Region& R, const float4* src,
-                                        const Region& Rs, float4* dst) {
-  using L = UpLevel<T, K>;
-  constexpr int SS = UpLevel<T, K + 1>::S;
-  const float wk = B.wt[K];
-#pragma unroll
-  for (int j = 0; j < L::N; ++j) {
-    const int l = threadIdx.x + 256 * j;
-    const int r = l / L::S, c = l - r * L::S;
-    if (c > R.hix - R.lox || r > R.hiy - R.loy) continue;
-    const int x = R.lox + c, y = R.loy + r;
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (K < B.levels) {
-      float4 v00, v10, v01, v11;
-      if constexpr (K == kBloomTileLevels) {
-        v00 = q[j][0];
-        v10 = q[j][1];
-        v01 = q[j][2];
-        v11 = q[j][3];
-      } else {
-        const int cnx = B.w[K + 1], cny = B.h[K + 1];
-        const int xa = max((x - 1) >> 1, 0), xb = min((x + 1) >> 1, cnx - 1);
-        const int ya = max((y - 1) >> 1, 0), yb = min((y + 1) >> 1, cny - 1);
-        v00 = src[(ya - Rs.loy) * SS + xa - Rs.lox];
-        v10 = src[(ya - Rs.loy) * SS + xb - Rs.lox];
-        v01 = src[(yb - Rs.loy) * SS + xa - Rs.lox];
-        v11 = src[(yb - Rs.loy) * SS + xb - Rs.lox];
-      }
-      v = blend(v00, v10, v01, v11, (x & 1) ? 0.25f : 0.75f, (y & 1) ? 0.25f : 0.75f);
-    }
-    dst[l] = f4_fma(wk, p[j], v);
-  }
+// level K = 6 .. 2 of the chain: the threads that own an element write U_K
+template <class S, int K>
+__device__ __forceinline__ void u_level(const BloomDev& B, const float4& p, const Region& R,
+                                        const Region& Rs, UpLds<S>& L) {
+  int r, c;
+  if (!up_element<S, K>(R, &r, &c)) return;
+  if constexpr (K == kBloomTileLevels)
+    L.rest[threadIdx.x] = u_value<K, 4>(B, p, R, r, c, L.u7, Rs);
+  else
+    L.rest[threadIdx.x] =
+        u_value<K, S::side(K + 1)>(B, p, R, r, c, L.rest + S::first(K + 1), Rs);
 }
-
-// Output tile edge: 64 for the linear output; 32 when the pass also encodes for display, whose
-// per-pixel arithmetic (three transcendentals per channel at the end of each workgroup)
-// overlaps other workgroups' memory traffic better with four times as many of them.
-constexpr int kBloomUpTile = 64, kBloomUpTileDisplay = 32;
 
 // DISPLAY: `out` receives the display encoding of O (uint32 per pixel), else O (float4)
-template <int T, bool DISPLAY>
-__global__ void __launch_bounds__(256)
+template <class S, bool DISPLAY>
+__global__ void __launch_bounds__(S::TH)
     k_bloom_up(const float4* __restrict__ img, void* __restrict__ out,
                const float4* __restrict__ P, const float4* __restrict__ U, BloomDev B,
                float exposure) {
-  constexpr int SA = UpLevel<T, 1>::S, SB = UpLevel<T, 2>::S;
-  static_assert(UpLevel<T, 3>::S == SA && UpLevel<T, 4>::S == SB, "odd / even strides");
-  static_assert(256 % T == 0 && T % (256 / T) == 0, "whole rows per pass, whole passes per tile");
-  __shared__ float4 sa[SA * SA];
-  __shared__ float4 sb[SB * SB];
+  constexpr int T = S::T, TH = S::TH, S1 = S::side(1), N1 = (S1 * S1 + TH - 1) / TH;
+  __shared__ UpLds<S> L;
   const int ntx = (B.w[0] + T - 1) / T;
   const int tx = blockIdx.x % ntx, ty = blockIdx.x / ntx;
   const int m = min(B.levels, kBloomTileLevels);
@@ -377,61 +361,81 @@ __global__ void __launch_bounds__(256)
     R[k].loy = max((R[k - 1].loy - 1) >> 1, 0);
     R[k].hiy = min((R[k - 1].hiy + 1) >> 1, ny - 1);
   }
-  // every P value of the chain, in flight at once (levels beyond m are not loaded)
-  float4 p1[UpLevel<T, 1>::N], p2[UpLevel<T, 2>::N], p3[UpLevel<T, 3>::N],
-      p4[UpLevel<T, 4>::N], p5[UpLevel<T, 5>::N], p6[UpLevel<T, 6>::N];
-  if (m >= 6) load_p<T, 6>(B, P, R[6], p6);
-  if (m >= 5) load_p<T, 5>(B, P, R[5], p5);
-  if (m >= 4) load_p<T, 4>(B, P, R[4], p4);
-  if (m >= 3) load_p<T, 3>(B, P, R[3], p3);
-  if (m >= 2) load_p<T, 2>(B, P, R[2], p2);
-  if (m >= 1) load_p<T, 1>(B, P, R[1], p1);
-  float4 q6[UpLevel<T, 6>::N][4];
-  __shared__ float4 su7[kU7Max];
-  const Region C7 = coarse_region(B, R[6]);
-  if (B.levels == kBloomTileLevels + 1) {  // uniform: the barrier is reached by all threads
-    fill_u7(B, P, C7, su7);
-    __syncthreads();
+  // P of the chain, in flight at once (levels beyond m are not loaded)
+  float4 pk, p1[N1];
+  if (m >= 6) load_p<S, 6>(B, P, R[6], &pk);
+  if (m >= 5) load_p<S, 5>(B, P, R[5], &pk);
+  if (m >= 4) load_p<S, 4>(B, P, R[4], &pk);
+  if (m >= 3) load_p<S, 3>(B, P, R[3], &pk);
+  if (m >= 2) load_p<S, 2>(B, P, R[2], &pk);
+  if (m >= 1) {
+#pragma unroll
+    for (int j = 0; j < N1; ++j) {
+      const int l = threadIdx.x + TH * j, r = l / S1, c = l - r * S1;
+      if (c <= R[1].hix - R[1].lox && r <= R[1].hiy - R[1].loy)
+        p1[j] = P[B.off[1] + (size_t)(R[1].loy + r) * B.w[1] + R[1].lox + c];
+    }
   }
-  if (B.levels > kBloomTileLevels) load_u_coarse<T>(B, U, R[6], su7, C7, q6);
-  // this thread's image pixels (column x, rows y0 + kRows j), in flight during the chain;
+  const Region C7 = coarse_region(B, R[6]);
+  if (B.levels > kBloomTileLevels && threadIdx.x < 16) fill_u7(B, P, U, C7, L.u7);
+  // this thread's image pixels (column x, row pairs y0 + kStep j), in flight during the chain;
   // positions past the image's edge load the edge pixel, unused
-  constexpr int kRows = 256 / T, kIt = T / kRows;
+  constexpr int kStep = 2 * (TH / T), kIt = T / kStep;
   const int x = R[0].lox + (int)(threadIdx.x % T);
-  const int y0 = R[0].loy + (int)(threadIdx.x / T);
-  const bool xin = x <= R[0].hix;
-  float4 im[kIt];
+  const int y0 = R[0].loy + 2 * (int)(threadIdx.x / T);
+  float4 im[kIt][2];
 #pragma unroll
   for (int j = 0; j < kIt; ++j)
-    im[j] = img[(size_t)min(y0 + kRows * j, R[0].hiy) * B.w[0] + min(x, R[0].hix)];
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+      im[j][q] = img[(size_t)min(y0 + kStep * j + q, R[0].hiy) * B.w[0] + min(x, R[0].hix)];
   // U_k, k = m .. 1 (m is the same for the whole launch, so the barriers are uniform)
-  if (m >= 6) { u_level<T, 6>(B, p6, q6, R[6], sa, R[6], sb); __syncthreads(); }
-  if (m >= 5) { u_level<T, 5>(B, p5, nullptr, R[5], sb, R[6], sa); __syncthreads(); }
-  if (m >= 4) { u_level<T, 4>(B, p4, nullptr, R[4], sa, R[5], sb); __syncthreads(); }
-  if (m >= 3) { u_level<T, 3>(B, p3, nullptr, R[3], sb, R[4], sa); __syncthreads(); }
-  if (m >= 2) { u_level<T, 2>(B, p2, nullptr, R[2], sa, R[3], sb); __syncthreads(); }
-  if (m >= 1) { u_level<T, 1>(B, p1, nullptr, R[1], sb, R[2], sa); __syncthreads(); }
-  // O = w_0 I + up(U_1)
+  if (B.levels > kBloomTileLevels) __syncthreads();
+  if (m >= 6) { u_level<S, 6>(B, pk, R[6], C7, L); __syncthreads(); }
+  if (m >= 5) { u_level<S, 5>(B, pk, R[5], R[6], L); __syncthreads(); }
+  if (m >= 4) { u_level<S, 4>(B, pk, R[4], R[5], L); __syncthreads(); }
+  if (m >= 3) { u_level<S, 3>(B, pk, R[3], R[4], L); __syncthreads(); }
+  if (m >= 2) { u_level<S, 2>(B, pk, R[2], R[3], L); __syncthreads(); }
+  if (m >= 1) {
+#pragma unroll
+    for (int j = 0; j < N1; ++j) {
+      const int l = threadIdx.x + TH * j, r = l / S1, c = l - r * S1;
+      if (c <= R[1].hix - R[1].lox && r <= R[1].hiy - R[1].loy)
+        L.l1[l] = u_value<1, S::side(2)>(B, p1[j], R[1], r, c, L.rest, R[2]);
+    }
+    __syncthreads();
+  }
+  // O = w_0 I + up(U_1): rows 2i and 2i + 1 blend rows i - 1, i and i, i + 1 of U_1
+  if (x > R[0].hix) return;
   const float w0 = B.wt[0];
-  if (!xin) return;
+  const int cnx = B.w[1], cny = B.h[1];
+  const int xa = max((x - 1) >> 1, 0) - R[1].lox, xb = min((x + 1) >> 1, cnx - 1) - R[1].lox;
+  const float fx = (x & 1) ? 0.25f : 0.75f;
 #pragma unroll
   for (int j = 0; j < kIt; ++j) {
-    const int y = y0 + kRows * j;
+    const int y = y0 + kStep * j, i = y >> 1;
     if (y > R[0].hiy) break;
-    const size_t i = (size_t)y * B.w[0] + x;
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+    float4 h[3];  // rows i - 1, i, i + 1 of U_1 at column x
     if (B.levels >= 1) {
-      const int cnx = B.w[1], cny = B.h[1];
-      const int xa = max((x - 1) >> 1, 0) - R[1].lox, xb = min((x + 1) >> 1, cnx - 1) - R[1].lox;
-      const int ya = max((y - 1) >> 1, 0) - R[1].loy, yb = min((y + 1) >> 1, cny - 1) - R[1].loy;
-      v = blend(sa[ya * SA + xa], sa[ya * SA + xb], sa[yb * SA + xa], sa[yb * SA + xb],
-                (x & 1) ? 0.25f : 0.75f, (y & 1) ? 0.25f : 0.75f);
+      const int row[3] = {max(i - 1, 0), min(i, cny - 1), min(i + 1, cny - 1)};
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        const float4* s = L.l1 + (row[q] - R[1].loy) * S1;
+        h[q] = across(s[xa], s[xb], fx);
+      }
     }
-    const float4 o = f4_fma(w0, im[j], v);
-    if constexpr (DISPLAY)
-      store_stream(&static_cast<uint32_t*>(out)[i], display_pixel(o, exposure));
-    else
-      store_stream(&static_cast<float4*>(out)[i], o);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      if (q && y + 1 > R[0].hiy) break;
+      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (B.levels >= 1) v = down(h[q], h[q + 1], q ? 0.25f : 0.75f);
+      const float4 o = f4_fma(w0, im[j][q], v);
+      const size_t at = (size_t)(y + q) * B.w[0] + x;
+      if constexpr (DISPLAY)
+        store_stream(&static_cast<uint32_t*>(out)[at], display_pixel(o, exposure));
+      else
+        store_stream(&static_cast<float4*>(out)[at], o);
+    }
   }
 }
 
@@ -442,12 +446,43 @@ hipError_t launch_tonemap(const float4* in, uint32_t* out, int64_t n, float expo
   return hipGetLastError();
 }
 
+template <int T, int TH, bool DISPLAY>
+static void up(const float4* in, void* out, const float4* P, const float4* U, const BloomDev& B,
+               float exposure, hipStream_t s) {
+  const int tiles = ((B.w[0] + T - 1) / T) * ((B.h[0] + T - 1) / T);
+  hipLaunchKernelGGL((k_bloom_up<UpShape<T, TH>, DISPLAY>), dim3(tiles), dim3(TH), 0, s, in, out,
+                     P, U, B, exposure);
+}
+
+// Output tiles.  64 x 64 tiles of 16 waves read the least around each tile, but a small image
+// has too few of them to fill the chip: below kUpFewTiles (about 960 x 540) 32 x 32 tiles of 8
+// waves (640 x 360 display: 11.4 against 13.3 us; 1280 x 720: 21.1 against 18.4).  With the
+// encoding's arithmetic, images of many rounds of workgroups overlap better in small ones: 7680 x
+// 4320 display 289 us in 32 x 32 tiles of 4 waves, 305 in 64 x 64; 3840 x 2160 85 against 83.
+constexpr int kUpFewTiles = 128, kUpManyTiles = 4096;
+
+static hipError_t launch_bloom_up(const float4* in, void* out, const float4* P, const float4* U,
+                                  const BloomDev& B, bool display, float exposure,
+                                  hipStream_t s) {
+  const int tiles = B.tiles_x * B.tiles_y;
+  if (tiles < kUpFewTiles) {
+    display ? up<32, 512, true>(in, out, P, U, B, exposure, s)
+            : up<32, 512, false>(in, out, P, U, B, exposure, s);
+  } else if (display) {
+    tiles > kUpManyTiles ? up<32, 256, true>(in, out, P, U, B, exposure, s)
+                         : up<64, 1024, true>(in, out, P, U, B, exposure, s);
+  } else {
+    up<64, 1024, false>(in, out, P, U, B, exposure, s);
+  }
+  return hipGetLastError();
+}
+
 // display: write the display encoding of O (exposure) to `out` (uint32 per pixel), else O
 hipError_t launch_bloom(const float4* in, void* out, float4* P, float4* U, const BloomDev& B,
                         bool display, float exposure, hipStream_t s) {
   const int tiles = B.tiles_x * B.tiles_y;
   if (B.levels >= 1) {
-    hipLaunchKernelGGL(k_bloom_down, dim3(tiles), dim3(256), 0, s, in, P, B);
+    hipLaunchKernelGGL(k_bloom_down, dim3(tiles), dim3(kDownThreads), 0, s, in, P, B);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -462,15 +497,7 @@ hipError_t launch_bloom(const float4* in, void* out, float4* P, float4* U, const
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  const int T = display ? kBloomUpTileDisplay : kBloomUpTile;
-  const int ut = ((B.w[0] + T - 1) / T) * ((B.h[0] + T - 1) / T);
-  if (display)
-    hipLaunchKernelGGL((k_bloom_up<kBloomUpTileDisplay, true>), dim3(ut), dim3(256), 0, s, in,
-                       out, P, U, B, exposure);
-  else
-    hipLaunchKernelGGL((k_bloom_up<kBloomUpTile, false>), dim3(ut), dim3(256), 0, s, in, out, P,
-                       U, B, exposure);
-  return hipGetLastError();
+  return launch_bloom_up(in, out, P, U, B, display, exposure, s);
 }
 
 }  // namespace bh
