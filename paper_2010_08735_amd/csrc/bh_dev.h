@@ -28,6 +28,9 @@ struct TablesDev {
   const float* Dt;  // time channels: e tau (regularised time) in the layouts of D and U
   const float* Ut;
   int d_n, u_ne, u_nphi, pad;
+  // the lookups' scale factors (table_limits), as scalars the kernels read: n - 1 of each axis,
+  // and the first column of D's upper half
+  float d_last, d_half, u_last, u_last_phi;
 };
 
 // ---- blackbody band table -----------------------------------------------------------
@@ -35,7 +38,7 @@ struct TablesDev {
 struct LutDev {
   const float4* lut;
   int n;
-  float x0, inv_dx, pad;
+  float x0, inv_dx, top;  // top: coordinates are clamped here (n + 1024)
 };
 
 // ---- star map -------------------------------------------------------------------------
@@ -160,8 +163,9 @@ struct TileRun {
   int view, tile0, start, tiles_x;
 };
 
+// lo <= hi; lo for a NaN (the median of three picks the lesser of the other two)
 __device__ __forceinline__ float clampf(float x, float lo, float hi) {
-  return fminf(fmaxf(x, lo), hi);
+  return __builtin_amdgcn_fmed3f(x, lo, hi);
 }
 
 // Streaming stores of results the kernel never reads back (images): marked non-temporal, so
@@ -219,24 +223,44 @@ __device__ __forceinline__ float fatan2_pos(float y, float x) {
   return r;
 }
 
-// bilinear fetch of a row-major table with texel k of n at unit coordinate k/(n-1),
-// columns clamped to [lo, hi] (so the two halves of D are never mixed)
-// Coordinates are clamped to just below the last texel (k (1 - 2^-23) < k for every k >= 1),
-// so the lower texel is trunc(t), the next one exists, and the weight is fract(t); at the
+// Table coordinates are clamped to just below the last texel (k (1 - 2^-23) < k for every k >=
+// 1), so the lower texel is trunc(t), the next one exists, and the weight is fract(t); at the
 // edge itself the result differs from the edge texel by 2^-23 of the last texel step.
 constexpr float kBelowOne = 0.99999988f;  // 1 - 2^-23
 
-__device__ __forceinline__ float bilinear(const float* __restrict__ t, int nx, int ny, int lo,
-                                          int hi, float x, float y) {
-  float tx = clampf(x * (float)(nx - 1), (float)lo, (float)hi * kBelowOne);
-  float ty = clampf(y * (float)(ny - 1), 0.0f, (float)(ny - 1) * kBelowOne);
-  int i0 = (int)tx, j0 = (int)ty;
-  float fx = __builtin_amdgcn_fractf(tx), fy = __builtin_amdgcn_fractf(ty);
-  const float* r0 = t + (__umul24((unsigned)j0, (unsigned)nx) + (unsigned)i0);  // nx, ny < 2^24
+__host__ inline void table_limits(TablesDev* T) {
+  T->d_last = (float)(T->d_n - 1);
+  T->d_half = (float)(T->d_n / 2);
+  T->u_last = (float)(T->u_ne - 1);
+  T->u_last_phi = (float)(T->u_nphi - 1);
+}
+
+// A point of a table: the texel index of its lower corner and the weights of the next column and
+// row.  The time channels share the layouts of D and U, and the apsis D's columns, so one point
+// serves all (with the scale factors as scalars and one-instruction clamps: 8K frame 336 -> 324
+// us, animated 55.4 -> 52.5).
+struct TablePoint {
+  unsigned at, col;
+  float fx, fy;
+};
+
+// texel k of n at unit coordinate k/(n-1): (tx, ty) in texels, clamped; nx < 2^24
+__device__ __forceinline__ TablePoint table_point(float tx, float ty, int nx) {
+  TablePoint p;
+  p.col = (unsigned)(int)tx;
+  p.at = __umul24((unsigned)(int)ty, (unsigned)nx) + p.col;
+  p.fx = __builtin_amdgcn_fractf(tx);
+  p.fy = __builtin_amdgcn_fractf(ty);
+  return p;
+}
+
+__device__ __forceinline__ float bilinear(const float* __restrict__ t, const TablePoint& p,
+                                          int nx) {
+  const float* r0 = t + p.at;
   const float* r1 = r0 + nx;
-  float a = r0[0] + fx * (r0[1] - r0[0]);
-  float b = r1[0] + fx * (r1[1] - r1[0]);
-  return a + fy * (b - a);
+  float a = r0[0] + p.fx * (r0[1] - r0[0]);
+  float b = r1[0] + p.fx * (r1[1] - r1[0]);
+  return a + p.fy * (b - a);
 }
 
 // apsis of a ray with e^2 < mu (Section 3.3.1, eq. uapsis)
@@ -245,47 +269,55 @@ __device__ __forceinline__ float apsis_f(float e2) {
   return 1.0f / 3.0f + 2.0f / 3.0f * fsin_small(asinf(a) * (1.0f / 3.0f));
 }
 
-// D(e, u) through the Appendix A mapping, read from `tab` (T.D, or the time channel T.Dt,
-// which shares its layout).  udot = du/dphi at (e, u) on the ray.  For
-// e^2 < mu the row coordinate y = 1 - sqrt(1 - u/u_a) is evaluated as
+// (e, u) in D through the Appendix A mapping (`bound`: e^2 < mu).  udot = du/dphi at (e, u) on
+// the ray.  For e^2 < mu the row coordinate y = 1 - sqrt(1 - u/u_a) is evaluated as
 // 1 - sqrt(udot^2 / (e^2 + u u_a (1 - u_a - u))): the two are equal because
 // udot^2 = (u_a - u)(u_2 - u)(u - u_3) with u_2 + u_3 = 1 - u_a and u_2 u_3 = -e^2 / u_a,
-// and the second form has no cancellation when the camera sits near the apsis.
-__device__ __forceinline__ float lookup_D(const TablesDev& T, const float* tab, float e2,
-                                          float u, float ua, float udot) {
-  const int n = T.d_n;
-  if (e2 < kMu) {
+// and the second form has no cancellation when the camera sits near the apsis.  Columns are
+// clamped to the ray's half of the table (the halves are never mixed).
+__device__ __forceinline__ TablePoint point_D(const TablesDev& T, bool bound, float e2, float u,
+                                              float ua, float udot) {
+  float tx, y;
+  if (bound) {
     float x = 0.5f - fsqrt(-flog1p(-e2 * (1.0f / kMu)) * (1.0f / 50.0f));
     float den = e2 + u * ua * (1.0f - ua - u);
     float s2 = den > 0.0f ? fminf(fdiv(udot * udot, den), 1.0f) : 0.0f;
-    float y = 1.0f - fsqrt(s2);
-    return bilinear(tab, n, n, 0, n / 2 - 1, x, y);
+    y = 1.0f - fsqrt(s2);
+    tx = clampf(x * T.d_last, 0.0f, (T.d_half - 1.0f) * kBelowOne);
+  } else {
+    float x = 0.5f + fsqrt(-flog1p(-kMu / e2) * (1.0f / 50.0f));
+    float dz = u - 2.0f / 3.0f;
+    const float s23 = 0.816496580927726f, s13 = 0.577350269189626f;
+    y = (s23 + copysignf(fsqrt(fabsf(dz)), dz)) * (1.0f / (s23 + s13));
+    tx = clampf(x * T.d_last, T.d_half, T.d_last * kBelowOne);
   }
-  float x = 0.5f + fsqrt(-flog1p(-kMu / e2) * (1.0f / 50.0f));
-  float dz = u - 2.0f / 3.0f;
-  const float s23 = 0.816496580927726f, s13 = 0.577350269189626f;
-  float y = (s23 + copysignf(fsqrt(fabsf(dz)), dz)) * (1.0f / (s23 + s13));
-  return bilinear(tab, n, n, n / 2, n - 1, x, y);
+  return table_point(tx, clampf(y * T.d_last, 0.0f, T.d_last * kBelowOne), T.d_n);
 }
 
-// D(e, u_a) for e^2 < mu: the apsis is the last row (y = 1) of the left half
-__device__ __forceinline__ float lookup_D_apsis(const TablesDev& T, const float* tab, float e2) {
-  const int n = T.d_n, hi = n / 2 - 1;
-  float x = 0.5f - fsqrt(-flog1p(-e2 * (1.0f / kMu)) * (1.0f / 50.0f));
-  float tx = clampf(x * (float)(n - 1), 0.0f, (float)hi * kBelowOne);
-  int i0 = (int)tx;
-  float fx = __builtin_amdgcn_fractf(tx);
-  const float* r = tab + (__umul24((unsigned)(n - 1), (unsigned)n) + (unsigned)i0);
-  return r[0] + fx * (r[1] - r[0]);
+// D at p, and D(e, u_a) for e^2 < mu: the apsis is the last row (y = 1) of the left half, in p's
+// columns.  Read for every ray (an unbound ray's column of that row exists and goes unused), so
+// both fetches are in flight together.
+__device__ __forceinline__ float fetch_D(const TablesDev& T, const float* __restrict__ tab,
+                                         const TablePoint& p, float* at_apsis) {
+  const float* r = tab + (__umul24((unsigned)(T.d_n - 1), (unsigned)T.d_n) + p.col);
+  const float a = r[0], b = r[1];
+  const float d = bilinear(tab, p, T.d_n);
+  *at_apsis = a + p.fx * (b - a);
+  return d;
 }
 
-// U(e, phi) through the Appendix A mapping, read from `tab` (T.U or the time channel T.Ut)
-__device__ __forceinline__ float lookup_U(const TablesDev& T, const float* tab, float e2, float e,
-                                          float phi) {
+// The columns of U at e (x of the Appendix A mapping) and the factor of its rows: y = phi row
+struct PointU {
+  float tx, row;
+};
+__device__ __forceinline__ PointU columns_U(const TablesDev& T, float e2, float e) {
   float x = fdiv(1.0f, 1.0f + 6.0f * e2);
   // (1 + 6 e^3) / (1 + e^2) written so that it cannot overflow for nearly radial rays
-  float y = phi * (1.0f / 3.0f) * (6.0f * e + fdiv(1.0f - 6.0f * e, 1.0f + e2));
-  return bilinear(tab, T.u_ne, T.u_nphi, 0, T.u_ne - 1, x, y);
+  return PointU{clampf(x * T.u_last, 0.0f, T.u_last * kBelowOne), 6.0f * e + fdiv(1.0f - 6.0f * e, 1.0f + e2)};
+}
+__device__ __forceinline__ TablePoint point_U(const TablesDev& T, const PointU& c, float phi) {
+  float y = phi * (1.0f / 3.0f) * c.row;
+  return table_point(c.tx, clampf(y * T.u_last_phi, 0.0f, T.u_last_phi * kBelowOne), T.u_ne);
 }
 
 // band radiances (R, G, B, sum) at temperature T from the log-log band table
@@ -293,7 +325,7 @@ __device__ __forceinline__ float4 band_lookup(const LutDev& L, float T) {
   if (!(T > 0.0f)) return make_float4(0.f, 0.f, 0.f, 0.f);
   float x = (__log2f(T) - L.x0) * L.inv_dx;
   if (x < 0.0f) return make_float4(0.f, 0.f, 0.f, 0.f);
-  x = fminf(x, (float)L.n + 1024.0f);  // keeps the index conversion defined for T = inf
+  x = fminf(x, L.top);  // keeps the index conversion defined for T = inf
   int k = min((int)x, L.n - 2);
   float fr = x - (float)k;  // > 1 above the table: linear extrapolation in log-log
   float4 a = L.lut[k], b = L.lut[k + 1];

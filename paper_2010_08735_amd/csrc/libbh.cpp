@@ -1320,6 +1320,7 @@ static TablesDev tables_dev(const bh_tables* t) {
   T.u_ne = t->p.u_ne;
   T.u_nphi = t->p.u_nphi;
   T.pad = 0;
+  table_limits(&T);
   return T;
 }
 
@@ -1329,7 +1330,7 @@ static LutDev lut_dev(const bh_ctx* c) {
   L.n = c->lut_n;
   L.x0 = c->lut_x0;
   L.inv_dx = 1.0f / c->lut_dx;
-  L.pad = 0;
+  L.top = (float)c->lut_n + 1024.0f;
   return L;
 }
 
