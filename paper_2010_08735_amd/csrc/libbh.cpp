@@ -50,6 +50,7 @@ hipError_t launch_area_build(const float* it, int n0, float2* tex, int* bad, hip
 hipError_t launch_area_build_bands(const float* rgbx, int n0, float4* tex, int* bad,
                                    hipStream_t s);
 hipError_t launch_cshift_build(const CshiftRule& q, double4* spec, float4* tab, hipStream_t s);
+hipError_t launch_cshift_nodes(const float4* tab, float4* out, hipStream_t s);
 hipError_t launch_render_batch(int cfg, int persistent, int feat, const ViewDev* views,
                                const TileRun* runs, int nruns, int ntiles, int* counter,
                                const TablesDev& T, const LutDev& L, int grid, hipStream_t s);
@@ -1140,8 +1141,13 @@ extern "C" bh_status bh_color_shift_table_download(bh_ctx* c, float* host) {
   HIPCHK(hipSetDevice(c->device));
   bh_status st = ensure_cshift(c, nullptr);
   if (st) return st;
-  HIPCHK(hipMemcpy(host, c->ctab, sizeof(float4) * kCshiftN * kCshiftN * kCshiftN,
-                   hipMemcpyDeviceToHost));
+  const size_t bytes = sizeof(float4) * kCshiftN * kCshiftN * kCshiftN;
+  float4* tmp = nullptr;
+  HIPCHK(hipMalloc(&tmp, bytes));
+  hipError_t e = launch_cshift_nodes(c->ctab, tmp, nullptr);
+  if (e == hipSuccess) e = hipMemcpy(host, tmp, bytes, hipMemcpyDeviceToHost);
+  (void)hipFree(tmp);
+  if (e != hipSuccess) return fail(BH_EDEVICE, hipGetErrorString(e));
   return BH_OK;
 }
 

@@ -190,7 +190,7 @@ __device__ __forceinline__ void gather(const void* tex, const Footprint& F, cons
     weigh(x0, i0, true);
     weigh(x1, i1, two);
   };
-  if constexpr (PAIR && (FMT == kTexIT16 || FMT == kTexIT32)) {
+  if constexpr (PAIR) {
     while (lo) {
       const int i0 = __builtin_ctzll(lo);
       lo &= lo - 1u;
@@ -209,8 +209,9 @@ __device__ __forceinline__ void gather(const void* tex, const Footprint& F, cons
     }
   } else {
     // band texels are twice as wide: one tap per iteration keeps the band kernels' register
-    // budget (two in flight spilled 19 registers at 8 waves per SIMD), and the kernel for
-    // band star maps without area maps takes (I, T) maps one tap at a time too (PAIR)
+    // budget (two in flight spilled 19 registers at 8 waves per SIMD, and gave nothing at 5: the
+    // 1080p any-colour frame 109.3 us with, 108.7 without), and the kernel for band star maps
+    // without area maps takes (I, T) maps one tap at a time too (PAIR)
     auto one_tap = [&](int i) {
       if (COUNT) {
         const uint32_t ta = F.texel0 + at(i);
@@ -545,152 +546,283 @@ __device__ __forceinline__ FaceOf face_of(float p0, float p1, float p2) {
 template <bool BANDS> struct AreaTexel { using type = float2; };
 template <> struct AreaTexel<true> { using type = float4; };
 
-__device__ __forceinline__ float2 lerp_texel(float f, float2 a, float2 b) {
-  return make_float2(fmaf(f, b.x - a.x, a.x), fmaf(f, b.y - a.y, a.y));
-}
-__device__ __forceinline__ float4 lerp_texel(float f, float4 a, float4 b) {
-  return make_float4(fmaf(f, b.x - a.x, a.x), fmaf(f, b.y - a.y, a.y), fmaf(f, b.z - a.z, a.z),
-                     0.0f);
+// One level of the map as a probe reads it
+struct AreaLevel {
+  uint32_t first;        // its texel 0
+  int nL, last;          // last = max(nL - 2, 0)
+  float half, off, top;  // nL / 2, nL / 2 - 1/2, nL - 1
+};
+__device__ __forceinline__ AreaLevel area_level(const AreaDev& M, int L) {
+  AreaLevel a;
+  a.nL = M.n0 >> L;
+  a.last = max(a.nL - 2, 0);
+  a.first = 8u * ((uint32_t)M.n0 * (uint32_t)M.n0 - (uint32_t)a.nL * (uint32_t)a.nL);
+  const float fn = (float)a.nL;
+  a.half = 0.5f * fn;
+  a.off = fmaf(0.5f, fn, -0.5f);
+  a.top = fn - 1.0f;
+  return a;
 }
 
-// every channel of level L, bilinear, at face coordinates (U, V) of `face`
+// The 2 x 2 texels of a level around face coordinates (U, V) of `face`, and the position between
+// them.  On the level of one texel a face the read starts at that texel, but three texels before
+// the map's end at the latest, and area_add picks the face's own.
 template <bool BANDS>
-__device__ __forceinline__ typename AreaTexel<BANDS>::type area_fetch(const AreaDev& M, int L,
-                                                                      int face, float U,
-                                                                      float V) {
-  using Tx = typename AreaTexel<BANDS>::type;
-  const int nL = M.n0 >> L;
-  const uint32_t level0 = 8u * ((uint32_t)M.n0 * (uint32_t)M.n0 - (uint32_t)nL * (uint32_t)nL);
-  const Tx* t = (const Tx*)M.tex + level0 + (uint32_t)face * (uint32_t)nL * (uint32_t)nL;
-  if (nL == 1) return t[0];
-  const float fn = (float)nL, top = fn - 1.0f;
-  const float x = clampf(fmaf(0.5f * fn, U + 1.0f, -0.5f), 0.0f, top);
-  const float y = clampf(fmaf(0.5f * fn, V + 1.0f, -0.5f), 0.0f, top);
-  const int i0 = min((int)x, nL - 2), j0 = min((int)y, nL - 2);
-  const float fx = x - (float)i0, fy = y - (float)j0;
-  const Tx* r0 = t + (uint32_t)j0 * (uint32_t)nL + (uint32_t)i0;
-  const Tx a = r0[0], b = r0[1], c = r0[nL], e = r0[nL + 1];
-  return lerp_texel(fy, lerp_texel(fx, a, b), lerp_texel(fx, c, e));
-}
-
-// length, in level-0 texels, of the face-coordinate change along direction change (xk, xa,
-// xb) (components in the face's axis order) at d' (im = 1 / |d'_k|, sg = sign of d'_k,
-// (U, V) of d')
-__device__ __forceinline__ float area_axis(float im, float sg, float U, float V, float xk,
-                                           float xa, float xb, float half_n0) {
-  const float dU = (xa - U * sg * xk) * im, dV = (xb - V * sg * xk) * im;
-  return half_n0 * fsqrt(dU * dU + dV * dV);
-}
-
-// mean (I, I T) of the map over the footprint of d' with axes dw, dh, or mean (R, G, B)
-// of a band map (BANDS, into A, B, C)
+struct AreaQuad {
+  typename AreaTexel<BANDS>::type a, b, c, e;
+  float fx, fy;
+};
 template <bool BANDS>
-__device__ __forceinline__ void area_filter(const AreaDev& M, float d0, float d1, float d2,
-                                            float w0, float w1, float w2, float h0, float h1,
-                                            float h2, float& A, float& B, float& Cc) {
+__device__ __forceinline__ AreaQuad<BANDS> area_read(const AreaDev& M, const AreaLevel& A,
+                                                     int face, float U, float V) {
+  const float x = clampf(fmaf(A.half, U, A.off), 0.0f, A.top);
+  const float y = clampf(fmaf(A.half, V, A.off), 0.0f, A.top);
+  const int i0 = min((int)x, A.last), j0 = min((int)y, A.last);
+  AreaQuad<BANDS> q;
+  q.fx = x - (float)i0;
+  q.fy = y - (float)j0;
+  // face nL + j0 and nL have 24 bits at most; a map has 2 GiB at most (n0 <= 4096), so the offset
+  // stays in 32 bits beside the map's address
+  const uint32_t nL = (uint32_t)A.nL;
+  const uint32_t first = __umul24(__umul24((uint32_t)face, nL) + (uint32_t)j0, nL) +
+                         (A.first + (uint32_t)i0);
+  const uint32_t end = 8u * (uint32_t)M.n0 * (uint32_t)M.n0 - 2u;
   using Tx = typename AreaTexel<BANDS>::type;
-  const FaceOf c = face_of(d0, d1, d2);
-  const int k = c.k;
-  auto perm = [k](float x0, float x1, float x2, float& xk, float& xa, float& xb) {
-    xk = k == 0 ? x0 : (k == 1 ? x1 : x2);
-    xa = k == 0 ? x1 : (k == 1 ? x2 : x0);
-    xb = k == 0 ? x2 : (k == 1 ? x0 : x1);
-  };
+  const uint32_t at = min(first, end - 3u) * (uint32_t)sizeof(Tx);
+  const Tx* r0 = (const Tx*)((const char*)M.tex + at);
+  const Tx* r1 = (const Tx*)((const char*)M.tex + (at + nL * (uint32_t)sizeof(Tx)));
+  q.a = r0[0];
+  q.b = r0[1];
+  q.c = r1[0];
+  q.e = r1[1];
+  return q;
+}
+// s += weight * (the bilinear value of q)
+template <bool BANDS>
+__device__ __forceinline__ void area_add(const AreaQuad<BANDS>& q, float weight, int nL,
+                                         int face, float3& s) {
+  if (nL == 1) {
+    auto own = [&](float a, float b, float e) { return face < 4 ? a : (face == 4 ? b : e); };
+    s.x = fmaf(weight, own(q.a.x, q.b.x, q.e.x), s.x);
+    s.y = fmaf(weight, own(q.a.y, q.b.y, q.e.y), s.y);
+    if constexpr (BANDS) s.z = fmaf(weight, own(q.a.z, q.b.z, q.e.z), s.z);
+    return;
+  }
+  const float y1 = q.fy * weight, y0 = weight - y1;
+  const float wb = q.fx * y0, we = q.fx * y1, wa = y0 - wb, wc = y1 - we;
+  s.x = fmaf(we, q.e.x, fmaf(wc, q.c.x, fmaf(wb, q.b.x, fmaf(wa, q.a.x, s.x))));
+  s.y = fmaf(we, q.e.y, fmaf(wc, q.c.y, fmaf(wb, q.b.y, fmaf(wa, q.a.y, s.y))));
+  if constexpr (BANDS) s.z = fmaf(we, q.e.z, fmaf(wc, q.c.z, fmaf(wb, q.b.z, fmaf(wa, q.a.z, s.z))));
+}
+
+// The footprint of d' on the face of its centre, shared by the star gather and the area filter:
+// the axes d_w d', d_h d' in the face's component order and their face-coordinate changes
+// (J00, J10) and (J01, J11).
+struct FaceFootprint {
+  FaceOf c;
+  float im, sg, U, V;              // 1 / |d'_k|, sign of d'_k, face coordinates of d'
   float wk, wa, wb, hk, ha, hb;
-  perm(w0, w1, w2, wk, wa, wb);
-  perm(h0, h1, h2, hk, ha, hb);
-  const float im = fdiv(1.0f, c.m), sg = c.pk < 0.0f ? -1.0f : 1.0f;
-  const float U = c.pa * im, V = c.pb * im, half_n0 = 0.5f * (float)M.n0;
-  const float la = area_axis(im, sg, U, V, wk, wa, wb, half_n0);
-  const float lb = area_axis(im, sg, U, V, hk, ha, hb, half_n0);
+  float J00, J01, J10, J11;
+};
+
+__device__ __forceinline__ FaceFootprint face_footprint(float d0, float d1, float d2, float w0,
+                                                        float w1, float w2, float h0, float h1,
+                                                        float h2) {
+  FaceFootprint f;
+  f.c = face_of(d0, d1, d2);
+  const int k = f.c.k;
+  f.wk = k == 0 ? w0 : (k == 1 ? w1 : w2);
+  f.wa = k == 0 ? w1 : (k == 1 ? w2 : w0);
+  f.wb = k == 0 ? w2 : (k == 1 ? w0 : w1);
+  f.hk = k == 0 ? h0 : (k == 1 ? h1 : h2);
+  f.ha = k == 0 ? h1 : (k == 1 ? h2 : h0);
+  f.hb = k == 0 ? h2 : (k == 1 ? h0 : h1);
+  f.sg = f.c.pk < 0.0f ? -1.0f : 1.0f;
+  f.im = fdiv(1.0f, f.c.m);
+  f.U = f.c.pa * f.im;
+  f.V = f.c.pb * f.im;
+  f.J00 = (f.wa - f.U * f.sg * f.wk) * f.im;
+  f.J01 = (f.ha - f.U * f.sg * f.hk) * f.im;
+  f.J10 = (f.wb - f.V * f.sg * f.wk) * f.im;
+  f.J11 = (f.hb - f.V * f.sg * f.hk) * f.im;
+  return f;
+}
+
+// The probes of a footprint, in the component order (k, k + 1, k + 2) of the face of d'
+struct AreaProbes {
+  int k, face;              // axis and face of d'
+  bool one_face;            // every probe lies on that face
+  float pk, pa, pb;         // d'
+  float jk, ja, jb;         // major axis
+  float nk, na, nb;         // minor axis
+  int n, minor;             // number of probes, and along the minor axis (1 or 2)
+  float inv;                // 1 / number along the major axis
+};
+struct AreaAt { int face; float u, v; };
+
+// where probe i (i < n) reads: the minor axis runs fastest
+__device__ __forceinline__ AreaAt area_at(const AreaProbes& P, int i) {
+  const float ta = fmaf((float)(i >> (P.minor - 1)) + 0.5f, P.inv, -0.5f);
+  const float tb = P.minor == 1 ? 0.0f : ((i & 1) ? 0.25f : -0.25f);
+  const float pk = fmaf(tb, P.nk, fmaf(ta, P.jk, P.pk));
+  const float pa = fmaf(tb, P.na, fmaf(ta, P.ja, P.pa));
+  const float pb = fmaf(tb, P.nb, fmaf(ta, P.jb, P.pb));
+  AreaAt at;
+  float m = fabsf(pk), u = pa, v = pb;
+  at.face = P.face;
+  if (!P.one_face) {
+    const FaceOf f = face_of(pk, pa, pb);
+    int k = P.k + f.k;
+    k = k > 2 ? k - 3 : k;
+    at.face = 2 * k + (f.pk < 0.0f);
+    m = f.m;
+    u = f.pa;
+    v = f.pb;
+  }
+  const float im = fdiv(1.0f, m);
+  at.u = u * im;
+  at.v = v * im;
+  return at;
+}
+
+// mean (I, I T) of the map over the footprint f of d', or mean (R, G, B) of a band map (BANDS,
+// into A, B, C).  PAIR: two probes per iteration also where two levels are read.
+template <bool BANDS, bool PAIR>
+__device__ __forceinline__ void area_filter(const AreaDev& M, const FaceFootprint& f, float& A,
+                                            float& B, float& Cc) {
+  const float half_n0 = 0.5f * (float)M.n0;
+  // axis lengths in level-0 texels
+  const float la = half_n0 * fsqrt(f.J00 * f.J00 + f.J10 * f.J10);
+  const float lb = half_n0 * fsqrt(f.J01 * f.J01 + f.J11 * f.J11);
   const bool swap = lb > la;
   const float lmaj = swap ? lb : la, lmin = swap ? la : lb;
-  // the axes in world order (probes whose face is looked up) and in the face's order
-  const float j0 = swap ? h0 : w0, j1 = swap ? h1 : w1, j2 = swap ? h2 : w2;   // major
-  const float n0_ = swap ? w0 : h0, n1 = swap ? w1 : h1, n2 = swap ? w2 : h2;  // minor
-  const float jk = swap ? hk : wk, ja = swap ? ha : wa, jb = swap ? hb : wb;
-  const float nk = swap ? wk : hk, na = swap ? wa : ha, nb = swap ? wb : hb;
   const float spc = fmaxf(0.5f * lmin, 0.5f), ispc = fdiv(1.0f, spc);
   const int nmaj = (int)clampf(ceilf(lmaj * ispc), 1.0f, 16.0f);
   const int nmin = lmin * ispc > 1.0f ? 2 : 1;
-  const float fmaj = (float)nmaj, fmin = (float)nmin;
-  const float sp = fmaxf(fdiv(lmaj, fmaj), fdiv(lmin, fmin));
-  float lam = sp > 0.0f ? __log2f(sp) - 1.0f : 0.0f;
-  lam = clampf(lam, 0.0f, (float)(M.levels - 1));
-  const int L0 = (int)lam, L1 = min(L0 + 1, M.levels - 1);
-  const float fr = lam - (float)L0;
-  const bool two = fr > 0.0f && L1 != L0;  // the second level has weight
-  // The directions on one face form a convex set of (w, h) (an intersection of half-planes),
-  // so when the parallelogram's four corners lie on the face of d', every probe does too and
-  // its face coordinates follow from the axes in the face's order without a face lookup.
-  bool one_face = true;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const float sa_ = (q & 1) ? 0.5f : -0.5f, sb_ = (q & 2) ? 0.5f : -0.5f;
-    const FaceOf f = face_of(fmaf(sb_, n0_, fmaf(sa_, j0, d0)), fmaf(sb_, n1, fmaf(sa_, j1, d1)),
-                             fmaf(sb_, n2, fmaf(sa_, j2, d2)));
-    one_face = one_face && f.face == c.face;
-  }
-  float sa = 0.0f, sb = 0.0f, sc = 0.0f;
-  const float inv = fdiv(1.0f, fmaj);
-  for (int i = 0; i < nmaj; ++i) {
-    const float ta = fmaf((float)i + 0.5f, inv, -0.5f);
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      if (b >= nmin) break;
-      const float tb = nmin == 1 ? 0.0f : (b == 0 ? -0.25f : 0.25f);
-      int face;
-      float pu, pv;
-      if (one_face) {
-        const float pk = fmaf(tb, nk, fmaf(ta, jk, c.pk));
-        const float ip = fdiv(1.0f, fabsf(pk));
-        pu = fmaf(tb, na, fmaf(ta, ja, c.pa)) * ip;
-        pv = fmaf(tb, nb, fmaf(ta, jb, c.pb)) * ip;
-        face = c.face;
-      } else {
-        const FaceOf f = face_of(fmaf(tb, n0_, fmaf(ta, j0, d0)), fmaf(tb, n1, fmaf(ta, j1, d1)),
-                                 fmaf(tb, n2, fmaf(ta, j2, d2)));
-        const float ip = fdiv(1.0f, f.m);
-        pu = f.pa * ip;
-        pv = f.pb * ip;
-        face = f.face;
+  float3 sum = make_float3(0.0f, 0.0f, 0.0f);
+  const AreaLevel l0 = area_level(M, 0);
+  // A footprint within half a texel takes one probe, at d' itself and on level 0 (its spacing is
+  // at most half a texel): no corners, levels or probe loop.  Most of a frame magnifies the map;
+  // a wave of such pixels skips the rest.
+  if (nmaj == 1 && nmin == 1) {
+    area_add<BANDS>(area_read<BANDS>(M, l0, f.c.face, f.U, f.V), 1.0f, l0.nL, f.c.face, sum);
+  } else {
+    const float fmaj = (float)nmaj, fmin = (float)nmin;
+    const float sp = fmaxf(fdiv(lmaj, fmaj), fdiv(lmin, fmin));
+    float lam = sp > 0.0f ? __log2f(sp) - 1.0f : 0.0f;
+    lam = clampf(lam, 0.0f, (float)(M.levels - 1));
+    // The directions on one face form a convex set of (w, h) (an intersection of half-planes),
+    // so when the parallelogram's four corners lie on the face of d', every probe does too and
+    // needs no face lookup.  The corners lie on it when |p_k| - |p_a| and |p_k| - |p_b| stay
+    // positive there: four linear functions of (w, h), least at the corner where both axes lower
+    // them.
+    auto least = [&](float p, float wp, float hp) {
+      return fmaf(f.sg, f.c.pk, p) -
+             0.5f * (fabsf(fmaf(f.sg, f.wk, wp)) + fabsf(fmaf(f.sg, f.hk, hp)));
+    };
+    AreaProbes P;
+    P.k = f.c.k;
+    P.face = f.c.face;
+    P.one_face = fminf(fminf(least(f.c.pa, f.wa, f.ha), least(-f.c.pa, -f.wa, -f.ha)),
+                       fminf(least(f.c.pb, f.wb, f.hb), least(-f.c.pb, -f.wb, -f.hb))) > 0.0f;
+    P.pk = f.c.pk;
+    P.pa = f.c.pa;
+    P.pb = f.c.pb;
+    P.jk = swap ? f.hk : f.wk;
+    P.ja = swap ? f.ha : f.wa;
+    P.jb = swap ? f.hb : f.wb;
+    P.nk = swap ? f.wk : f.hk;
+    P.na = swap ? f.wa : f.ha;
+    P.nb = swap ? f.wb : f.hb;
+    P.n = nmaj * nmin;
+    P.minor = nmin;
+    P.inv = fdiv(1.0f, fmaj);
+    const float in = P.inv * (nmin == 1 ? 1.0f : 0.5f);  // weight of a probe
+    // A probe is one wait for its scattered texels, and the waves of the photon ring (0.4% of a
+    // 1600 x 900 frame's take 32 probes on two levels) end last, on an idle chip: 13 of 44 us went
+    // to footprints of more than 4 major probes.  So two probes' texels are in flight at a time.
+    // Level 0 alone, for every lane here (97% of the waves under a map of 512 x 512 texels): its
+    // record is the wave's.
+    if (__ballot(lam > 0.0f) == 0ull) {
+      for (int t = 0; t < P.n; t += 2) {
+        const AreaAt p0 = area_at(P, t), p1 = area_at(P, min(t + 1, P.n - 1));
+        const AreaQuad<BANDS> q0 = area_read<BANDS>(M, l0, p0.face, p0.u, p0.v);
+        const AreaQuad<BANDS> q1 = area_read<BANDS>(M, l0, p1.face, p1.u, p1.v);
+        area_add<BANDS>(q0, in, l0.nL, p0.face, sum);
+        if (t + 1 < P.n) area_add<BANDS>(q1, in, l0.nL, p1.face, sum);
       }
-      const Tx v0 = area_fetch<BANDS>(M, L0, face, pu, pv);
-      Tx v = v0;
-      if (two) v = lerp_texel(fr, v0, area_fetch<BANDS>(M, L1, face, pu, pv));
-      sa += v.x;
-      sb += v.y;
-      if constexpr (BANDS) sc += v.z;
+    } else {
+      const int La = (int)lam, Lb = min(La + 1, M.levels - 1);
+      const float fr = lam - (float)La;
+      const bool two = fr > 0.0f && Lb != La;  // the second level has weight
+      const float in1 = two ? fr * in : 0.0f, in0 = in - in1;
+      const AreaLevel la_ = area_level(M, La), lb_ = area_level(M, Lb);
+      // In the kernels with band code a second probe has no registers: it spilled 11 of them and
+      // cost the 1080p any-colour frame 109.6 -> 111.3 us; without it the odd-sized nebula frame
+      // takes 44.8 us for 39.8.
+      constexpr int kProbes = PAIR ? 2 : 1;
+      for (int t = 0; t < P.n; t += kProbes) {
+        AreaQuad<BANDS> q0[kProbes], q1[kProbes];
+        int face[kProbes];
+#pragma unroll
+        for (int i = 0; i < kProbes; ++i) {
+          const AreaAt p = area_at(P, min(t + i, P.n - 1));
+          face[i] = p.face;
+          q0[i] = area_read<BANDS>(M, la_, p.face, p.u, p.v);
+          q1[i] = area_read<BANDS>(M, lb_, p.face, p.u, p.v);
+        }
+#pragma unroll
+        for (int i = 0; i < kProbes; ++i) {
+          if (i > 0 && t + i >= P.n) break;
+          area_add<BANDS>(q0[i], in0, la_.nL, face[i], sum);
+          if (two) area_add<BANDS>(q1[i], in1, lb_.nL, face[i], sum);
+        }
+      }
     }
   }
-  const float in = inv * (nmin == 1 ? 1.0f : 0.5f);
-  A = sa * in;
-  B = sb * in;
-  Cc = sc * in;
+  A = sum.x;
+  B = sum.y;
+  Cc = sum.z;
 }
 
 // C_b(r, g, D) from the colour-shift table (Section 3.4.2; cshift.hip): log2 values read
 // trilinearly, linearly in r and g and, between the two D nodes around D, linearly in 1 / D;
 // r, g and log2 D clamped to the node range
-__device__ __forceinline__ float3 cshift_lookup(const float4* __restrict__ tab, float r, float g,
-                                                float D) {
-  constexpr float top = (float)(kCshiftN - 1), step = 6.0f / (float)(kCshiftN - 1);
-  const float x = clampf(r * top, 0.0f, top), y = clampf(g * top, 0.0f, top);
-  const int i0 = min((int)x, kCshiftN - 2), j0 = min((int)y, kCshiftN - 2);
-  const float fx = x - (float)i0, fy = y - (float)j0;
+__device__ __forceinline__ float3 lerp3(float f, float3 a, float3 b) {
+  return make_float3(fmaf(f, b.x - a.x, a.x), fmaf(f, b.y - a.y, a.y), fmaf(f, b.z - a.z, a.z));
+}
+struct ShiftPlane {  // the D nodes around a pixel's D, the same for its stars and its sky
+  int k0;
+  float fz;
+};
+__device__ __forceinline__ ShiftPlane cshift_plane(float D) {
+  constexpr float step = 6.0f / (float)(kCshiftN - 1);
   const float Dc = clampf(D, 0.125f, 8.0f);
   const int k0 = min((int)((__log2f(Dc) + 3.0f) * (1.0f / step)), kCshiftN - 2);
-  const float inv0 = exp2f(3.0f - (float)k0 * step), inv1 = exp2f(3.0f - (float)(k0 + 1) * step);
-  const float fz = clampf(fdiv(fdiv(1.0f, Dc) - inv0, inv1 - inv0), 0.0f, 1.0f);
-  const float4* p = tab + ((uint32_t)i0 * kCshiftN + (uint32_t)j0) * kCshiftN + (uint32_t)k0;
-  constexpr uint32_t si = kCshiftN * kCshiftN, sj = kCshiftN;
-  const float4 c000 = p[0], c001 = p[1], c010 = p[sj], c011 = p[sj + 1];
-  const float4 c100 = p[si], c101 = p[si + 1], c110 = p[si + sj], c111 = p[si + sj + 1];
-  const float4 e = lerp_texel(fx, lerp_texel(fy, lerp_texel(fz, c000, c001),
-                                             lerp_texel(fz, c010, c011)),
-                              lerp_texel(fy, lerp_texel(fz, c100, c101),
-                                         lerp_texel(fz, c110, c111)));
-  return make_float3(exp2f(e.x), exp2f(e.y), exp2f(e.z));
+  // hardware 2^x: the arguments, and the table's log2 C >= -100, keep the results normal
+  const float inv0 = __builtin_amdgcn_exp2f(3.0f - (float)k0 * step);
+  const float inv1 = __builtin_amdgcn_exp2f(3.0f - (float)(k0 + 1) * step);
+  return ShiftPlane{k0, clampf(fdiv(fdiv(1.0f, Dc) - inv0, inv1 - inv0), 0.0f, 1.0f)};
+}
+
+__device__ __forceinline__ float3 cshift_lookup(const float4* __restrict__ tab, float r, float g,
+                                                const ShiftPlane& D) {
+  constexpr float top = (float)(kCshiftN - 1);
+  const float x = clampf(r * top, 0.0f, top), y = clampf(g * top, 0.0f, top);
+  const int i0 = min((int)x, kCshiftN - 2), j0 = min((int)y, kCshiftN - 2);
+  const float fx = x - (float)i0, fy = y - (float)j0, fz = D.fz;
+  const int k0 = D.k0;
+  const float4* p = tab + ((uint32_t)k0 * kCshiftN + (uint32_t)i0) * kCshiftN + (uint32_t)j0;
+  constexpr uint32_t sk = kCshiftN * kCshiftN, si = kCshiftN;
+  const float4 c000 = p[0], c010 = p[1], c100 = p[si], c110 = p[si + 1];
+  const float4 c001 = p[sk], c011 = p[sk + 1], c101 = p[sk + si], c111 = p[sk + si + 1];
+  auto between = [&](const float4& a, const float4& b) {  // in D
+    return lerp3(fz, make_float3(a.x, a.y, a.z), make_float3(b.x, b.y, b.z));
+  };
+  const float3 e = lerp3(fx, lerp3(fy, between(c000, c001), between(c010, c011)),
+                         lerp3(fy, between(c100, c101), between(c110, c111)));
+  return make_float3(__builtin_amdgcn_exp2f(e.x), __builtin_amdgcn_exp2f(e.y),
+                     __builtin_amdgcn_exp2f(e.z));
 }
 
 // The view record of a kernel that takes it as its first argument, to be read again from the
@@ -856,28 +988,14 @@ __device__ __forceinline__ void render_pixel(const ViewDev& v0, const TablesDev&
   float dw0 = quad_diff<1>(dp0), dw1 = quad_diff<1>(dp1), dw2 = quad_diff<1>(dp2);
   float dh0 = quad_diff<2>(dp0), dh1 = quad_diff<2>(dp1), dh2 = quad_diff<2>(dp2);
   if (cap) bits |= BH_STAR_ZEROED_BIT;
+  ShiftPlane sp{0, 0.0f};
+  if constexpr (AREA >= 2) sp = cshift_plane(dcam);
   if (w.has_stars && !cap) {
     const StarsDev& S = w.stars;
-    float a0 = fabsf(dp0), a1 = fabsf(dp1), a2 = fabsf(dp2);
-    int k = 0;
-    float m = a0;
-    if (a1 > m) { k = 1; m = a1; }
-    if (a2 > m) { k = 2; m = a2; }
-    float dk = k == 0 ? dp0 : (k == 1 ? dp1 : dp2);
-    float da = k == 0 ? dp1 : (k == 1 ? dp2 : dp0);
-    float db = k == 0 ? dp2 : (k == 1 ? dp0 : dp1);
-    float wk = k == 0 ? dw0 : (k == 1 ? dw1 : dw2);
-    float wa = k == 0 ? dw1 : (k == 1 ? dw2 : dw0);
-    float wb = k == 0 ? dw2 : (k == 1 ? dw0 : dw1);
-    float hk = k == 0 ? dh0 : (k == 1 ? dh1 : dh2);
-    float ha = k == 0 ? dh1 : (k == 1 ? dh2 : dh0);
-    float hb = k == 0 ? dh2 : (k == 1 ? dh0 : dh1);
-    int face = 2 * k + (dk < 0.0f);
-    float sgk = dk < 0.0f ? -1.0f : 1.0f;
-    float im = fdiv(1.0f, m);
-    float U = da * im, V = db * im;
-    float J00 = (wa - U * sgk * wk) * im, J01 = (ha - U * sgk * hk) * im;
-    float J10 = (wb - V * sgk * wk) * im, J11 = (hb - V * sgk * hk) * im;
+    const FaceFootprint ff = face_footprint(dp0, dp1, dp2, dw0, dw1, dw2, dh0, dh1, dh2);
+    const float U = ff.U, V = ff.V;
+    const float J00 = ff.J00, J01 = ff.J01, J10 = ff.J10, J11 = ff.J11;
+    const int face = ff.c.face;
     float hu = fabsf(J00) + fabsf(J01), hv = fabsf(J10) + fabsf(J11);
     float E0 = fmaxf(hu, hv) * (float)S.n0;
     // smallest level with E0 / 2^L <= 8: from the exponent and mantissa of E0 / 8
@@ -940,9 +1058,9 @@ __device__ __forceinline__ void render_pixel(const ViewDev& v0, const TablesDev&
       if constexpr (AREA >= 2) {
         if (bands) {
           if (S.fp16)
-            gather<kTexBand16, COUNT>(S.tex, F, cnt, req, A, B, Cb);
+            gather<kTexBand16, COUNT, false>(S.tex, F, cnt, req, A, B, Cb);
           else
-            gather<kTexBand32, COUNT>(S.tex, F, cnt, req, A, B, Cb);
+            gather<kTexBand32, COUNT, false>(S.tex, F, cnt, req, A, B, Cb);
         }
       }
       if (!bands) {
@@ -973,7 +1091,7 @@ __device__ __forceinline__ void render_pixel(const ViewDev& v0, const TablesDev&
       const float Ssum = A + B + Cb;
       if (Ssum > 0.0f && omp2 > 0.0f) {
         const float iS = fdiv(1.0f, Ssum);
-        const float3 C = cshift_lookup(S.ctab, A * iS, B * iS, dcam);
+        const float3 C = cshift_lookup(S.ctab, A * iS, B * iS, sp);
         const float sc = trans * w.k_star * fsqrt(om2) * __builtin_amdgcn_rsqf(omp2) * Ssum;
         cr += sc * C.x;
         cg += sc * C.y;
@@ -991,24 +1109,27 @@ __device__ __forceinline__ void render_pixel(const ViewDev& v0, const TablesDev&
     }
   }
 
+
   // ---- area sources: the footprint's mean radiance, one Doppler shift per pixel as for
-  // stars, no lensing amplification (Section 3.4.1)
+  // stars, no lensing amplification (Section 3.4.1).  The face footprint is formed again: kept
+  // across the star gather it would spill.
   if ((AREA == 1 || AREA == 2) && w.area.tex && !cap && trans > 0.0f) {
+    const FaceFootprint ff = face_footprint(dp0, dp1, dp2, dw0, dw1, dw2, dh0, dh1, dh2);
     float A, B, Cc;
     if (AREA == 2 && w.area.bands) {
       // light of any colour: band sum S and chromaticity (r, g), shifted by C(r, g, D_cam)
-      area_filter<true>(w.area, dp0, dp1, dp2, dw0, dw1, dw2, dh0, dh1, dh2, A, B, Cc);
+      area_filter<true, false>(w.area, ff, A, B, Cc);
       const float S = A + B + Cc;
       if (S > 0.0f) {
         const float iS = fdiv(1.0f, S);
-        const float3 C = cshift_lookup(w.area.ctab, A * iS, B * iS, dcam);
+        const float3 C = cshift_lookup(w.area.ctab, A * iS, B * iS, sp);
         const float sc = trans * w.area.k_area * S;
         cr += sc * C.x;
         cg += sc * C.y;
         cb += sc * C.z;
       }
     } else {
-      area_filter<false>(w.area, dp0, dp1, dp2, dw0, dw1, dw2, dh0, dh1, dh2, A, B, Cc);
+      area_filter<false, AREA == 1>(w.area, ff, A, B, Cc);
       if (A > 0.0f) {
         const float Tpix = fdiv(B, A);
         const float4 Lr = band_lookup(L, dcam * Tpix), Ln = band_lookup(L, Tpix);
@@ -1019,7 +1140,6 @@ __device__ __forceinline__ void render_pixel(const ViewDev& v0, const TablesDev&
       }
     }
   }
-
   }
 
   if (COUNT) {
@@ -1090,11 +1210,12 @@ static inline int xcd_grid(int tiles_x, int tiles_y) {
 }
 
 // Resident waves per SIMD the one-launch and per-tile kernels are held to (the register
-// budget the compiler keeps to): 8, and 6 for the area-source variants, whose probe loop
-// spilled 20 vector registers to memory at 8 waves and ran 17% faster at 6 without spills,
-// 5 when they also read band colours.  Band star maps without area maps fit 8 (64 VGPRs).
+// budget the compiler keeps to): 8, and 5 for the area-source variants, whose probe loop
+// spilled 20 vector registers at 8 waves and 9 at 6 (nebula frame 1599 x 899: 43.5 us at 6 waves,
+// 42.4 at 5, one probe in flight; at 7 waves 48.5, and the any-colour frame 139 us for 109).  Band
+// star maps without area maps fit 8 (64 VGPRs).
 template <int FEAT>
-constexpr int kMinWaves = (FEAT & kFeatArea) ? ((FEAT & kFeatBands) ? 5 : 6) : 8;
+constexpr int kMinWaves = (FEAT & kFeatArea) ? 5 : 8;
 
 // the area and band code a feature set needs (render_pixel's AREA): 0 none, 1 (I, I T) area
 // maps, 2 area maps of either format and band star maps (run-time branches on the maps'
