@@ -106,6 +106,8 @@ struct CshiftRule {
 // kFeatBands: band colours received through the colour-shift table, from an area map (then
 // with kFeatArea) or a star map.
 constexpr int kFeatParticles = 1, kFeatArea = 2, kFeatBands = 4;
+// resident waves per SIMD of the persistent batch kernel (k_render_batch)
+constexpr int batch_waves(int feat) { return (feat & kFeatArea) ? 5 : 7; }
 
 // ---- per-view constant block (host computes it in FP64 from bh_view) -----------------
 // The camera axes and the velocity direction are passed split into their parts transverse

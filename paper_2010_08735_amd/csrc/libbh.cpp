@@ -1400,11 +1400,11 @@ extern "C" bh_status bh_set_batch_form(bh_ctx* c, int32_t persistent) {
 }
 
 // Workgroups (of 4 waves, each claiming tiles on its own) of a persistent batched launch:
-// as many as fit at the kernel's 7 resident waves per SIMD, 4 SIMDs per CU (k_render_batch);
+// as many as fit at the kernel's resident waves per SIMD, 4 SIMDs per CU (k_render_batch);
 // fewer when the launch has fewer tiles than waves.
-static int batch_grid(const bh_ctx* c, int cfg, int64_t ntiles) {
-  (void)cfg;
-  return (int)std::max<int64_t>(1, std::min<int64_t>((ntiles + 3) / 4, (int64_t)c->cus * 7));
+static int batch_grid(const bh_ctx* c, int feat, int64_t ntiles) {
+  return (int)std::max<int64_t>(1, std::min<int64_t>((ntiles + 3) / 4,
+                                                     (int64_t)c->cus * batch_waves(feat)));
 }
 
 // Upload view blocks and tile runs through a pinned staging buffer and enqueue one batched
@@ -1434,10 +1434,10 @@ static bh_status enqueue_batch(bh_ctx* c, int cfg, int pers, const TablesDev& T,
     HIPCHK(hipEventRecord(copied, cs));
     HIPCHK(hipStreamWaitEvent(s, copied, 0));
   }
-  int grid = batch_grid(c, cfg, ntiles);
   int nruns = (int)runs.size();
   int feat = 0;  // the union of the views' features selects the kernel
   for (const ViewDev& vd : vds) feat |= view_features(vd);
+  int grid = batch_grid(c, feat, ntiles);
   LutDev L = lut_dev(c);
   if (!use_graph) {
     HIPCHK(launch_render_batch(cfg, pers, feat, dviews, druns, nruns, ntiles, counter, T, L,
@@ -1591,7 +1591,7 @@ extern "C" bh_status bh_render_batch_noalloc(bh_ctx* c, const bh_tables* t, cons
   int feat = 0;
   for (int i = 0; i < n; ++i) feat |= view_features(hv[i]);
   HIPCHK(launch_render_batch(cfg, c->persistent, feat, dviews, druns, n, (int)ntiles, dcounter,
-                             tables_dev(t), lut_dev(c), batch_grid(c, cfg, ntiles), s));
+                             tables_dev(t), lut_dev(c), batch_grid(c, feat, ntiles), s));
   return BH_OK;
 }
 

@@ -1286,15 +1286,23 @@ __device__ __forceinline__ void render_flat_tile(const ViewDev* __restrict__ vie
 // indices from an atomic counter and renders every 8x8 block of the tiles a claim covers,
 // so no claim waits on a barrier and the workgroup shape (4 waves) is the same for every
 // tile configuration.  Claim j < nbig covers claim_tiles consecutive flat tiles (about 16
-// blocks); the last `tail` tiles (4 per wave) go one per claim, so the launch does not end
-// waiting on a few long claims.  A wave leaves at its first claim past the last tile; the
+// blocks); the last `tail` tiles (one for every fourth wave) go one per claim, so the launch does
+// not end waiting on a few long claims.  The counter is what bounds this form: one address takes an
+// atomic every 17 ns, so the first claim is the wave's own number and takes none, and a longer
+// tail costs more than it evens out (24 uneven views: 4 single claims per wave and a claimed
+// start 1210 us, a numbered start and 1 per wave 905, every fourth wave 865; four 1080p frames
+// 605, 317, 261; claims of 32 blocks 919 and 395).  A wave leaves at its first claim past the last tile; the
 // counter only grows, so every wave reaches that exit.  Held to 7 resident waves per SIMD:
 // the loop over tiles keeps ~14 more vector registers live than one tile does, so at 8
-// waves it would spill; the host sizes the grid to 7 waves per SIMD.
+// waves it would spill; with area code to 5, as the other launches are (at 7 it spilled 46 and
+// four 1599 x 899 nebula views took 1003 us, 727 at 5).  The host sizes the grid to the same.
 constexpr int kBatchThreads = 256;
 
+template <int FEAT>
+constexpr int kBatchWaves = batch_waves(FEAT);
+
 template <int TW, int TH, int PPT, int FEAT>
-__global__ void __launch_bounds__(kBatchThreads, 7)
+__global__ void __launch_bounds__(kBatchThreads, kBatchWaves<FEAT>)
     k_render_batch(const ViewDev* __restrict__ views, const TileRun* __restrict__ runs,
                    int nruns, int ntiles, int* __restrict__ counter, TablesDev T, LutDev L) {
   using C = TileCfg<TW, TH, 1>;
@@ -1303,13 +1311,14 @@ __global__ void __launch_bounds__(kBatchThreads, 7)
   const int lane = threadIdx.x & 63;
   const int q = lane >> 2;
   const int ox = 2 * (q & 3) + (lane & 1), oy = 2 * (q >> 2) + ((lane >> 1) & 1);
-  const int tail = min(ntiles, 4 * (int)(gridDim.x * (kBatchThreads / 64)));
+  const int waves = (int)(gridDim.x * (kBatchThreads / 64));
+  const int tail = min(ntiles, waves / 4);
   const int nbig = (ntiles - tail) / claim_tiles;          // tiles [0, claim_tiles nbig)
   const int first_single = claim_tiles * nbig;
+  // the first claim is the wave's own number, the later ones follow from the counter
+  int j = (int)(blockIdx.x * (kBatchThreads / 64) + threadIdx.x / 64);
+  j = __builtin_amdgcn_readfirstlane(j);
   for (;;) {
-    int j = 0;
-    if (lane == 0) j = atomicAdd(counter, 1);
-    j = __builtin_amdgcn_readfirstlane(j);                 // lane 0's claim, the wave's
     int it0, it1;
     if (j < nbig) {
       it0 = claim_tiles * j;
@@ -1333,6 +1342,8 @@ __global__ void __launch_bounds__(kBatchThreads, 7)
             v, T, L, bx + ox, by + oy, nullptr);
       }
     }
+    if (lane == 0) j = waves + atomicAdd(counter, 1);
+    j = __builtin_amdgcn_readfirstlane(j);                 // lane 0's claim, the wave's
   }
 }
 
