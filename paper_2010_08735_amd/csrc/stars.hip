@@ -228,9 +228,10 @@ __device__ __forceinline__ float brightest(const Master<BANDS>& m) {
 }
 
 // Quotients by one divisor d > 0: a reciprocal by Newton's iteration, then each quotient
-// corrected once by its own remainder (within an ulp of FP64, exact where the quotient is; it is
-// rounded to FP32 next).  Outside the range where nothing can overflow or vanish the plain
-// division is used.
+// corrected once by its own remainder, which rounds as the division itself does (Markstein; the
+// stored texels are the division's bit for bit).  Divisors that could overflow or vanish on the
+// way, and an infinite numerator (a star of infinite temperature), which has no remainder, take
+// the plain division.
 struct Divider {
   double d, r;
   bool plain;
@@ -241,7 +242,7 @@ struct Divider {
     r = fma(fma(-x, r, 1.0), r, r);
   }
   __device__ __forceinline__ float operator()(double n) const {
-    if (plain) return (float)(n / d);
+    if (plain || isinf(n)) return (float)(n / d);
     const double q = n * r;
     return (float)fma(fma(-d, q, n), r, q);
   }

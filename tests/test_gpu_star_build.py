@@ -174,3 +174,45 @@ def test_maps_built_in_released_blocks(budget):
     assert not bad
     assert bh.bh_bytes_in_use(ctx) == base
     bh.bh_destroy(ctx)
+
+
+@pytest.mark.parametrize("fmt", [bh.BH_TEXEL_FP16, bh.BH_TEXEL_FP32])
+def test_infinite_temperatures_stay_infinite(gpu_ctx, fmt):
+    """A texel's temperature is the weighted mean of its stars', in every level: infinite when one
+    of them is (a NaN would reach the image), and the others' texels are not touched."""
+    import torch
+    n0 = 4
+    d = np.array([[1, 0.1, 0.1], [1, 0.1, 0.1], [1, -0.9, -0.9], [-1, 0.2, 0.3]], np.float32)
+    inten = np.array([2.0, 1.0, 1.0, 3.0], np.float32)
+    temp = np.array([np.inf, 5000.0, 4000.0, 6000.0], np.float32)
+    dd, ii, tt = (torch.from_numpy(x).cuda() for x in (d, inten, temp))
+    h = bh.bh_build_stars(gpu_ctx, dd.data_ptr(), ii.data_ptr(), tt.data_ptr(), len(d), n0, fmt,
+                          bh.current_stream())
+    for level in range(3):
+        nl = n0 >> level
+        got = np.empty((6, nl, nl, 4), np.float32)
+        bh.bh_stars_download(h, level, got.ctypes.data)
+        assert not np.isnan(got).any(), level
+        assert np.isinf(got[0, ..., 1]).sum() == 1 and np.isfinite(got[1:]).all(), level
+        assert got[1, ..., 1].max() == pytest.approx(6000.0, rel=2.0 ** -11)
+        if level < 2:  # the finite star's own texel
+            assert got[0, 0, 0, 1] == pytest.approx(4000.0, rel=2.0 ** -11)
+    bh.bh_release_stars(h)
+
+
+@pytest.mark.parametrize("n0,n", [(64, 3000), (64, 60000)])
+def test_level0_quotients_are_the_rounded_division(gpu_ctx, n0, n):
+    """FP32 texels are FP64 sums in star order and one FP64 division each: the same bits as numpy's
+    (every product of two FP32 values is exact in FP64)."""
+    import torch
+    d, inten, temp = _field(n, n0, "clustered", 9)
+    dd, ii, tt = (torch.from_numpy(x).cuda() for x in (d, inten, temp))
+    h = bh.bh_build_stars(gpu_ctx, dd.data_ptr(), ii.data_ptr(), tt.data_ptr(), n, n0,
+                          bh.BH_TEXEL_FP32, bh.current_stream())
+    w = inten.astype(np.float64)
+    ok = (w > 0) & (np.abs(d).max(1) > 0)
+    lev = _levels(d[ok], np.stack([w, w * temp], 1)[ok], w[ok], n0)
+    lit = lev[:, 0] > 0
+    want = np.concatenate([lev[lit, :1], lev[lit, 1:] / lev[lit, :1]], 1).astype(np.float32)
+    assert np.array_equal(_level0(h, n0)[lit], want)
+    bh.bh_release_stars(h)
