@@ -34,3 +34,20 @@ def test_tables_at_the_edges_of_their_split(gpu_ctx, orc, d_n, u_ne, u_nphi, pre
         err = np.abs(got - want) / np.maximum(1.0, np.abs(want))
         assert err.max() < tol, (name, float(err.max()),
                                  [int(v) for v in np.unravel_index(err.argmax(), err.shape)])
+
+
+def test_every_row_is_written_at_small_steps(gpu_ctx, orc):
+    """Steps below 5e-6 take the longest columns past 4e6 steps: their last rows were left as the
+    memory was.  Tolerance: the default step's 1e-6, and 14.7 rad at the FP32 step's rounding."""
+    ref = orc.Tables(64, 8, 8, time=True)
+    t = bh.bh_precompute_tables(gpu_ctx, 64, 8, 8, B, 0.05, 3e-6)
+    D, Dt = np.full((2, 64, 64), np.nan, np.float32)
+    U, Ut = np.full((2, 8, 8), np.nan, np.float32)
+    bh.bh_tables_download(t, D.ctypes.data, U.ctypes.data)
+    bh.bh_tables_download_time(t, Dt.ctypes.data, Ut.ctypes.data)
+    bh.bh_release_tables(t)
+    for name, got, want in (("D", D, ref.D), ("Dt", Dt, ref.Dt), ("U", U, ref.U),
+                            ("Ut", Ut, ref.Ut)):
+        want = np.asarray(want).reshape(got.shape)
+        err = np.abs(got - want) / np.maximum(1.0, np.abs(want))
+        assert err.max() < 1e-6 + 14.7 * 2.0 ** -24, (name, float(err.max()))
