@@ -116,9 +116,10 @@ __device__ __forceinline__ bool uniform(bool c) {
 }
 
 // Wave 0: up to kChunk steps of one precision into st (st[0] = the state they start from).
-// Steps go in blocks of kBlock, looked at once: u rises until w changes its sign, so a block
-// that ends inside its precision's range and before the column's end was inside all along; one
-// that does not is taken back and stepped singly.  (Tests and branches after every step took
+// Steps go in blocks of kBlock, looked at once: u rises until w changes its sign, so a block in
+// which w kept it and that ends inside its precision's range and before the column's end was
+// inside all along; one that does not is taken back and stepped singly.  (Columns of U go on past
+// the apsis, which may lie in the FP64 band with both ends of the block below it.)  (Tests and branches after every step took
 // more than half of the step: 2.05 against 0.96 ms for the pass above.)
 constexpr int kBlock = 8;
 
@@ -195,7 +196,8 @@ __device__ __forceinline__ ChunkInfo integrate_chunk(Integrator& I, double h, in
         put();
       }
       // a block may not pass the whole band either (a narrow one, wide steps)
-      if (uniform(near_end() || near_band() || (u0 <= near_lo) != (I.uf <= near_lo))) {
+      const bool turned = END == kPhi && (w0 > 0.0f) != (I.wf > 0.0f);
+      if (uniform(near_end() || near_band() || turned || (u0 <= near_lo) != (I.uf <= near_lo))) {
         I.uf = u0;
         I.wf = w0;
         I.cu = cu0;

@@ -82,10 +82,35 @@ static bool step_limit() {
   return ok;
 }
 
+// Every step is taken in the precision that its start asks for, in columns of U too, whose u falls
+// again past the apsis: apsides from just below the band's edge to well inside it, where the FP64
+// steps are a few around the apsis.
+static bool band_rule() {
+  bool ok = true;
+  long in_band = 0;
+  for (double step : {5e-4, 2e-3, 1e-2, 0.05})
+    for (double band : {1e-3, 0.05, 0.3})
+      for (double above : {-1e-6, 3e-8, 3e-7, 3e-6, 1e-5, 1e-4, 3e-4}) {
+        if (above >= band) continue;
+        const double ua = 2.0 / 3.0 - band + above, e2 = ua * ua * (1.0 - ua);
+        const double e = std::sqrt(e2), h = step / (1.0 + e);
+        const double phi = 3.0 * (1.0 + e2) / (1.0 + 6.0 * e2 * e);
+        const Run r = run<kPhi>(e2, step, kTabBand, band, (int)std::ceil(phi / h));
+        if (r.wrong) {
+          std::printf("step %g band %g apsis %g above its edge: %ld steps in the other precision\n",
+                      step, band, above, r.wrong);
+          ok = false;
+        }
+        in_band += above > 0;
+      }
+  return ok && in_band > 0;
+}
+
 int main(int argc, char** argv) {
   const char* name = argc > 1 ? argv[1] : "";
   bool ok = false;
   if (!std::strcmp(name, "step_limit")) ok = step_limit();
+  if (!std::strcmp(name, "band_rule")) ok = band_rule();
   std::printf("%s %s\n", name, ok ? "ok" : "failed");
   return ok ? 0 : 1;
 }

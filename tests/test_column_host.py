@@ -21,7 +21,7 @@ def exe(request, tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("scenario", ["step_limit"])
+@pytest.mark.parametrize("scenario", ["step_limit", "band_rule"])
 def test_column(exe, scenario):
     r = subprocess.run([exe, scenario], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0 and scenario + " ok" in r.stdout, r.stdout + r.stderr
