@@ -22,6 +22,7 @@
 
 #include "bh.h"
 #include "bh_dev.h"
+#include "bh_pool.h"
 #include "bh_sched.h"
 
 namespace bh {
@@ -188,15 +189,24 @@ struct Staging {
 
 struct ServeBackend;
 
+// the device as the block pool uses it, with the context's device current
+struct HipBlocks {
+  bool alloc(void** p, size_t bytes) {
+    const bool ok = hipMalloc(p, bytes) == hipSuccess;
+    if (!ok) (void)hipGetLastError();
+    return ok;
+  }
+  void free(void* p) { (void)hipFree(p); }
+  bool wait() { return hipDeviceSynchronize() == hipSuccess; }
+};
+
 struct bh_ctx {
   int device = 0;
   uint64_t budget = 0;
   std::atomic<uint64_t> used{0};
-  // blocks of released handles and finished builds, kept for the next ones (dev_recycle)
-  std::mutex kept_mu;
-  std::multimap<size_t, void*> kept;  // by size
-  size_t kept_bytes = 0;
-  std::set<void*> unrounded;          // blocks smaller than their size step, never kept
+  // blocks of released handles and finished builds, kept for the next ones (bh_pool.h); none in a
+  // context with a budget, which counts what is allocated
+  BlockPool<HipBlocks> pool;
   int cus = 256;
   std::mutex mu;  // resources, tile config, batch staging
   std::map<std::string, bh_tables*> tables;
@@ -243,30 +253,6 @@ static double now_s() {
       .count();
 }
 
-// Blocks kept for reuse.  Fresh device memory is cleared before a process gets it, and a build
-// that allocates and frees a 268 MB map waits for that: a new 6 x 2048^2 star map took 4.5 ms
-// of which its kernels are 0.35.  A context without a budget therefore keeps idle blocks of at
-// least kKeepLeast, at most kKeepMost in all, and hands them out again by size; they are freed
-// when an allocation fails and with the context.  Sizes are rounded up to eight steps an octave so
-// that nearly equal builds share blocks.  With a budget, which counts what is allocated, nothing is
-// kept or rounded.
-constexpr size_t kKeepLeast = (size_t)1 << 20, kKeepMost = (size_t)1 << 30;
-
-static size_t block_size(const bh_ctx* c, size_t bytes) {
-  if (c->budget || bytes < kKeepLeast) return bytes;
-  size_t step = kKeepLeast >> 3;
-  while ((step << 4) <= bytes) step <<= 1;
-  return (bytes + step - 1) / step * step;
-}
-
-// frees every kept block (with the context's device current)
-static void drop_kept(bh_ctx* c) {
-  std::lock_guard<std::mutex> g(c->kept_mu);
-  for (auto& kv : c->kept) (void)hipFree(kv.second);
-  c->kept.clear();
-  c->kept_bytes = 0;
-}
-
 // Reserves the bytes in the budget first (one atomic add, so concurrent callers cannot both
 // pass the check), then allocates; both steps are undone on failure.
 static bh_status dev_alloc(bh_ctx* c, size_t bytes, void** p) {
@@ -276,42 +262,16 @@ static bh_status dev_alloc(bh_ctx* c, size_t bytes, void** p) {
     return fail(BH_ENOMEM, "HBM budget exceeded: " + std::to_string(before + bytes) + " > " +
                                std::to_string(c->budget));
   }
-  const size_t block = block_size(c, bytes);
-  if (block >= kKeepLeast) {
-    std::lock_guard<std::mutex> g(c->kept_mu);
-    auto it = c->kept.find(block);
-    if (it != c->kept.end()) {
-      *p = it->second;
-      c->kept.erase(it);
-      c->kept_bytes -= block;
-      return BH_OK;
-    }
-  }
-  hipError_t e = hipMalloc(p, block);
-  if (e != hipSuccess) {
-    (void)hipGetLastError();
-    drop_kept(c);
-    e = hipMalloc(p, block);
-    if (e != hipSuccess && block != bytes) {
-      (void)hipGetLastError();
-      e = hipMalloc(p, bytes);
-      if (e == hipSuccess) {
-        std::lock_guard<std::mutex> g(c->kept_mu);
-        c->unrounded.insert(*p);
-      }
-    }
-  }
-  if (e != hipSuccess) {
+  if (!c->pool.alloc(p, bytes)) {
     c->used -= bytes;
-    *p = nullptr;
-    return fail(BH_ENOMEM, std::string("hipMalloc: ") + hipGetErrorString(e));
+    return fail(BH_ENOMEM, std::string("hipMalloc: ") + hipGetErrorString(hipErrorOutOfMemory));
   }
   return BH_OK;
 }
 
 static void dev_free(bh_ctx* c, void* p, size_t bytes) {
   if (!p) return;
-  (void)hipFree(p);
+  c->pool.free(p);
   c->used -= bytes;
 }
 
@@ -319,18 +279,21 @@ static void dev_free(bh_ctx* c, void* p, size_t bytes) {
 // on any stream: it may be handed out again at once.
 static void dev_recycle(bh_ctx* c, void* p, size_t bytes) {
   if (!p) return;
-  const size_t block = block_size(c, bytes);
-  if (!c->budget && block >= kKeepLeast) {
-    std::lock_guard<std::mutex> g(c->kept_mu);
-    if (!c->unrounded.erase(p) && c->kept_bytes + block <= kKeepMost) {
-      c->kept.emplace(block, p);
-      c->kept_bytes += block;
-      c->used -= bytes;
-      return;
-    }
-  }
-  dev_free(c, p, bytes);
+  c->pool.recycle(p, bytes);
+  c->used -= bytes;
 }
+
+// Waits for the device, then takes back the blocks of one handle.
+struct Releasing {
+  bh_ctx* c;
+  BlockPool<HipBlocks>::Release blocks;
+  explicit Releasing(bh_ctx* ctx) : c(ctx), blocks(ctx->pool) {}
+  void operator()(void* p, size_t bytes) {
+    if (!p) return;
+    blocks(p, bytes);
+    c->used -= bytes;
+  }
+};
 
 static bh_status ensure_staging(Staging& s, size_t bytes) {
   if (s.cap >= bytes) return BH_OK;
@@ -381,6 +344,7 @@ extern "C" bh_status bh_create(int device, uint64_t budget, bh_ctx** out) {
   std::unique_ptr<bh_ctx> c(new bh_ctx);
   c->device = device;
   c->budget = budget;
+  c->pool.keeps = budget == 0;
   hipDeviceProp_t prop;
   HIPCHK(hipGetDeviceProperties(&prop, device));
   c->cus = prop.multiProcessorCount;
@@ -449,7 +413,7 @@ extern "C" void bh_destroy(bh_ctx* c) {
     handle_drop(p);
     delete p;
   }
-  drop_kept(c);
+  c->pool.drop();
   dev_free(c, c->lut, 0);
   dev_free(c, c->ctab, 0);
   dev_free(c, c->b_counter, 0);
@@ -554,7 +518,7 @@ extern "C" bh_status bh_release_tables(bh_tables* t) {
   std::lock_guard<std::mutex> g(c->mu);
   if (--t->refs > 0) return BH_OK;
   (void)hipSetDevice(c->device);
-  (void)hipDeviceSynchronize();
+  Releasing give_back(c);
   // captured batch launches that read these tables must not be replayed on a later table
   // set that happens to reuse the freed addresses
   for (auto it = c->graphs.begin(); it != c->graphs.end();) {
@@ -566,10 +530,10 @@ extern "C" bh_status bh_release_tables(bh_tables* t) {
     }
   }
   c->tables.erase(t->key);
-  dev_recycle(c, t->D, sizeof(float) * (size_t)t->p.d_n * t->p.d_n);
-  dev_recycle(c, t->U, sizeof(float) * (size_t)t->p.u_ne * t->p.u_nphi);
-  dev_recycle(c, t->Dt, sizeof(float) * (size_t)t->p.d_n * t->p.d_n);
-  dev_recycle(c, t->Ut, sizeof(float) * (size_t)t->p.u_ne * t->p.u_nphi);
+  give_back(t->D, sizeof(float) * (size_t)t->p.d_n * t->p.d_n);
+  give_back(t->U, sizeof(float) * (size_t)t->p.u_ne * t->p.u_nphi);
+  give_back(t->Dt, sizeof(float) * (size_t)t->p.d_n * t->p.d_n);
+  give_back(t->Ut, sizeof(float) * (size_t)t->p.u_ne * t->p.u_nphi);
   handle_drop(t);
   delete t;
   return BH_OK;
@@ -774,9 +738,9 @@ extern "C" bh_status bh_bloom_release(bh_bloom* b) {
   std::lock_guard<std::mutex> g(c->mu);
   if (!c->blooms.erase(b)) return fail(BH_ENOTFOUND, "unknown bloom");
   (void)hipSetDevice(c->device);
-  (void)hipDeviceSynchronize();  // launches may still use the pyramid
-  dev_recycle(c, b->P, sizeof(float4) * b->elems);
-  dev_recycle(c, b->U, sizeof(float4) * b->elems);
+  Releasing give_back(c);  // launches may still use the pyramid
+  give_back(b->P, sizeof(float4) * b->elems);
+  give_back(b->U, sizeof(float4) * b->elems);
   handle_drop(b);
   delete b;
   return BH_OK;
@@ -1005,16 +969,16 @@ extern "C" bh_status bh_release_stars(bh_stars* s) {
   std::lock_guard<std::mutex> g(c->mu);
   if (--s->refs > 0) return BH_OK;
   (void)hipSetDevice(c->device);
-  (void)hipDeviceSynchronize();
+  Releasing give_back(c);
   c->stars.erase(s->key);
   const size_t tsz = (s->fp16 ? 8 : 16) * (s->bands ? 2 : 1);
   uint64_t total = 0;
   for (int l = 0; l < s->levels; ++l) total += 6ull * (s->n0 >> l) * (s->n0 >> l);
-  dev_recycle(c, s->tex, tsz * total);
-  dev_recycle(c, s->scale, sizeof(float) * s->levels);
-  dev_recycle(c, s->level_off_dev, sizeof(uint32_t) * s->levels);
-  dev_recycle(c, s->occ, s->occ_bytes);
-  dev_recycle(c, s->occ_off_dev, sizeof(uint32_t) * s->levels);
+  give_back(s->tex, tsz * total);
+  give_back(s->scale, sizeof(float) * s->levels);
+  give_back(s->level_off_dev, sizeof(uint32_t) * s->levels);
+  give_back(s->occ, s->occ_bytes);
+  give_back(s->occ_off_dev, sizeof(uint32_t) * s->levels);
   handle_drop(s);
   delete s;
   return BH_OK;
@@ -1169,8 +1133,8 @@ extern "C" bh_status bh_release_area(bh_area* a) {
   std::lock_guard<std::mutex> g(c->mu);
   if (!c->areas.erase(a)) return fail(BH_EINVAL, "unknown area map");
   (void)hipSetDevice(c->device);
-  (void)hipDeviceSynchronize();
-  dev_recycle(c, a->tex, a->bytes);
+  Releasing give_back(c);
+  give_back(a->tex, a->bytes);
   handle_drop(a);
   delete a;
   return BH_OK;

@@ -1,0 +1,179 @@
+// The pool of idle device blocks (bh_pool.h) over a scripted device, on the CPU.  A scenario
+// prints "<name> ok".
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <mutex>
+#include <thread>
+#include <vector>
+
+#include "bh_pool.h"
+
+#define CHECK(c)                                                      \
+  do {                                                                \
+    if (!(c)) {                                                       \
+      std::printf("%s:%d: %s\n", __FILE__, __LINE__, #c);             \
+      std::exit(1);                                                   \
+    }                                                                 \
+  } while (0)
+
+// Memory of `room` bytes; `busy` blocks may still be used by queued work until a wait succeeds.
+struct Memory {
+  std::mutex mu;
+  size_t room = (size_t)8 << 30, in_use = 0;
+  std::map<void*, size_t> live;
+  std::vector<void*> freed;
+  bool refuse_wait = false;
+  int allocs = 0, waits = 0;
+};
+
+struct Fake {
+  Memory* m;
+  bool alloc(void** p, size_t bytes) {
+    std::lock_guard<std::mutex> g(m->mu);
+    if (m->in_use + bytes > m->room) return false;
+    static size_t next = 0x1000;
+    *p = (void*)next;
+    next += 0x1000;
+    m->live[*p] = bytes;
+    m->in_use += bytes;
+    ++m->allocs;
+    return true;
+  }
+  void free(void* p) {
+    std::lock_guard<std::mutex> g(m->mu);
+    auto it = m->live.find(p);
+    CHECK(it != m->live.end());
+    m->in_use -= it->second;
+    m->live.erase(it);
+    m->freed.push_back(p);
+  }
+  bool wait() {
+    std::lock_guard<std::mutex> g(m->mu);
+    ++m->waits;
+    return !m->refuse_wait;
+  }
+};
+
+using Pool = bh::BlockPool<Fake>;
+constexpr size_t MiB = (size_t)1 << 20;
+
+static void reuse() {
+  Memory m;
+  Pool pool(Fake{&m});
+  void *a, *b;
+  CHECK(pool.alloc(&a, 10 * MiB));
+  {
+    Pool::Release give_back(pool);
+    give_back(a, 10 * MiB);
+  }
+  CHECK(pool.alloc(&b, 10 * MiB - 1000) && b == a && m.allocs == 1);  // the same size step
+  CHECK(pool.alloc(&a, 10 * MiB) && a != b && m.allocs == 2);
+  pool.free(a);
+  pool.free(b);
+  pool.drop();
+  CHECK(m.live.empty());
+}
+
+// A wait that is refused does not make a block idle: it goes to the device, not to the next build.
+static void refused_wait() {
+  Memory m;
+  Pool pool(Fake{&m});
+  void *a, *b;
+  CHECK(pool.alloc(&a, 4 * MiB));
+  m.refuse_wait = true;
+  {
+    Pool::Release give_back(pool);
+    give_back(a, 4 * MiB);
+  }
+  CHECK(m.waits == 1 && m.freed.size() == 1 && m.freed[0] == a);
+  CHECK(pool.alloc(&b, 4 * MiB) && b != a);
+  m.refuse_wait = false;
+  {
+    Pool::Release give_back(pool);
+    give_back(b, 4 * MiB);
+  }
+  CHECK(m.freed.size() == 1 && pool.alloc(&a, 4 * MiB) && a == b);
+  pool.free(a);
+  CHECK(m.live.empty());
+}
+
+// A failing allocation first gives the kept blocks back, then does without the rounding.
+static void allocation_failure() {
+  Memory m;
+  m.room = 64 * MiB;
+  Pool pool(Fake{&m});
+  void *a, *b;
+  CHECK(pool.alloc(&a, 40 * MiB));
+  pool.recycle(a, 40 * MiB);
+  CHECK(m.in_use == 40 * MiB);
+  CHECK(pool.alloc(&b, 60 * MiB) && m.in_use == 60 * MiB);
+  pool.free(b);
+  const size_t odd = 63 * MiB;  // its size step is 64 MiB
+  m.room = odd;
+  CHECK(pool.alloc(&b, odd) && m.in_use == odd);
+  pool.recycle(b, odd);         // smaller than its step: not kept
+  CHECK(m.live.empty());
+  m.room = MiB;
+  CHECK(!pool.alloc(&b, 2 * MiB) && b == nullptr);
+}
+
+// With a budget nothing is rounded or kept.
+static void budget() {
+  Memory m;
+  Pool pool(Fake{&m});
+  pool.keeps = false;
+  void* a;
+  CHECK(pool.alloc(&a, 9 * MiB + 1) && m.in_use == 9 * MiB + 1);
+  pool.recycle(a, 9 * MiB + 1);
+  CHECK(m.live.empty());
+}
+
+static void threads() {
+  Memory m;
+  Pool pool(Fake{&m});
+  std::mutex mu;
+  std::map<void*, int> held;
+  std::vector<std::thread> ts;
+  for (int t = 0; t < 4; ++t)
+    ts.emplace_back([&, t] {
+      for (int r = 0; r < 2000; ++r) {
+        const size_t bytes = (size_t)(1 + (r * 7 + t * 3) % 40) * MiB;
+        void* p;
+        CHECK(pool.alloc(&p, bytes));
+        {
+          std::lock_guard<std::mutex> g(mu);
+          CHECK(held[p]++ == 0);  // one owner at a time
+        }
+        if (r % 97 == 0) pool.drop();
+        {
+          std::lock_guard<std::mutex> g(mu);
+          --held[p];
+        }
+        Pool::Release give_back(pool);
+        give_back(p, bytes);
+      }
+    });
+  for (auto& t : ts) t.join();
+  pool.drop();
+  CHECK(m.live.empty());
+}
+
+int main(int argc, char** argv) {
+  const struct {
+    const char* name;
+    void (*run)();
+  } all[] = {{"reuse", reuse},
+             {"refused_wait", refused_wait},
+             {"allocation_failure", allocation_failure},
+             {"budget", budget},
+             {"threads", threads}};
+  for (const auto& s : all)
+    if (argc > 1 && !std::strcmp(argv[1], s.name)) {
+      s.run();
+      std::printf("%s ok\n", s.name);
+      return 0;
+    }
+  return 2;
+}
