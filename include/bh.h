@@ -60,7 +60,8 @@ void bh_destroy(bh_ctx* ctx);
 const char* bh_last_error(const bh_ctx* ctx);
 /* Device bytes currently allocated by the library on this context.  A context without a budget
  * also keeps up to 1 GiB of the blocks of released handles for its next builds; they are not
- * counted, and go back to the device when an allocation fails and in bh_destroy. */
+ * counted, nor is the rounding of its blocks (up to an eighth of each of 1 MiB and more), and they
+ * go back to the device when an allocation of any context on it fails and in bh_destroy. */
 uint64_t bh_bytes_in_use(const bh_ctx* ctx);
 /* Release any handle the library returned (tables, star maps, area maps, particles, bloom
  * pyramids): the same as the release call of its type.  Tables and star maps are

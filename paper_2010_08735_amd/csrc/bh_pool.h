@@ -6,8 +6,9 @@
 // Fresh device memory is cleared before a process gets it, and a build that allocates and frees a
 // 268 MB map waits for that: a new 6 x 2048^2 star map took 4.5 ms of which its kernels are 0.35.
 // So idle blocks of at least kKeepLeast are kept, at most kKeepMost in all, and handed out again
-// by size; they are freed when an allocation fails and with the pool's owner.  Sizes are rounded
-// up to eight steps an octave so that nearly equal builds share blocks.
+// by size.  Sizes are rounded up to eight steps an octave so that nearly equal builds share
+// blocks.  Kept blocks are freed with the pool's owner, and all pools of a device (Peers) free
+// theirs when an allocation on it fails, before it is tried again.
 #pragma once
 
 #include <cstddef>
@@ -22,7 +23,29 @@ constexpr size_t kKeepLeast = (size_t)1 << 20, kKeepMost = (size_t)1 << 30;
 template <class Device>
 class BlockPool {
  public:
-  explicit BlockPool(Device d = Device()) : dev_(d) {}
+  // The pools of one device.
+  class Peers {
+   public:
+    void drop() {
+      std::lock_guard<std::mutex> g(mu_);
+      for (BlockPool* p : pools_) p->drop();
+    }
+
+   private:
+    friend class BlockPool;
+    std::mutex mu_;  // held before a pool's own
+    std::set<BlockPool*> pools_;
+  };
+
+  BlockPool(Device d, Peers& peers) : dev_(d), peers_(peers) {
+    std::lock_guard<std::mutex> g(peers_.mu_);
+    peers_.pools_.insert(this);
+  }
+  ~BlockPool() {
+    std::lock_guard<std::mutex> g(peers_.mu_);
+    peers_.pools_.erase(this);
+  }
+  BlockPool(const BlockPool&) = delete;
 
   // `keeps`: false allocates and frees exactly what is asked for, and keeps nothing (a context
   // whose budget counts what is allocated).
@@ -40,14 +63,21 @@ class BlockPool {
         return true;
       }
     }
-    if (dev_.alloc(p, block)) return true;
-    drop();
-    if (dev_.alloc(p, block)) return true;
+    if (alloc_exact(p, block)) return true;
     if (block != bytes && dev_.alloc(p, bytes)) {
       std::lock_guard<std::mutex> g(mu_);
       unrounded_.insert(*p);
       return true;
     }
+    *p = nullptr;
+    return false;
+  }
+
+  // A block of exactly `bytes` from the device, to be given back to it (free).
+  bool alloc_exact(void** p, size_t bytes) {
+    if (dev_.alloc(p, bytes)) return true;
+    peers_.drop();
+    if (dev_.alloc(p, bytes)) return true;
     *p = nullptr;
     return false;
   }
@@ -108,6 +138,7 @@ class BlockPool {
   }
 
   Device dev_;
+  Peers& peers_;
   std::mutex mu_;
   std::multimap<size_t, void*> kept_;  // by size
   size_t kept_bytes_ = 0;

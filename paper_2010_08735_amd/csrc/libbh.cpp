@@ -200,13 +200,24 @@ struct HipBlocks {
   bool wait() { return hipDeviceSynchronize() == hipSuccess; }
 };
 
+using BlocksPool = BlockPool<HipBlocks>;
+
+// the pools of a device, for the life of the process
+static BlocksPool::Peers& pools_of(int device) {
+  static std::mutex mu;
+  static auto* all = new std::map<int, BlocksPool::Peers>;
+  std::lock_guard<std::mutex> g(mu);
+  return (*all)[device];
+}
+
 struct bh_ctx {
-  int device = 0;
+  explicit bh_ctx(int dev) : device(dev), pool(HipBlocks(), pools_of(dev)) {}
+  const int device;
   uint64_t budget = 0;
   std::atomic<uint64_t> used{0};
   // blocks of released handles and finished builds, kept for the next ones (bh_pool.h); none in a
   // context with a budget, which counts what is allocated
-  BlockPool<HipBlocks> pool;
+  BlocksPool pool;
   int cus = 256;
   std::mutex mu;  // resources, tile config, batch staging
   std::map<std::string, bh_tables*> tables;
@@ -275,6 +286,13 @@ static void dev_free(bh_ctx* c, void* p, size_t bytes) {
   c->used -= bytes;
 }
 
+// Device memory that no budget counts (temporaries of reads and measurements, the serving
+// thread's records), released with hipFree.
+template <class T>
+static hipError_t raw_alloc(bh_ctx* c, T** p, size_t bytes) {
+  return c->pool.alloc_exact((void**)p, bytes) ? hipSuccess : hipErrorOutOfMemory;
+}
+
 // dev_free of a block (of `bytes` when it was allocated) that no queued or running work uses,
 // on any stream: it may be handed out again at once.
 static void dev_recycle(bh_ctx* c, void* p, size_t bytes) {
@@ -286,7 +304,7 @@ static void dev_recycle(bh_ctx* c, void* p, size_t bytes) {
 // Waits for the device, then takes back the blocks of one handle.
 struct Releasing {
   bh_ctx* c;
-  BlockPool<HipBlocks>::Release blocks;
+  BlocksPool::Release blocks;
   explicit Releasing(bh_ctx* ctx) : c(ctx), blocks(ctx->pool) {}
   void operator()(void* p, size_t bytes) {
     if (!p) return;
@@ -341,8 +359,7 @@ extern "C" bh_status bh_create(int device, uint64_t budget, bh_ctx** out) {
   HIPCHK(hipGetDeviceCount(&n));
   if (device < 0 || device >= n) return fail(BH_EINVAL, "no such device");
   HIPCHK(hipSetDevice(device));
-  std::unique_ptr<bh_ctx> c(new bh_ctx);
-  c->device = device;
+  std::unique_ptr<bh_ctx> c(new bh_ctx(device));
   c->budget = budget;
   c->pool.keeps = budget == 0;
   hipDeviceProp_t prop;
@@ -951,7 +968,7 @@ extern "C" bh_status bh_stars_download(const bh_stars* s, int32_t level, float* 
   HIPCHK(hipMemcpy(&scale, s->scale + level, sizeof(float), hipMemcpyDeviceToHost));
   float4* tmp = nullptr;
   const int per = s->bands ? 2 : 1;  // float4 records per texel
-  HIPCHK(hipMalloc(&tmp, sizeof(float4) * cnt * per));
+  HIPCHK(raw_alloc(c, &tmp, sizeof(float4) * cnt * per));
   const size_t tsz = (s->fp16 ? 8 : 16) * per;
   const void* lvl = (const char*)s->tex + tsz * s->level_off[level];
   hipError_t e = s->bands ? launch_star_unpack_bands(lvl, cnt, scale, s->fp16, tmp, nullptr)
@@ -1107,7 +1124,7 @@ extern "C" bh_status bh_color_shift_table_download(bh_ctx* c, float* host) {
   if (st) return st;
   const size_t bytes = sizeof(float4) * kCshiftN * kCshiftN * kCshiftN;
   float4* tmp = nullptr;
-  HIPCHK(hipMalloc(&tmp, bytes));
+  HIPCHK(raw_alloc(c, &tmp, bytes));
   hipError_t e = launch_cshift_nodes(c->ctab, tmp, nullptr);
   if (e == hipSuccess) e = hipMemcpy(host, tmp, bytes, hipMemcpyDeviceToHost);
   (void)hipFree(tmp);
@@ -1656,8 +1673,8 @@ extern "C" bh_status bh_footprint_texels(bh_ctx* c, const bh_tables* t, const bh
   int64_t words = (int64_t)((total + 31) / 32);
   uint32_t* bits = nullptr;
   unsigned long long* cnt = nullptr;  // [0] distinct texels, [1] requested bytes
-  HIPCHK(hipMalloc(&bits, sizeof(uint32_t) * words));
-  hipError_t e = hipMalloc(&cnt, 2 * sizeof(unsigned long long));
+  HIPCHK(raw_alloc(c, &bits, sizeof(uint32_t) * words));
+  hipError_t e = raw_alloc(c, &cnt, 2 * sizeof(unsigned long long));
   if (e == hipSuccess) e = hipMemset(bits, 0, sizeof(uint32_t) * words);
   if (e == hipSuccess) e = hipMemset(cnt, 0, 2 * sizeof(unsigned long long));
   if (e == hipSuccess)
@@ -1684,8 +1701,8 @@ extern "C" bh_status bh_probe_l2_read(bh_ctx* c, int64_t window_bytes, int32_t r
   float4* buf = nullptr;
   float* sink = nullptr;
   hipEvent_t e0 = nullptr, e1 = nullptr;
-  hipError_t e = hipMalloc(&buf, window_bytes);
-  if (e == hipSuccess) e = hipMalloc(&sink, sizeof(float) * grid);
+  hipError_t e = raw_alloc(c, &buf, window_bytes);
+  if (e == hipSuccess) e = raw_alloc(c, &sink, sizeof(float) * grid);
   if (e == hipSuccess) e = hipMemset(buf, 0, window_bytes);
   if (e == hipSuccess) e = hipEventCreate(&e0);
   if (e == hipSuccess) e = hipEventCreate(&e1);
@@ -1793,7 +1810,7 @@ struct ServeBackend {
       e = hipMemPoolSetAttribute(img_pool, hipMemPoolAttrReleaseThreshold, &keep);
     }
     for (int k = 0; k < slots && e == hipSuccess; ++k) {
-      e = hipMalloc(&dcounter[k], sizeof(int) * 16);
+      e = raw_alloc(c, &dcounter[k], sizeof(int) * 16);
       if (e == hipSuccess) e = hipEventCreateWithFlags(&slot_free[k], hipEventDisableTiming);
       if (e == hipSuccess) e = hipEventCreateWithFlags(&copied[k], hipEventDisableTiming);
     }
@@ -1832,6 +1849,9 @@ struct ServeBackend {
     const uint64_t before = c->used.fetch_add(bytes);
     if (!c->budget || before + bytes <= c->budget) {
       void* p = nullptr;
+      if (hipMallocFromPoolAsync(&p, bytes, img_pool, stream) == hipSuccess) return p;
+      (void)hipGetLastError();
+      pools_of(c->device).drop();
       if (hipMallocFromPoolAsync(&p, bytes, img_pool, stream) == hipSuccess) return p;
     }
     c->used -= bytes;
@@ -1886,8 +1906,8 @@ struct ServeBackend {
       druns[slot] = nullptr;
       rcap[slot] = 0;
       const size_t cap = std::max<size_t>(vds.size(), 256);
-      if (hipMalloc(&dviews[slot], sizeof(ViewDev) * cap) != hipSuccess ||
-          hipMalloc(&druns[slot], sizeof(TileRun) * cap) != hipSuccess) {
+      if (raw_alloc(c, &dviews[slot], sizeof(ViewDev) * cap) != hipSuccess ||
+          raw_alloc(c, &druns[slot], sizeof(TileRun) * cap) != hipSuccess) {
         dev_ok = false;
         return sched::kEDEVICE;
       }

@@ -61,7 +61,8 @@ constexpr size_t MiB = (size_t)1 << 20;
 
 static void reuse() {
   Memory m;
-  Pool pool(Fake{&m});
+  Pool::Peers peers;
+  Pool pool(Fake{&m}, peers);
   void *a, *b;
   CHECK(pool.alloc(&a, 10 * MiB));
   {
@@ -79,7 +80,8 @@ static void reuse() {
 // A wait that is refused does not make a block idle: it goes to the device, not to the next build.
 static void refused_wait() {
   Memory m;
-  Pool pool(Fake{&m});
+  Pool::Peers peers;
+  Pool pool(Fake{&m}, peers);
   void *a, *b;
   CHECK(pool.alloc(&a, 4 * MiB));
   m.refuse_wait = true;
@@ -103,7 +105,8 @@ static void refused_wait() {
 static void allocation_failure() {
   Memory m;
   m.room = 64 * MiB;
-  Pool pool(Fake{&m});
+  Pool::Peers peers;
+  Pool pool(Fake{&m}, peers);
   void *a, *b;
   CHECK(pool.alloc(&a, 40 * MiB));
   pool.recycle(a, 40 * MiB);
@@ -119,10 +122,36 @@ static void allocation_failure() {
   CHECK(!pool.alloc(&b, 2 * MiB) && b == nullptr);
 }
 
+// The blocks that other pools of the device keep are given back too, for a block of any kind, and
+// a pool that is gone is not asked.
+static void peers() {
+  Memory m;
+  m.room = 100 * MiB;
+  Pool::Peers all;
+  Pool one(Fake{&m}, all);
+  void *a, *b;
+  {
+    Pool two(Fake{&m}, all);
+    CHECK(two.alloc(&a, 80 * MiB));
+    two.recycle(a, 80 * MiB);
+    CHECK(one.alloc(&b, 64 * MiB) && m.in_use == 64 * MiB);
+    one.free(b);
+    CHECK(two.alloc(&a, 80 * MiB));
+    two.recycle(a, 80 * MiB);
+    CHECK(one.alloc_exact(&b, 30 * MiB + 5) && m.in_use == 30 * MiB + 5);
+    one.free(b);
+    CHECK(two.alloc(&a, 80 * MiB));
+    two.free(a);
+  }
+  m.room = MiB;
+  CHECK(!one.alloc_exact(&b, 2 * MiB) && b == nullptr && m.live.empty());
+}
+
 // With a budget nothing is rounded or kept.
 static void budget() {
   Memory m;
-  Pool pool(Fake{&m});
+  Pool::Peers peers;
+  Pool pool(Fake{&m}, peers);
   pool.keeps = false;
   void* a;
   CHECK(pool.alloc(&a, 9 * MiB + 1) && m.in_use == 9 * MiB + 1);
@@ -132,7 +161,8 @@ static void budget() {
 
 static void threads() {
   Memory m;
-  Pool pool(Fake{&m});
+  Pool::Peers peers;
+  Pool pool(Fake{&m}, peers);
   std::mutex mu;
   std::map<void*, int> held;
   std::vector<std::thread> ts;
@@ -167,6 +197,7 @@ int main(int argc, char** argv) {
   } all[] = {{"reuse", reuse},
              {"refused_wait", refused_wait},
              {"allocation_failure", allocation_failure},
+             {"peers", peers},
              {"budget", budget},
              {"threads", threads}};
   for (const auto& s : all)
