@@ -6,13 +6,15 @@
 // Fresh device memory is cleared before a process gets it, and a build that allocates and frees a
 // 268 MB map waits for that: a new 6 x 2048^2 star map took 4.5 ms of which its kernels are 0.35.
 // So idle blocks of at least kKeepLeast are kept, at most kKeepMost in all, and handed out again
-// by size.  Sizes are rounded up to eight steps an octave so that nearly equal builds share
-// blocks.  Kept blocks are freed with the pool's owner, and all pools of a device (Peers) free
+// by size.  Past kKeepMost the blocks kept longest make room, so that sizes no longer asked for do
+// not fill the pool for good.  Sizes are rounded up to eight steps an octave so that nearly equal
+// builds share blocks.  Kept blocks are freed with the pool's owner, and all pools of a device (Peers) free
 // theirs when an allocation on it fails, before it is tried again.
 #pragma once
 
 #include <cstddef>
-#include <map>
+#include <iterator>
+#include <list>
 #include <mutex>
 #include <set>
 
@@ -55,13 +57,13 @@ class BlockPool {
     const size_t block = block_size(bytes);
     if (block >= kKeepLeast) {
       std::lock_guard<std::mutex> g(mu_);
-      auto it = kept_.find(block);
-      if (it != kept_.end()) {
-        *p = it->second;
-        kept_.erase(it);
-        kept_bytes_ -= block;
-        return true;
-      }
+      for (auto it = kept_.rbegin(); it != kept_.rend(); ++it)
+        if (it->size == block) {
+          *p = it->p;
+          kept_.erase(std::next(it).base());
+          kept_bytes_ -= block;
+          return true;
+        }
     }
     if (alloc_exact(p, block)) return true;
     if (block != bytes && dev_.alloc(p, bytes)) {
@@ -97,11 +99,18 @@ class BlockPool {
   void recycle(void* p, size_t bytes) {
     if (!p) return;
     const size_t block = block_size(bytes);
-    if (keeps && block >= kKeepLeast) {
-      std::lock_guard<std::mutex> g(mu_);
-      if (!unrounded_.count(p) && kept_bytes_ + block <= kKeepMost) {
-        kept_.emplace(block, p);
+    if (keeps && block >= kKeepLeast && block <= kKeepMost) {
+      std::unique_lock<std::mutex> g(mu_);
+      if (!unrounded_.count(p)) {
+        std::list<Kept> out;  // the oldest, freed after the lock is given up (a free waits)
+        while (kept_bytes_ + block > kKeepMost) {
+          kept_bytes_ -= kept_.front().size;
+          out.splice(out.end(), kept_, kept_.begin());
+        }
+        kept_.push_back(Kept{p, block});
         kept_bytes_ += block;
+        g.unlock();
+        for (const Kept& k : out) dev_.free(k.p);
         return;
       }
     }
@@ -123,10 +132,13 @@ class BlockPool {
 
   // Frees every kept block.
   void drop() {
-    std::lock_guard<std::mutex> g(mu_);
-    for (auto& kv : kept_) dev_.free(kv.second);
-    kept_.clear();
-    kept_bytes_ = 0;
+    std::list<Kept> out;
+    {
+      std::lock_guard<std::mutex> g(mu_);
+      out.swap(kept_);
+      kept_bytes_ = 0;
+    }
+    for (const Kept& k : out) dev_.free(k.p);
   }
 
  private:
@@ -140,9 +152,13 @@ class BlockPool {
   Device dev_;
   Peers& peers_;
   std::mutex mu_;
-  std::multimap<size_t, void*> kept_;  // by size
+  struct Kept {
+    void* p;
+    size_t size;
+  };
+  std::list<Kept> kept_;       // oldest first; at most kKeepMost / kKeepLeast
   size_t kept_bytes_ = 0;
-  std::set<void*> unrounded_;          // blocks smaller than their size step, never kept
+  std::set<void*> unrounded_;  // blocks smaller than their size step, never kept
 };
 
 }  // namespace bh

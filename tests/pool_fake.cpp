@@ -122,6 +122,41 @@ static void allocation_failure() {
   CHECK(!pool.alloc(&b, 2 * MiB) && b == nullptr);
 }
 
+// A full pool: the blocks kept longest make room, so later builds still find theirs; the bound on
+// what is kept holds, and a block above it is never kept.
+static void full_pool() {
+  Memory m;
+  Pool::Peers peers;
+  Pool pool(Fake{&m}, peers);
+  std::vector<void*> old;
+  for (int k = 0; k < 8; ++k) {  // 8 x 128 MiB: full
+    void* p;
+    CHECK(pool.alloc(&p, 128 * MiB));
+    old.push_back(p);
+  }
+  for (void* p : old) pool.recycle(p, 128 * MiB);
+  CHECK(m.in_use == bh::kKeepMost);
+  int allocs = 0;
+  for (int r = 0; r < 5; ++r) {  // a session of other sizes
+    void *a, *b;
+    CHECK(pool.alloc(&a, 288 * MiB) && pool.alloc(&b, 60 * MiB));
+    if (r == 0) allocs = m.allocs;
+    pool.recycle(a, 288 * MiB);
+    pool.recycle(b, 60 * MiB);
+    CHECK(m.in_use <= bh::kKeepMost);
+  }
+  CHECK(m.allocs == allocs);  // only the first of them asked the device
+  CHECK(m.freed.size() == 3 && m.freed[0] == old[0] && m.freed[2] == old[2]);
+  void* big;
+  m.room = (size_t)16 << 30;
+  CHECK(pool.alloc(&big, bh::kKeepMost + 1));
+  const size_t before = m.in_use;
+  pool.recycle(big, bh::kKeepMost + 1);
+  CHECK(m.in_use < before && m.in_use <= bh::kKeepMost);
+  pool.drop();
+  CHECK(m.live.empty());
+}
+
 // The blocks that other pools of the device keep are given back too, for a block of any kind, and
 // a pool that is gone is not asked.
 static void peers() {
@@ -197,6 +232,7 @@ int main(int argc, char** argv) {
   } all[] = {{"reuse", reuse},
              {"refused_wait", refused_wait},
              {"allocation_failure", allocation_failure},
+             {"full_pool", full_pool},
              {"peers", peers},
              {"budget", budget},
              {"threads", threads}};
