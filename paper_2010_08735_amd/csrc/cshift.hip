@@ -133,19 +133,6 @@ __global__ void k_cshift_table(CshiftRule q, const double4* __restrict__ spec,
   tab[t] = make_float4(out[0], out[1], out[2], 0.0f);
 }
 
-// the table with k innermost, as the caller reads it
-__global__ void k_cshift_nodes(const float4* __restrict__ tab, float4* __restrict__ out) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= kCshiftN * kCshiftN * kCshiftN) return;
-  out[t] = tab[(t % kCshiftN) * kCshiftN * kCshiftN + t / kCshiftN];
-}
-
-hipError_t launch_cshift_nodes(const float4* tab, float4* out, hipStream_t s) {
-  const int nt = kCshiftN * kCshiftN * kCshiftN;
-  hipLaunchKernelGGL(k_cshift_nodes, dim3((nt + 255) / 256), dim3(256), 0, s, tab, out);
-  return hipGetLastError();
-}
-
 hipError_t launch_cshift_build(const CshiftRule& q, double4* spec, float4* tab, hipStream_t s) {
   const int nc = kCshiftN * kCshiftN, nt = kCshiftN * kCshiftN * kCshiftN;
   hipLaunchKernelGGL(k_cshift_spectra, dim3((nc + 63) / 64), dim3(64), 0, s, q, spec);

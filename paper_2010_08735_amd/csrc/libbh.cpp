@@ -14,6 +14,7 @@
 #include <set>
 #include <memory>
 #include <mutex>
+#include <new>
 #include <string>
 #include <thread>
 #include <tuple>
@@ -51,7 +52,6 @@ hipError_t launch_area_build(const float* it, int n0, float2* tex, int* bad, hip
 hipError_t launch_area_build_bands(const float* rgbx, int n0, float4* tex, int* bad,
                                    hipStream_t s);
 hipError_t launch_cshift_build(const CshiftRule& q, double4* spec, float4* tab, hipStream_t s);
-hipError_t launch_cshift_nodes(const float4* tab, float4* out, hipStream_t s);
 hipError_t launch_render_batch(int cfg, int persistent, int feat, const ViewDev* views,
                                const TileRun* runs, int nruns, int ntiles, int* counter,
                                const TablesDev& T, const LutDev& L, int grid, hipStream_t s);
@@ -1122,13 +1122,16 @@ extern "C" bh_status bh_color_shift_table_download(bh_ctx* c, float* host) {
   HIPCHK(hipSetDevice(c->device));
   bh_status st = ensure_cshift(c, nullptr);
   if (st) return st;
-  const size_t bytes = sizeof(float4) * kCshiftN * kCshiftN * kCshiftN;
-  float4* tmp = nullptr;
-  HIPCHK(raw_alloc(c, &tmp, bytes));
-  hipError_t e = launch_cshift_nodes(c->ctab, tmp, nullptr);
-  if (e == hipSuccess) e = hipMemcpy(host, tmp, bytes, hipMemcpyDeviceToHost);
-  (void)hipFree(tmp);
-  if (e != hipSuccess) return fail(BH_EDEVICE, hipGetErrorString(e));
+  // plane by plane (D outermost on the device, innermost for the caller)
+  constexpr size_t plane = (size_t)kCshiftN * kCshiftN;
+  std::unique_ptr<float4[]> nodes(new (std::nothrow) float4[plane]);
+  if (!nodes) return fail(BH_ENOMEM, "no host memory for the colour-shift table");
+  for (size_t k = 0; k < kCshiftN; ++k) {
+    HIPCHK(hipMemcpy(nodes.get(), c->ctab + k * plane, sizeof(float4) * plane,
+                     hipMemcpyDeviceToHost));
+    for (size_t ij = 0; ij < plane; ++ij)
+      memcpy(host + 4 * (ij * kCshiftN + k), &nodes[ij], sizeof(float4));
+  }
   return BH_OK;
 }
 
