@@ -63,6 +63,8 @@ const char* bh_last_error(const bh_ctx* ctx);
  * counted, nor is the rounding of its blocks (up to an eighth of each of 1 MiB and more), and they
  * go back to the device when an allocation of any context on it fails and in bh_destroy. */
 uint64_t bh_bytes_in_use(const bh_ctx* ctx);
+/* Give the kept blocks back to the device now (before another allocator needs the memory). */
+bh_status bh_trim(bh_ctx* ctx);
 /* Release any handle the library returned (tables, star maps, area maps, particles, bloom
  * pyramids): the same as the release call of its type.  Tables and star maps are
  * reference-counted (one release per build call that returned them); the others are

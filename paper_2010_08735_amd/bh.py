@@ -22,7 +22,7 @@ BH_DENSITY_UNIFORM, BH_DENSITY_PARTICLES = 0, 1
 
 # every symbol include/bh.h declares
 EXPORTS = [
-    "bh_create", "bh_destroy", "bh_last_error", "bh_bytes_in_use", "bh_release",
+    "bh_create", "bh_destroy", "bh_last_error", "bh_bytes_in_use", "bh_trim", "bh_release",
     "bh_precompute_tables", "bh_tables_download", "bh_tables_download_time", "bh_release_tables",
     "bh_create_particles", "bh_release_particles",
     "bh_bloom_create", "bh_bloom_apply", "bh_bloom_release", "bh_bloom_apply_display",
@@ -91,6 +91,7 @@ def lib():
             "bh_last_error": ([vp], C.c_char_p),
             "bh_release": ([vp], i32),
             "bh_bytes_in_use": ([vp], u64),
+            "bh_trim": ([vp], i32),
             "bh_precompute_tables": ([vp, C.POINTER(TableParams), vp, C.POINTER(vp)], i32),
             "bh_tables_download": ([vp, vp, vp], i32),
             "bh_tables_download_time": ([vp, vp, vp], i32),
@@ -166,6 +167,10 @@ def bh_destroy(ctx: int) -> None:
 
 def bh_bytes_in_use(ctx: int) -> int:
     return lib().bh_bytes_in_use(ctx)
+
+
+def bh_trim(ctx) -> None:
+    _check(lib().bh_trim(ctx))
 
 
 def bh_precompute_tables(ctx, d_n=512, u_ne=64, u_nphi=32, precision=BH_TAB_FP64_BAND,

@@ -447,6 +447,13 @@ extern "C" void bh_destroy(bh_ctx* c) {
 
 extern "C" uint64_t bh_bytes_in_use(const bh_ctx* c) { return c ? c->used.load() : 0; }
 
+extern "C" bh_status bh_trim(bh_ctx* c) {
+  if (!c) return fail(BH_EINVAL, "NULL context");
+  HIPCHK(hipSetDevice(c->device));
+  c->pool.drop();
+  return BH_OK;
+}
+
 // ---- tables --------------------------------------------------------------------------------
 
 static std::string table_key(const bh_table_params& p) {

@@ -176,6 +176,21 @@ def test_maps_built_in_released_blocks(budget):
     bh.bh_destroy(ctx)
 
 
+def test_trim_gives_kept_blocks_back():
+    """A released pyramid's blocks stay with the context, and bh_trim gives them back."""
+    import torch
+    ctx = bh.bh_create(0, 0)
+    try:
+        start = torch.cuda.mem_get_info()[0]
+        bh.bh_release(bh.bh_bloom_create(ctx, 8192, 4096, 1))  # 2 x 128 MiB
+        kept = start - torch.cuda.mem_get_info()[0]
+        bh.bh_trim(ctx)
+        left = start - torch.cuda.mem_get_info()[0]
+        assert kept >= 2 << 27 and left < 1 << 24, (kept, left)
+    finally:
+        bh.bh_destroy(ctx)
+
+
 @pytest.mark.parametrize("fmt", [bh.BH_TEXEL_FP16, bh.BH_TEXEL_FP32])
 def test_infinite_temperatures_stay_infinite(gpu_ctx, fmt):
     """A texel's temperature is the weighted mean of its stars', in every level: infinite when one
