@@ -230,8 +230,8 @@ __device__ __forceinline__ float brightest(const Master<BANDS>& m) {
 // Quotients by one divisor d > 0: a reciprocal by Newton's iteration, then each quotient
 // corrected once by its own remainder, which rounds as the division itself does (Markstein; the
 // stored texels are the division's bit for bit).  Divisors that could overflow or vanish on the
-// way, and an infinite numerator (a star of infinite temperature), which has no remainder, take
-// the plain division.
+// way take the plain division.  An infinite numerator (a temperature can be infinite) has no
+// remainder: of_any returns it as it is.
 struct Divider {
   double d, r;
   bool plain;
@@ -242,9 +242,12 @@ struct Divider {
     r = fma(fma(-x, r, 1.0), r, r);
   }
   __device__ __forceinline__ float operator()(double n) const {
-    if (plain || isinf(n)) return (float)(n / d);
+    if (plain) return (float)(n / d);
     const double q = n * r;
     return (float)fma(fma(-d, q, n), r, q);
+  }
+  __device__ __forceinline__ float of_any(double n) const {
+    return !plain && isinf(n) ? (float)n : (*this)(n);
   }
 };
 
@@ -283,7 +286,7 @@ struct Sums {
     } else if (s[0] > 0.0) {
       const Divider over(s[0]);
       m.v[0] = (float)s[0];
-      m.v[1] = over(s[1]);
+      m.v[1] = over.of_any(s[1]);
       m.v[2] = over(s[2]);
       m.v[3] = over(s[3]);
     }
