@@ -774,6 +774,20 @@ extern "C" bh_status bh_bloom_release(bh_bloom* b) {
 
 static bh_status ensure_cshift(bh_ctx* c, hipStream_t hs);
 
+// Scratch of one build, given back on every way out.
+struct BuildScratch {
+  bh_ctx* c;
+  char* p = nullptr;
+  size_t bytes = 0;
+  bool idle = false;  // nothing that uses it is queued or running
+  explicit BuildScratch(bh_ctx* ctx) : c(ctx) {}
+  bh_status get(size_t b) {
+    bytes = b;
+    return dev_alloc(c, b, (void**)&p);
+  }
+  ~BuildScratch() { idle ? dev_recycle(c, p, bytes) : dev_free(c, p, bytes); }
+};
+
 // (I, T) maps (bands = 0: intensity_dev and temperature_dev) or band-colour maps (bands = 1:
 // rgb in intensity_dev, three floats per star, temperature_dev unused)
 static bh_status build_stars(bh_ctx* c, const float* dir_xyz_dev, const float* intensity_dev,
@@ -827,50 +841,63 @@ static bh_status build_stars(bh_ctx* c, const float* dir_xyz_dev, const float* i
   const size_t o_val = take(values ? (bands ? 20 : 16) * nstars : 0);
   const size_t o_tmax = take(star_tile_max_bytes() * (size_t)B.tiles);
   const size_t o_tail = take(star_tail_texel_bytes(bands) * (size_t)tail_all);
-  char* scratch = nullptr;
-  bh_status st = dev_alloc(c, bytes, (void**)&scratch);
-  // no room to build: the hash alone, since a resident map needs no scratch
-  const bool only_hash = st != BH_OK;
-  const std::string no_room = g_err;
-  if (only_hash) {
-    bytes = 16;
-    st = dev_alloc(c, bytes, (void**)&scratch);
-    if (st) return st;
-  }
-  struct Guard {  // gives the scratch back on every way out
-    bh_ctx* c;
-    char* p;
-    size_t bytes;
-    bool idle;  // nothing that uses it is queued or running
-    ~Guard() { idle ? dev_recycle(c, p, bytes) : dev_free(c, p, bytes); }
-  } guard{c, scratch, bytes, false};
-  unsigned long long* acc = (unsigned long long*)(scratch + o_acc);
-  int* count = (int*)(scratch + o_count);
-  // content hash and bin counts of the arrays (ordered after the caller's work on the stream)
+  // The content hash (ordered after the caller's work on the stream), and with the build's scratch
+  // also the bin counts and whether a band value is bad, in the same pass over the arrays.
   struct {
     unsigned long long hash;
     int bad, pad;
   } first = {0, 0, 0};
-  {
-    hipError_t e = launch_fill_int((int*)scratch,
-                                   (int64_t)(std::min(cleared, bytes) / sizeof(int)), 0, hs);
+  const auto hash_pass = [&](BuildScratch& m) -> bh_status {
+    const bool counts = m.bytes == bytes;
+    unsigned long long* acc = (unsigned long long*)(m.p + o_acc);
+    hipError_t e = launch_fill_int((int*)m.p, (int64_t)(counts ? cleared : m.bytes) / 4, 0, hs);
     if (e == hipSuccess)
       e = launch_star_count(dir_xyz_dev, intensity_dev, temperature_dev, n, n0, bands, acc,
-                            (int*)(acc + 1), only_hash ? nullptr : count, hs);
-    if (e == hipSuccess) e = hipMemcpyAsync(&first, acc, 16, hipMemcpyDeviceToHost, hs);
+                            counts ? (int*)(acc + 1) : nullptr,
+                            counts ? (int*)(m.p + o_count) : nullptr, hs);
+    if (e == hipSuccess)
+      e = hipMemcpyAsync(&first, acc, counts ? 16 : 8, hipMemcpyDeviceToHost, hs);
     if (e == hipSuccess) e = hipStreamSynchronize(hs);
     if (e != hipSuccess) return fail(BH_EDEVICE, std::string("star hash: ") + hipGetErrorString(e));
-  }
-  guard.idle = true;
-  std::lock_guard<std::mutex> g(c->mu);
-  StarKey key{first.hash, n, n0, texel_format, bands};
-  auto found = c->stars.find(key);
-  if (found != c->stars.end()) {
+    m.idle = true;
+    return BH_OK;
+  };
+  // the resident map of these contents, if there is one (c->mu held)
+  const auto shared = [&] {
+    auto found = c->stars.find(StarKey{first.hash, n, n0, texel_format, bands});
+    if (found == c->stars.end()) return false;
     found->second->refs++;
     *out = found->second;
-    return BH_OK;
+    return true;
+  };
+  // A resident map needs no scratch: where one of this size exists, or where there is no room to
+  // build, the hash comes first, alone.
+  bool alone = false;
+  {
+    std::lock_guard<std::mutex> g(c->mu);
+    for (const auto& kv : c->stars)
+      alone = alone || (std::get<1>(kv.first) == n && std::get<2>(kv.first) == n0 &&
+                        std::get<3>(kv.first) == texel_format && std::get<4>(kv.first) == bands);
   }
-  if (only_hash) return fail(BH_ENOMEM, no_room);
+  BuildScratch build{c};
+  bh_status st = alone ? BH_OK : build.get(bytes);
+  if (alone || st) {
+    const std::string no_room = g_err;
+    BuildScratch hash{c};
+    bh_status hst = hash.get(sizeof(first.hash));
+    if (!hst) hst = hash_pass(hash);
+    if (hst) return hst;
+    std::lock_guard<std::mutex> g(c->mu);
+    if (shared()) return BH_OK;
+    if (st) return fail(st, no_room);
+  }
+  if (alone && (st = build.get(bytes))) return st;
+  if ((st = hash_pass(build))) return st;
+  char* const scratch = build.p;
+  int* count = (int*)(scratch + o_count);
+  std::lock_guard<std::mutex> g(c->mu);
+  if (shared()) return BH_OK;
+  const StarKey key{first.hash, n, n0, texel_format, bands};
   int levels = 0;
   while ((n0 >> levels) >= 1) ++levels;
   std::vector<uint32_t> off(levels), ooff(levels);
@@ -926,10 +953,10 @@ static bh_status build_stars(bh_ctx* c, const float* dir_xyz_dev, const float* i
     }
     B.off[levels] = (uint32_t)total;
     B.tail_texels = (int64_t)total - B.off[B.tl + 1];
-    guard.idle = false;
+    build.idle = false;
     e = launch_star_build(B, count, n, bands, hs);
     if (e == hipSuccess) e = hipStreamSynchronize(hs);
-    guard.idle = e == hipSuccess;
+    build.idle = e == hipSuccess;
   }
   if (st || e != hipSuccess || first.bad) {
     dev_free(c, s->tex, s->tex ? btex : 0);

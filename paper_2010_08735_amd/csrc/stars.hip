@@ -139,8 +139,8 @@ __device__ __forceinline__ uint64_t star_hash(const float* __restrict__ dirs,
 constexpr int kSortThreads = 1024, kSortPer = 8, kSortStars = kSortThreads * kSortPer;
 constexpr int kMaxBins = 1536;
 
-// Hash of the field, stars per bin (unless `count` is null), and whether a band value is
-// negative, infinite or NaN (which fails the whole build).  One 64-bit atomic per workgroup:
+// Hash of the field, stars per bin and whether a band value is negative, infinite or NaN, which
+// fails the whole build (unless `count` and `bad` are null).  One 64-bit atomic per workgroup:
 // one per wave queued 15 600 of them on the same address, 192 us for 10^6 stars.
 template <bool BANDS>
 __global__ void __launch_bounds__(kSortThreads)
@@ -169,7 +169,7 @@ __global__ void __launch_bounds__(kSortThreads)
     const Place p = place_star<BANDS>(dirs, inten, s, n0);
     if (p.lit) atomicAdd(&hist[bin_of(p, n0, bl)], 1);
   }
-  if (any_bad) atomicOr(bad, 1);
+  if (any_bad && bad) atomicOr(bad, 1);
   for (int o = 32; o > 0; o >>= 1) h += __shfl_xor(h, o);
   if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = h;
   __syncthreads();
@@ -835,7 +835,7 @@ int star_bin_log(int n0) {
   return bl;
 }
 
-// hash (*acc), *bad and the stars per bin (`count`, or null); all zero before
+// hash (*acc), *bad and the stars per bin (`bad`, `count`: or null); all zero before
 hipError_t launch_star_count(const float* dirs, const float* inten, const float* temp, int64_t n,
                              int n0, int bands, unsigned long long* acc, int* bad, int* count,
                              hipStream_t s) {

@@ -176,6 +176,46 @@ def test_maps_built_in_released_blocks(budget):
     bh.bh_destroy(ctx)
 
 
+def test_a_resident_map_is_found_without_scratch():
+    """While a thread asks again and again for a map that is resident, another's allocations still
+    find the budget's rest, which the scratch of a build would take."""
+    import threading
+    import torch
+    n, n0 = 2_000_000, 64  # scratch of a build: 12 bytes a star and more
+    f = scenes.star_field(n, 2)
+    d, i, t = (torch.from_numpy(a).cuda() for a in (f.dirs, f.intensity, f.temperature))
+    torch.cuda.synchronize()
+
+    def build(ctx, stream=None):
+        return bh.bh_build_stars(ctx, d.data_ptr(), i.data_ptr(), t.data_ptr(), n, n0,
+                                 bh.BH_TEXEL_FP16, stream)
+    probe = bh.bh_create(0, 0)
+    build(probe)
+    used = bh.bh_bytes_in_use(probe)
+    bh.bh_destroy(probe)
+    ctx = bh.bh_create(0, used + 40 * n)
+    h, stop, failed = build(ctx), threading.Event(), []
+
+    def ask():
+        s = torch.cuda.Stream()
+        while not stop.is_set():
+            assert build(ctx, s.cuda_stream) == h
+            bh.bh_release_stars(h)
+    asking = threading.Thread(target=ask)
+    asking.start()
+    try:
+        for _ in range(200):
+            try:  # 2 x 32 MB of the 80
+                bh.bh_release(bh.bh_bloom_create(ctx, 2 * 1600, 2 * 1250, 1))
+            except bh.BhError as e:
+                failed.append(e)
+    finally:
+        stop.set()
+        asking.join()
+        bh.bh_destroy(ctx)
+    assert not failed, failed[0]
+
+
 def test_trim_gives_kept_blocks_back():
     """A released pyramid's blocks stay with the context, and bh_trim gives them back."""
     import torch
