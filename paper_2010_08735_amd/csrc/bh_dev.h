@@ -64,10 +64,12 @@ struct StarBuild {
   const float* inten;    // intensities, or (R, G, B) of a band map
   const float* temp;     // (I, T) maps only
   int* order;            // star indices in bin order
-  uint32_t* where;       // their texels inside the bin
+  uint32_t* where;       // their texels inside the bin, or null: found again from the stars
   float4* val;           // their values, or null: read through `order` (stars.hip)
   int* start;            // first slot of each bin in `order`, then their end
-  int* next;             // star lists beyond the stars kept in LDS
+  int* list;             // dense tiles: star indices by texel, and by texel and index
+  int* sorted;           // (slots in the bin, where there are values)
+  int* slots;            // slots of `list`, with `val` only
   float* tilemax;        // the tiles' maxima per level
   float* tail;
   unsigned* maxbits;     // per level, zero before

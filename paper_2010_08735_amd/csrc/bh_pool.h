@@ -8,8 +8,8 @@
 // So idle blocks of at least kKeepLeast are kept, at most kKeepMost in all, and handed out again
 // by size.  Past kKeepMost the blocks kept longest make room, so that sizes no longer asked for do
 // not fill the pool for good.  Sizes are rounded up to eight steps an octave so that nearly equal
-// builds share blocks.  Kept blocks are freed with the pool's owner, and all pools of a device (Peers) free
-// theirs when an allocation on it fails, before it is tried again.
+// builds share blocks.  Kept blocks are freed with the pool's owner, and all pools of a device
+// (Peers) free theirs when an allocation on it fails, before it is tried again.
 #pragma once
 
 #include <cstddef>

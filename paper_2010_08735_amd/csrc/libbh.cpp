@@ -32,8 +32,8 @@ hipError_t launch_precompute(float* D, float* Dt, int d_n, float* U, float* Ut, 
 hipError_t launch_band_lut(float4* lut, int n, float x0, float dx, hipStream_t s);
 hipError_t launch_band_eval(const LutDev& L, const float* temps, int64_t n, float* out,
                             hipStream_t s);
-int star_tile_log(int n0);
-int star_bin_log(int n0);
+int star_tile_log(int n0, int64_t n);
+int star_bin_log(int n0, int64_t n);
 size_t star_tail_texel_bytes(int bands);
 size_t star_tile_max_bytes();
 hipError_t launch_star_count(const float* dirs, const float* inten, const float* temp, int64_t n,
@@ -812,9 +812,9 @@ static bh_status build_stars(bh_ctx* c, const float* dir_xyz_dev, const float* i
   B.inten = intensity_dev;
   B.temp = temperature_dev;
   B.n0 = n0;
-  B.tl = star_tile_log(n0);
+  B.tl = star_tile_log(n0, n);
   B.tiles = 6 * (n0 >> B.tl) * (n0 >> B.tl);
-  B.bl = star_bin_log(n0);
+  B.bl = star_bin_log(n0, n);
   B.bins = 6 * (n0 >> B.bl) * (n0 >> B.bl);
   // scratch of the build, one allocation: the hash, the bad-value flag and the level maxima
   // (cleared together with the bin counts), the bin starts, the star order and lists, the
@@ -831,14 +831,16 @@ static bh_status build_stars(bh_ctx* c, const float* dir_xyz_dev, const float* i
   const size_t o_acc = take(16), o_max = take(sizeof(unsigned) * 16);
   const size_t o_count = take(sizeof(int) * (size_t)B.bins), cleared = bytes;
   const size_t o_start = take(sizeof(int) * ((size_t)B.bins + 1));
-  const size_t o_order = take(sizeof(int) * nstars), o_where = take(sizeof(uint32_t) * nstars);
-  const size_t o_next = take(sizeof(int) * nstars);
-  // Star values in bin order save a gather of three cache lines a star in each pass over the
-  // tiles (10^6 stars on 6 x 2048^2: 131 + 167 -> 121 + 150 us, the scatter 32 -> 39 us), but not
-  // on maps denser than 9 n0^2 stars, where 28 or 32 bytes of scratch a star would exceed what
-  // a build needed when it kept every level's FP32 texels (152 n0^2 bytes and 12 a star).
-  const bool values = n <= 9ll * n0 * n0;
+  // The whole stays within what a build needed when it kept every level's FP32 texels (152 n0^2
+  // bytes, 280 for bands, and 12 a star): star values in bin order (they save a gather of three
+  // cache lines a star in each pass over the tiles: 10^6 stars on 6 x 2048^2 131 + 167 -> 121 + 150
+  // us, the scatter 32 -> 39) and their slots up to 6 n0^2 stars, and the stars' texels up to 32.
+  const bool values = n <= 6ll * n0 * n0, texels = n <= 32ll * n0 * n0;
+  const size_t o_order = take(sizeof(int) * nstars);
+  const size_t o_list = take(sizeof(int) * nstars), o_sorted = take(sizeof(int) * nstars);
+  const size_t o_where = take(texels ? sizeof(uint32_t) * nstars : 0);
   const size_t o_val = take(values ? (bands ? 20 : 16) * nstars : 0);
+  const size_t o_slots = take(values ? sizeof(int) * nstars : 0);
   const size_t o_tmax = take(star_tile_max_bytes() * (size_t)B.tiles);
   const size_t o_tail = take(star_tail_texel_bytes(bands) * (size_t)tail_all);
   // The content hash (ordered after the caller's work on the stream), and with the build's scratch
@@ -931,11 +933,13 @@ static bh_status build_stars(bh_ctx* c, const float* dir_xyz_dev, const float* i
   hipError_t e = hipSuccess;
   if (!st && !first.bad) {
     B.order = (int*)(scratch + o_order);
-    B.where = (uint32_t*)(scratch + o_where);
+    B.where = texels ? (uint32_t*)(scratch + o_where) : nullptr;
     B.val = values ? (float4*)(scratch + o_val) : nullptr;
     B.n = n;
     B.start = (int*)(scratch + o_start);
-    B.next = (int*)(scratch + o_next);
+    B.list = (int*)(scratch + o_list);
+    B.sorted = (int*)(scratch + o_sorted);
+    B.slots = (int*)(scratch + o_slots);
     B.tilemax = (float*)(scratch + o_tmax);
     B.tail = (float*)(scratch + o_tail);
     B.maxbits = (unsigned*)(scratch + o_max);

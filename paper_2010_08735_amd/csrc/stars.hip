@@ -15,14 +15,15 @@
 // B / scale_L, p_u, p_v, 0, 0, 0) with the per-level power of two of the (I, T) format chosen
 // from the level's largest band value, or the same eight values in FP32.
 //
-// Build.  The level-0 map is cut into square tiles (64 x 64 texels, 32 x 32 on small maps) and
-// the stars are sorted into bins of one or more tiles (count, scan, scatter).  One workgroup
-// then owns a tile: it picks its stars from the bin, lists them per texel in LDS, merges them, and forms every mip level that fits inside
-// the tile, so no level ever goes through memory.  The FP16 scales need each level's maximum
-// first: a first pass over the tiles only finds the maxima and the tiles' topmost texels, from
-// which k_star_tail forms the remaining levels; a second pass merges again (the stars are few
-// against the texels) and writes the stored texels and the occupancy bits, each byte once.
-// 10^6 stars on 6 x 2048^2: 350 us of kernels (count 19, scatter 39, tiles 121 and 150, tail 13),
+// Build.  The level-0 map is cut into square tiles (star_tile_log) and the stars are sorted into
+// bins of one or more tiles (count, scan, scatter).  One workgroup then owns a tile: it picks its
+// stars from the bin, lists them per texel in LDS (or sorts them, where they are many), merges
+// them, and forms every mip level that fits inside the tile, so no level ever goes through
+// memory.  The FP16 scales need each level's maximum first: a first pass over the tiles only
+// finds the maxima and the tiles' topmost texels, from which k_star_tail forms the remaining
+// levels; a second pass merges again (the stars are few against the texels) and writes the
+// stored texels and the occupancy bits, each byte once.
+// 10^6 stars on 6 x 2048^2: 351 us of kernels (count 19, scatter 41, tiles 118 and 149, tail 13),
 // where linking the stars through a texel-sized head array and passing every level through
 // FP32 texels in memory took 1550 us, 60 launches and 0.9 GB of scratch.  The map's own 277 MB
 // are 45 us; the tile passes wait on their chains of LDS and FP64 latency (a wave lives for 13
@@ -373,7 +374,7 @@ __global__ void __launch_bounds__(kSortThreads)
     if (bin[q] < 0) continue;
     const int at = hist[bin[q]] + rank[q];
     B.order[at] = (int)(first + q * kSortThreads);
-    B.where[at] = texel[q];
+    if (B.where) B.where[at] = texel[q];
     if (B.val) put_value<BANDS>(B, at, m[q]);
   }
 }
@@ -492,13 +493,21 @@ constexpr int kTileMaxima = 8;      // per tile: the maxima of levels 0 .. 6
 // levels 0 and 1 are formed from lists: one lane per star merges the texels whose list it
 // heads, then one lane per parent that has a child.  Every texel of the tile in turn ran the
 // FP64 merge for the few lanes of each wave that had anything (230 us a pass, of issue alone).
-// A tile with more stars does that; the values that do not fit are read again.
 constexpr int kStash = 512;
+// Tiles with more stars, or with more than kListed a texel (a merge from a list looks through it
+// once for each of its stars), sort them first, through memory: counts per texel and their
+// prefix sums in LDS, a scatter of the star indices, and each star's rank among the indices of its
+// texel, one lane per star.  The second pass over the tiles counts again and finds the order in
+// memory.  Then a texel's sum is one walk.  All kernels for 10^6 stars, where every
+// texel looked through a list in memory once for each of its stars, and now: 6 x 32^2 229 and 1.1
+// ms, 64^2 19.3 and 0.44; 256^2 589 and 195 us, 512^2 235 and 181, 1024^2 243 and 237; on 2048^2
+// with half of the stars in a cluster of 0.02 rad 46 and 3.0 ms (one CU's work, almost all of it).
+constexpr int kListed = 8;
 
 // PACK: write the tile's stored texels and occupancy bits; otherwise only its levels' maxima
 // and its topmost texel (level tl) for the tail.
 template <bool BANDS, bool PACK>
-__global__ void __launch_bounds__(kTileThreads) k_star_tiles(StarBuild B) {
+__global__ void __launch_bounds__(kTileThreads, 6) k_star_tiles(StarBuild B) {
   using M = Master<BANDS>;
   constexpr int P = M::kN - 2;
   __shared__ int head[1 << (2 * kMaxTileLog)];
@@ -508,6 +517,7 @@ __global__ void __launch_bounds__(kTileThreads) k_star_tiles(StarBuild B) {
   __shared__ short stash_at[kStash], parents[kStash];
   __shared__ unsigned seen[32];           // parents already listed
   __shared__ int own, listed;             // stars of this tile, parents with a child
+  __shared__ int part[kTileThreads / 64];
   __shared__ unsigned word[2 * 64 + 64];  // PACK: occupancy words of levels 0 .. 6
   __shared__ unsigned top[kTileMaxima];
   const int t = threadIdx.x, tl = B.tl, T = 1 << tl, n0 = B.n0;
@@ -546,32 +556,45 @@ __global__ void __launch_bounds__(kTileThreads) k_star_tiles(StarBuild B) {
   if (t < 32) seen[t] = 0u;
   if (t == 0) own = listed = 0;
   __syncthreads();
-  // pick the tile's stars from the bin and list them per texel: star i < kStash in LDS, any
-  // other by its slot in the bin
+  // calls f(slot in the bin, texel of this tile) for the tile's stars, others(star's tile) for the
+  // bin's other stars
   constexpr int kScan = 4;  // loads in flight: a bin holds several tiles' stars
-  for (int q0 = t; q0 < cnt; q0 += kScan * kTileThreads) {
-    uint32_t w[kScan];
+  const auto scan_bin = [&](auto f, auto others) {
+    for (int q0 = t; q0 < cnt; q0 += kScan * kTileThreads) {
+      uint32_t w[kScan];
 #pragma unroll
-    for (int k = 0; k < kScan; ++k) {
-      const int q = q0 + k * kTileThreads;
-      w[k] = B.where[base + min(q, cnt - 1)];
-    }
-#pragma unroll
-    for (int k = 0; k < kScan; ++k) {
-      const int q = q0 + k * kTileThreads;
-      const int lx = (int)(w[k] & 0xffffu) - bx, ly = (int)(w[k] >> 16) - by;
-      if (q >= cnt || (unsigned)lx >= (unsigned)T || (unsigned)ly >= (unsigned)T) continue;
-      const int i = atomicAdd(&own, 1), e = i < kStash ? i : kStash + q, at = ly * T + lx;
-      const int before = atomicExch(&head[at], e);
-      if (i >= kStash) {
-        B.next[base + q] = before;
-        continue;
+      for (int k = 0; k < kScan; ++k) {
+        const int q = base + min(q0 + k * kTileThreads, cnt - 1);
+        w[k] = B.where ? B.where[q]
+                       : bin_texel(place_star<BANDS>(B.dirs, B.inten, B.order[q], n0), bl);
       }
-      stash[i] = value_at<BANDS>(B, base + q);
-      stash_id[i] = B.order[base + q];
-      stash_at[i] = (short)at;
-      stash_next[i] = before;
+#pragma unroll
+      for (int k = 0; k < kScan; ++k) {
+        const int q = q0 + k * kTileThreads;
+        const int x = (int)(w[k] & 0xffffu), y = (int)(w[k] >> 16), lx = x - bx, ly = y - by;
+        if (q >= cnt) continue;
+        if ((unsigned)lx < (unsigned)T && (unsigned)ly < (unsigned)T)
+          f(q, ly * T + lx);
+        else
+          others(((y >> tl) << sub) + (x >> tl));
+      }
     }
+  };
+  const int most = min(kStash, kListed * T * T);  // more stars are sorted
+  if (sub == 0 && cnt > most) {  // a bin of one tile
+    if (t == 0) own = cnt;
+  } else {
+    // pick the tile's stars from the bin and list the first kStash per texel
+    scan_bin(
+        [&](int q, int at) {
+          const int i = atomicAdd(&own, 1);
+          if (i >= kStash) return;
+          stash[i] = value_at<BANDS>(B, base + q);
+          stash_id[i] = B.order[base + q];
+          stash_at[i] = (short)at;
+          stash_next[i] = atomicExch(&head[at], i);
+        },
+        [](int) {});
   }
   __syncthreads();
   if (own == 0) {  // uniform
@@ -595,32 +618,118 @@ __global__ void __launch_bounds__(kTileThreads) k_star_tiles(StarBuild B) {
     }
     return;
   }
-  const auto id_of = [&](int e) { return e < kStash ? stash_id[e] : B.order[base + e - kStash]; };
-  const auto next_of = [&](int e) {
-    return e < kStash ? stash_next[e] : B.next[base + e - kStash];
+  const int mine = own;
+  // Sorts the tile's stars; returns where they are.
+  const auto sort_tile = [&] {
+    __syncthreads();
+    for (int q = t; q < T * T; q += kTileThreads) head[q] = 0;
+    if (t < kTileThreads / 64) part[t] = 0;
+    __syncthreads();
+    // stars per texel, and the stars of the bin's tiles before this one
+    const int number = ((ty & ((1 << sub) - 1)) << sub) + (tx & ((1 << sub) - 1));
+    int before = 0;
+    scan_bin([&](int, int at) { atomicAdd(&head[at], 1); },
+             [&](int tile) { before += tile < number ? 1 : 0; });
+    if (before) atomicAdd(&part[0], before);
+    __syncthreads();
+    const int first = base + part[0];
+    __syncthreads();
+    // prefix sums over runs of texels: starts (ends where the order is known already)
+    const int per = max(1, T * T / kTileThreads), k0 = t * per;
+    int sum = 0;
+    for (int k = 0; k < per; ++k)
+      if (k0 + k < T * T) sum += head[k0 + k];
+    int upto = sum;
+    for (int o = 1; o < 64; o <<= 1) {
+      const int v = __shfl_up(upto, o);
+      if ((t & 63) >= o) upto += v;
+    }
+    if ((t & 63) == 63) part[t >> 6] = upto;
+    __syncthreads();
+    for (int w = 0; w < t >> 6; ++w) upto += part[w];
+    int at = upto - sum;
+    for (int k = 0; k < per; ++k)
+      if (k0 + k < T * T) {
+        const int c = head[k0 + k];
+        head[k0 + k] = PACK ? at + c : at;
+        at += c;
+      }
+    __syncthreads();
+    int* sorted = B.sorted + first;
+    if (PACK) return sorted;
+    int* ids = B.list + first;
+    int* slots = B.val ? B.slots + first : nullptr;
+    scan_bin(
+        [&](int q, int at) {
+          const int p = atomicAdd(&head[at], 1);
+          ids[p] = B.order[base + q];
+          if (slots) slots[p] = q;
+        },
+        [](int) {});
+    __syncthreads();
+    for (int p = t; p < mine; p += kTileThreads) {
+      const int id = ids[p];
+      int lo = 0, hi = T * T - 1;  // the first texel that ends past p
+      while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (head[mid] > p)
+          hi = mid;
+        else
+          lo = mid + 1;
+      }
+      const int a = lo ? head[lo - 1] : 0, b = head[lo];
+      int rank = 0;
+#pragma unroll 8
+      for (int j = a; j < b; ++j) rank += ids[j] < id ? 1 : 0;
+      sorted[a + rank] = slots ? slots[p] : id;
+    }
+    __syncthreads();
+    return sorted;
   };
-  // level-0 texel: its stars in increasing star index
+  // level-0 texel from its list: its stars in increasing star index
   const auto merge = [&](int h) {
     if (h < 0) return no_star<BANDS>();
     Sums<BANDS> sum;
     int last = -1;
     for (;;) {
       int best = 0x7fffffff, at = -1;
-      for (int e = h; e >= 0; e = next_of(e)) {
-        const int id = id_of(e);
+      for (int e = h; e >= 0; e = stash_next[e]) {
+        const int id = stash_id[e];
         if (id > last && id < best) {
           best = id;
           at = e;
         }
       }
       if (at < 0) break;
-      M m;
-      if (at < kStash)
-        m = stash[at];
-      else
-        m = value_at<BANDS>(B, base + at - kStash);
+      const M m = stash[at];
       sum.add(m, (double)m.v[P], (double)m.v[P + 1]);
       last = best;
+    }
+    return sum.texel();
+  };
+  const bool dense = mine > most;
+  const int* sorted = nullptr;
+  if (dense) sorted = sort_tile();
+  // level-0 texel from the sorted stars
+  const auto merge_sorted = [&](int at) {
+    constexpr int kAhead = 4;  // stars whose values are in flight
+    Sums<BANDS> sum;
+    int j = at ? head[at - 1] : 0;
+    const int end = head[at];
+    const auto star = [&](int e) {
+      if (B.val) return value_at<BANDS>(B, base + e);
+      return star_value<BANDS>(B, e, place_star<BANDS>(B.dirs, B.inten, e, n0));
+    };
+    for (; j + kAhead <= end; j += kAhead) {
+      M m[kAhead];
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k) m[k] = star(sorted[j + k]);
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k) sum.add(m[k], (double)m[k].v[P], (double)m[k].v[P + 1]);
+    }
+    for (; j < end; ++j) {
+      const M m = star(sorted[j]);
+      sum.add(m, (double)m.v[P], (double)m.v[P + 1]);
     }
     return sum.texel();
   };
@@ -641,7 +750,7 @@ __global__ void __launch_bounds__(kTileThreads) k_star_tiles(StarBuild B) {
   };
   if (tl == 0) {  // a 1 x 1 face: its texel is also the topmost
     if (t == 0) {
-      const M m = merge(head[0]);
+      const M m = dense ? merge_sorted(0) : merge(head[0]);
       if (PACK) {
         if (store_texel<BANDS>(B.out, texel_at(0, 0, 0), m,
                                1.0f / level_scale(B.maxbits, 0, B.fp16), B.fp16))
@@ -657,8 +766,7 @@ __global__ void __launch_bounds__(kTileThreads) k_star_tiles(StarBuild B) {
   float max0 = 0.0f, max1 = 0.0f;
   const int half = T >> 1;
   const float inv0 = PACK ? 1.0f / level_scale(B.maxbits, 0, B.fp16) : 1.0f;
-  const int mine = own;
-  if (mine <= kStash) {
+  if (!dense) {
     for (int i = t; i < mine; i += kTileThreads) {
       const int at = stash_at[i];
       if (head[at] != i) continue;
@@ -685,22 +793,45 @@ __global__ void __launch_bounds__(kTileThreads) k_star_tiles(StarBuild B) {
         put_pair(0, 0, x, y, texel0(h.x), texel0(h.y), inv0);
       }
     }
-  } else {
-    for (int q = t; q < half * half; q += kTileThreads) {
-      const int x = 2 * (q & (half - 1)), y = 2 * (q >> (tl - 1));
+  } else if (4 * mine < T * T) {
+    // few stars a texel: a lane per parent
+    for (int p = t; p < half * half; p += kTileThreads) {
+      const int x = 2 * (p & (half - 1)), y = 2 * (p >> (tl - 1));
       M c[4];
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        c[k] = merge(head[(y + (k >> 1)) * T + x + (k & 1)]);
+        c[k] = merge_sorted((y + (k >> 1)) * T + x + (k & 1));
         max0 = fmaxf(max0, brightest(c[k]));
       }
       const M m = parent_texel<BANDS>([&](int k) { return c[k]; });
-      mip[q] = m;
+      mip[p] = m;
       max1 = fmaxf(max1, brightest(m));
       if (PACK) {
         put_pair(0, 0, x, y, c[0], c[1], inv0);
         put_pair(0, 0, x, y + 1, c[2], c[3], inv0);
       }
+    }
+  } else {
+    // a lane per texel, the four children of a parent side by side
+    for (int q = t; q < T * T; q += kTileThreads) {
+      const int p = q >> 2, x = 2 * (p & (half - 1)) + (q & 1);
+      const int y = 2 * (p >> (tl - 1)) + ((q >> 1) & 1);
+      const M own_texel = merge_sorted(y * T + x);
+      max0 = fmaxf(max0, brightest(own_texel));
+      const auto child = [&](int k) {
+        M m;
+#pragma unroll
+        for (int i = 0; i < M::kN; ++i) m.v[i] = __shfl(own_texel.v[i], (t & 60) + k);
+        return m;
+      };
+      const M c1 = child(1), c3 = child(3);
+      const M m = parent_texel<BANDS>(
+          [&](int k) { return k == 1 ? c1 : (k == 3 ? c3 : child(k)); });
+      if ((q & 3) == 0) {
+        mip[p] = m;
+        max1 = fmaxf(max1, brightest(m));
+      }
+      if (PACK && !(q & 1)) put_pair(0, 0, x, y, own_texel, (q & 2) ? c3 : c1, inv0);
     }
   }
   if (!PACK) {
@@ -816,11 +947,18 @@ __global__ void __launch_bounds__(kTileThreads) k_star_tail(StarBuild B) {
 // ---- host-side launchers ------------------------------------------------------------------------
 
 // Tiles of 64 texels an edge from 1024 texels a face, else 32: a map of few tiles needs the
-// smaller ones to spread over the chip (6 x 256^2: 384 workgroups instead of 96).
-int star_tile_log(int n0) {
+// smaller ones to spread over the chip (6 x 256^2: 384 workgroups instead of 96).  Smaller still
+// while they hold more than twice kStash on average, which too few workgroups would sort, down to
+// bins of four tiles, each of which looks through its bin.  Splitting to half of kStash
+// instead, so that the lists do, costs more rounds of workgroups than it saves: 10^6 stars on 6 x
+// 256^2 349 against 226 us, on 1024^2 299 against 276.
+int star_tile_log(int n0, int64_t n) {
   int lg = 0;
   while ((2 << lg) <= n0) ++lg;
-  return n0 >= 1024 ? kMaxTileLog : std::min(lg, kMaxTileLog - 1);
+  int tl = n0 >= 1024 ? kMaxTileLog : std::min(lg, kMaxTileLog - 1);
+  const auto tiles = [&](int l) { return (int64_t)6 * (n0 >> l) * (n0 >> l); };
+  while (tl > 0 && n > 2 * kStash * tiles(tl) && tiles(tl - 1) <= 4 * kMaxBins) --tl;
+  return tl;
 }
 
 size_t star_tail_texel_bytes(int bands) {
@@ -829,8 +967,8 @@ size_t star_tail_texel_bytes(int bands) {
 size_t star_tile_max_bytes() { return kTileMaxima * sizeof(float); }
 
 // Bins: one tile each while there are at most kMaxBins of them, else squares of tiles.
-int star_bin_log(int n0) {
-  int bl = star_tile_log(n0);
+int star_bin_log(int n0, int64_t n) {
+  int bl = star_tile_log(n0, n);
   while (6 * (n0 >> bl) * (n0 >> bl) > kMaxBins) ++bl;
   return bl;
 }
@@ -840,7 +978,7 @@ hipError_t launch_star_count(const float* dirs, const float* inten, const float*
                              int n0, int bands, unsigned long long* acc, int* bad, int* count,
                              hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  const int bl = star_bin_log(n0), nb = n0 >> bl;
+  const int bl = star_bin_log(n0, n), nb = n0 >> bl;
   const dim3 grid(blocks_for(n, kSortStars));
   if (bands)
     hipLaunchKernelGGL(k_star_count<true>, grid, dim3(kSortThreads), 0, s, dirs, inten, temp, n,

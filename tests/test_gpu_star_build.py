@@ -100,6 +100,19 @@ def test_star_map_levels_match_numpy(gpu_ctx, n0, n, kind, bands):
     bh.bh_release_stars(h)
 
 
+@pytest.mark.parametrize("n0,n,kind", [
+    (1, 700, "plain"), (2, 3000, "plain"),  # one sorted texel a tile; tiles of one texel
+    (16, 20000, "clustered"),               # texels found again from the stars
+    (32, 60000, "plain"), (64, 20000, "plain"), (64, 300000, "clustered"),
+    (1024, 1000000, "plain"),               # sorted tiles of few stars a texel
+    (2048, 300000, "clustered")])           # bins of several tiles, some sorted
+@pytest.mark.parametrize("bands", [False, True])
+def test_dense_tiles_match_numpy(gpu_ctx, n0, n, kind, bands):
+    """Tiles whose stars are sorted by texel and index before they are merged, among tiles whose
+    stars are listed."""
+    test_star_map_levels_match_numpy(gpu_ctx, n0, n, kind, bands)
+
+
 @pytest.mark.parametrize("n0", [2, 16, 32, 64, 256])
 @pytest.mark.parametrize("fmt", [bh.BH_TEXEL_FP16, bh.BH_TEXEL_FP32])
 def test_every_star_is_found_by_a_frame(gpu_ctx, gpu_tables, orc, orc_tables, n0, fmt):
