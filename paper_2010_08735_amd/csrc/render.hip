@@ -1282,20 +1282,17 @@ __device__ __forceinline__ void render_flat_tile(const ViewDev* __restrict__ vie
                                         (tile / r.tiles_x) * TH);
 }
 
-// Persistent launch over the tiles of many views.  Every wave works on its own: it claims
-// indices from an atomic counter and renders every 8x8 block of the tiles a claim covers,
-// so no claim waits on a barrier and the workgroup shape (4 waves) is the same for every
-// tile configuration.  Claim j < nbig covers claim_tiles consecutive flat tiles (about 16
-// blocks); the last `tail` tiles (one for every fourth wave) go one per claim, so the launch does
-// not end waiting on a few long claims.  The counter is what bounds this form: one address takes an
-// atomic every 17 ns, so the first claim is the wave's own number and takes none, and a longer
-// tail costs more than it evens out (24 uneven views: 4 single claims per wave and a claimed
-// start 1210 us, a numbered start and 1 per wave 905, every fourth wave 865; four 1080p frames
-// 605, 317, 261; claims of 32 blocks 919 and 395).  A wave leaves at its first claim past the last tile; the
-// counter only grows, so every wave reaches that exit.  Held to 7 resident waves per SIMD:
-// the loop over tiles keeps ~14 more vector registers live than one tile does, so at 8
-// waves it would spill; with area code to 5, as the other launches are (at 7 it spilled 46 and
-// four 1599 x 899 nebula views took 1003 us, 727 at 5).  The host sizes the grid to the same.
+// Persistent launch over the tiles of many views.  Every wave works on its own: wave j renders
+// the flat tiles j, j + waves, ..., every 8x8 block of each, so no tile waits on a barrier, the
+// workgroup shape (4 waves) is the same for every tile configuration, and neighbouring tiles,
+// which cost alike, go to different waves.  No wave has more than its share, rounded up, at any
+// size.  Claiming tiles from an atomic counter costs more than it evens out, since one
+// address takes an atomic every 17 ns: claims of 16 blocks with short ones at the end, then in
+// turn, us: 24 uneven views 865 and 862, four 1080p frames 262 and 153, one 176 and 59, one 512 x
+// 512 frame 159 and 40.  Held to 7 resident waves per SIMD: the loop over tiles keeps ~14 more vector
+// registers live than one tile does, so at 8 waves it would spill; with area code to 5, as the
+// other launches are (at 7 it spilled 46 and four 1599 x 899 nebula views took 1003 us, 727 at 5).
+// The host sizes the grid to the same.
 constexpr int kBatchThreads = 256;
 
 template <int FEAT>
@@ -1304,46 +1301,27 @@ constexpr int kBatchWaves = batch_waves(FEAT);
 template <int TW, int TH, int PPT, int FEAT>
 __global__ void __launch_bounds__(kBatchThreads, kBatchWaves<FEAT>)
     k_render_batch(const ViewDev* __restrict__ views, const TileRun* __restrict__ runs,
-                   int nruns, int ntiles, int* __restrict__ counter, TablesDev T, LutDev L) {
+                   int nruns, int ntiles, TablesDev T, LutDev L) {
   using C = TileCfg<TW, TH, 1>;
   constexpr int kBlocks = C::kBX * C::kBY;                // 8x8 blocks per tile
-  constexpr int claim_tiles = kBlocks >= 16 ? 1 : 16 / kBlocks;
   const int lane = threadIdx.x & 63;
   const int q = lane >> 2;
   const int ox = 2 * (q & 3) + (lane & 1), oy = 2 * (q >> 2) + ((lane >> 1) & 1);
   const int waves = (int)(gridDim.x * (kBatchThreads / 64));
-  const int tail = min(ntiles, waves / 4);
-  const int nbig = (ntiles - tail) / claim_tiles;          // tiles [0, claim_tiles nbig)
-  const int first_single = claim_tiles * nbig;
-  // the first claim is the wave's own number, the later ones follow from the counter
-  int j = (int)(blockIdx.x * (kBatchThreads / 64) + threadIdx.x / 64);
-  j = __builtin_amdgcn_readfirstlane(j);
-  for (;;) {
-    int it0, it1;
-    if (j < nbig) {
-      it0 = claim_tiles * j;
-      it1 = it0 + claim_tiles;
-    } else {
-      it0 = first_single + (j - nbig);
-      it1 = it0 + 1;
-    }
-    if (it0 >= ntiles) break;
+  const int first = (int)(blockIdx.x * (kBatchThreads / 64) + threadIdx.x / 64);
 #pragma unroll 1
-    for (int it = it0; it < it1; ++it) {
-      const TileRun r = find_run(runs, nruns, it);
-      const int tile = r.tile0 + (it - r.start);
-      const ViewDev& v = views[r.view];
-      const int tx0 = (tile % r.tiles_x) * TW, ty0 = (tile / r.tiles_x) * TH;
+  for (int it = __builtin_amdgcn_readfirstlane(first); it < ntiles; it += waves) {
+    const TileRun r = find_run(runs, nruns, it);
+    const int tile = r.tile0 + (it - r.start);
+    const ViewDev& v = views[r.view];
+    const int tx0 = (tile % r.tiles_x) * TW, ty0 = (tile / r.tiles_x) * TH;
 #pragma unroll 1
-      for (int blk = 0; blk < kBlocks; ++blk) {
-        const int bx = tx0 + 8 * (blk % C::kBX), by = ty0 + 8 * (blk / C::kBX);
-        if (bx >= v.width || by >= v.height) continue;    // block outside the image
-        render_pixel<false, (FEAT & kFeatParticles) != 0, false, kAreaOf<FEAT>>(
-            v, T, L, bx + ox, by + oy, nullptr);
-      }
+    for (int blk = 0; blk < kBlocks; ++blk) {
+      const int bx = tx0 + 8 * (blk % C::kBX), by = ty0 + 8 * (blk / C::kBX);
+      if (bx >= v.width || by >= v.height) continue;    // block outside the image
+      render_pixel<false, (FEAT & kFeatParticles) != 0, false, kAreaOf<FEAT>>(
+          v, T, L, bx + ox, by + oy, nullptr);
     }
-    if (lane == 0) j = waves + atomicAdd(counter, 1);
-    j = __builtin_amdgcn_readfirstlane(j);                 // lane 0's claim, the wave's
   }
 }
 
@@ -1362,8 +1340,6 @@ __global__ void __launch_bounds__((TW / 8) * (TH / 8) * 64 / PPT, kMinWaves<FEAT
   if (it >= ntiles) return;
   render_flat_tile<TW, TH, PPT, FEAT>(views, runs, nruns, it, T, L);
 }
-
-__global__ void k_reset_counter(int* c) { *c = 0; }
 
 // Measurement variant of the plain launch (16x16 tiles): marks the star-map texels that
 // the footprints visit.
@@ -1417,16 +1393,13 @@ __global__ void __launch_bounds__(256)
 }
 
 // ---- scratch of the allocation-free batched launch -------------------------------------------
-// Device memory of bh_render_batch_noalloc: the persistent form's claim counter (first 256
-// bytes), then up to kNoAllocViews view records and as many tile runs.  A file-scope device
-// array: each GPU the library runs on holds its own copy until the process ends, and every
-// call on that GPU shares it (it keeps the last call's contents; the counter is reset by a
-// kernel before each persistent launch).  In host code `scratch` only names the symbol: its
-// device address comes from scratch_address(), once per device.
+// Device memory of bh_render_batch_noalloc: up to kNoAllocViews view records and as many tile
+// runs.  A file-scope device array: each GPU the library runs on holds its own copy until the
+// process ends, and every call on that GPU shares it (it keeps the last call's contents).  In host
+// code `scratch` only names the symbol: its device address comes from scratch_address(), once per
+// device.
 constexpr int kNoAllocViews = BH_NOALLOC_MAX_VIEWS;
-constexpr size_t kNoAllocHead = 256;
-constexpr size_t kNoAllocBytes =
-    kNoAllocHead + (size_t)kNoAllocViews * (sizeof(ViewDev) + sizeof(TileRun));
+constexpr size_t kNoAllocBytes = (size_t)kNoAllocViews * (sizeof(ViewDev) + sizeof(TileRun));
 static_assert(sizeof(ViewDev) % 16 == 0, "view records keep the tile runs 16-byte aligned");
 static __device__ __align__(256) unsigned char scratch[kNoAllocBytes];
 
@@ -1442,8 +1415,8 @@ struct TileEntry {
   // indexed by the features the views may use: kFeatParticles | kFeatArea | kFeatBands
   // (kFeatBands alone: band star maps without area maps)
   void (*plain[8])(const ViewDev&, const TablesDev&, const LutDev&, hipStream_t);
-  void (*batch[8])(const ViewDev*, const TileRun*, int, int, int*, const TablesDev&,
-                   const LutDev&, int grid, hipStream_t);
+  void (*batch[8])(const ViewDev*, const TileRun*, int, int, const TablesDev&, const LutDev&,
+                   int grid, hipStream_t);
   void (*list[8])(const ViewDev*, const TileRun*, int, int, const TablesDev&, const LutDev&,
                   hipStream_t);
 };
@@ -1458,11 +1431,9 @@ static void launch_plain(const ViewDev& v, const TablesDev& T, const LutDev& L, 
 
 template <int TW, int TH, int PPT, int FEAT>
 static void launch_batch(const ViewDev* views, const TileRun* runs, int nruns, int ntiles,
-                         int* counter, const TablesDev& T, const LutDev& L, int grid,
-                         hipStream_t s) {
-  hipLaunchKernelGGL(k_reset_counter, dim3(1), dim3(1), 0, s, counter);
+                         const TablesDev& T, const LutDev& L, int grid, hipStream_t s) {
   hipLaunchKernelGGL((k_render_batch<TW, TH, PPT, FEAT>), dim3(grid), dim3(kBatchThreads), 0, s,
-                     views, runs, nruns, ntiles, counter, T, L);
+                     views, runs, nruns, ntiles, T, L);
 }
 
 template <int TW, int TH, int PPT, int FEAT>
@@ -1500,15 +1471,15 @@ hipError_t launch_render(int cfg, const ViewDev& v, const TablesDev& T, const Lu
   return hipGetLastError();
 }
 
-// persistent != 0: `grid` persistent workgroups pulling tiles from an atomic counter;
+// persistent != 0: `grid` persistent workgroups, whose waves take the tiles in turn;
 // otherwise one workgroup per tile.
 hipError_t launch_render_batch(int cfg, int persistent, int feat, const ViewDev* views,
-                               const TileRun* runs, int nruns, int ntiles, int* counter,
+                               const TileRun* runs, int nruns, int ntiles,
                                const TablesDev& T, const LutDev& L, int grid, hipStream_t s) {
   if (ntiles <= 0) return hipSuccess;
   const int a = feat & (kFeatParticles | kFeatArea | kFeatBands);
   if (persistent)
-    kTiles[cfg].batch[a](views, runs, nruns, ntiles, counter, T, L, grid, s);
+    kTiles[cfg].batch[a](views, runs, nruns, ntiles, T, L, grid, s);
   else
     kTiles[cfg].list[a](views, runs, nruns, ntiles, T, L, s);
   return hipGetLastError();
