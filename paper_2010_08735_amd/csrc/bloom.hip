@@ -456,10 +456,12 @@ static void up(const float4* in, void* out, const float4* P, const float4* U, co
 
 // Output tiles.  64 x 64 tiles of 16 waves read the least around each tile, but a small image
 // has too few of them to fill the chip: below kUpFewTiles (about 960 x 540) 32 x 32 tiles of 8
-// waves (640 x 360 display: 11.4 against 13.3 us; 1280 x 720: 21.1 against 18.4).  With the
-// encoding's arithmetic, images of many rounds of workgroups overlap better in small ones: 7680 x
-// 4320 display 289 us in 32 x 32 tiles of 4 waves, 305 in 64 x 64; 3840 x 2160 85 against 83.
-constexpr int kUpFewTiles = 128, kUpManyTiles = 4096;
+// waves (640 x 360 display: 11.4 against 13.3 us; 1280 x 720: 17.4 against 14.7).  With the
+// encoding's arithmetic, images of more than one round of workgroups (two 64 x 64 tiles reside on
+// a CU) overlap better in small ones, 32 x 32 of 4 waves: display, us, small against large: 1920 x
+// 1080 (510 tiles) 26.6 and 23.7, 1920 x 1200 (570) 29.7 and 30.1, 2560 x 1440 38.3 and 40.2, 3840 x
+// 2160 70.9 and 73.4 (3839 x 2158 78.5 and 77.2), 5120 x 2880 124 and 131, 7680 x 4320 280 and 295.
+constexpr int kUpFewTiles = 128, kUpManyTiles = 512;
 
 static hipError_t launch_bloom_up(const float4* in, void* out, const float4* P, const float4* U,
                                   const BloomDev& B, bool display, float exposure,

@@ -33,3 +33,9 @@ def test_fused_display_equals_encoded_linear(gpu_ctx, orc, w, h, levels):
                         np.asarray(wt, np.float32).astype(np.float64))
         # ~4 roundings of 2^-24 a level on sums of non-negative terms
         assert np.abs(lin.cpu().numpy() - ref).max() <= 4 * (levels + 1) * 2.0 ** -23 * ref.max()
+
+
+@pytest.mark.parametrize("w,h,levels", [(2047, 1024, 7), (2049, 1024, 7), (1937, 1087, 8)])
+def test_around_one_round_of_workgroups(gpu_ctx, orc, w, h, levels):
+    """512 and 528 tiles of 64 x 64: the line between the display shapes."""
+    test_fused_display_equals_encoded_linear(gpu_ctx, orc, w, h, levels)
