@@ -20,6 +20,8 @@
 //               level such that the extended footprint spans at most 9x9 texels,
 //               tent-weighted gather f(w) f(h), lensing factor Omega/Omega', one Doppler
 //               shift per pixel.
+#include <type_traits>
+
 #include "bh_dev.h"
 
 #include "bh_probes.h"
@@ -769,8 +771,8 @@ __device__ __forceinline__ float3 cshift_lookup(const float4* __restrict__ tab, 
                      __builtin_amdgcn_exp2f(e.z));
 }
 
-// The view record of a kernel that takes it as its first argument, to be read again from the
-// argument segment where it is used: fields kept since the kernel's start would hold scalar
+// The view record of a kernel that takes it as its first argument (launch_plain checks that it
+// does), to be read again from the argument segment where it is used: fields kept since the kernel's start would hold scalar
 // registers across the whole trace (8 to 28 of them spilled into vector registers, and two of
 // those to memory; without: 1080p frame 29.0 -> 28.0 us, 8K 324 -> 307, animated 52.5 -> 49.4).
 __device__ __forceinline__ const ViewDev& reread(const ViewDev&) {
@@ -785,6 +787,7 @@ __device__ __forceinline__ const ViewDev& reread(const ViewDev&) {
 // requests (measurement only, see CountBufs).  ANIM: views may have a particle disc
 // (retarded times).
 // MARCH: ray marching (march_ray) in place of TraceRay; no tables are read.
+// LATE: the view is the kernel's first argument (reread).
 template <bool COUNT, bool ANIM = false, bool MARCH = false, int AREA = 0, bool LATE = false>
 __device__ __forceinline__ void render_pixel(const ViewDev& v0, const TablesDev& T,
                                              const LutDev& L, int px, int py,
@@ -1365,9 +1368,19 @@ struct TileEntry {
                   hipStream_t);
 };
 
+template <class Kernel>
+struct FirstArgument;
+template <class A, class... Rest>
+struct FirstArgument<void (*)(A, Rest...)> {
+  using type = A;
+};
+
 template <int TW, int TH, int PPT, int FEAT>
 static void launch_plain(const ViewDev& v, const TablesDev& T, const LutDev& L, hipStream_t s) {
   using C = TileCfg<TW, TH, PPT>;
+  using Kernel = decltype(&k_render<TW, TH, PPT, FEAT>);
+  static_assert(std::is_same<typename FirstArgument<Kernel>::type, ViewDev>::value,
+                "k_render reads its view again at the start of its arguments");
   int tiles_x = (v.width + TW - 1) / TW, tiles_y = (v.height + TH - 1) / TH;
   hipLaunchKernelGGL((k_render<TW, TH, PPT, FEAT>), dim3(xcd_grid(tiles_x, tiles_y)),
                      dim3(C::kThreads), 0, s, v, T, L, tiles_x, tiles_y);
