@@ -57,3 +57,44 @@ def test_image_is_the_same_with_and_without_the_pixel_record(gpu_ctx, gpu_tables
             assert np.array_equal(with_record, without)
     finally:
         bh.bh_release_area(h)
+
+
+@pytest.mark.parametrize("bands", [False, True])
+def test_largest_map_reads_its_own_texels(gpu_ctx, gpu_tables, bands):
+    """The largest area map (2 GiB with band colours, byte offsets to the end of 32 bits).  Bilinear
+    reads and box-filtered levels reproduce a field that is linear on each face, so its frame is
+    the 256 x 256 map's of the same field: to 2^-24 of the texel count in the position, times the
+    field's slope of a texel, and the roundings of some ten products (1e-6), except where a
+    footprint reaches the outermost half texels of a face of either map (1 pixel in 30)."""
+    import torch
+
+    def build(n0):
+        c = (torch.arange(n0, device="cuda", dtype=torch.float64) + 0.5) * (2.0 / n0) - 1.0
+        f = torch.arange(6, device="cuda", dtype=torch.float64)
+        I = (2.0 + 0.3 * f[:, None, None] + 0.5 * c[None, None, :] + 0.25 * c[None, :, None])
+        I = I.float()
+        if bands:
+            tex = torch.stack([I, 0.5 * I, 0.25 * I, torch.zeros_like(I)], -1).contiguous()
+        else:
+            tex = torch.stack([I, torch.full_like(I, 6000.0)], -1).contiguous()
+        del I
+        make = bh.bh_build_area_bands if bands else bh.bh_build_area
+        h = make(gpu_ctx, tex.data_ptr(), n0, bh.current_stream())
+        torch.cuda.synchronize()
+        return h
+
+    small, large = build(256), build(4096)
+    try:
+        for aim in ((0.4, 0.7), (1.6, 2.4), (2.7, 4.5)):
+            v = scenes.small_static_view()
+            v.width, v.height, v.fov_y, v.disc_opacity, v.k_area = 201, 163, 2.0, 0.0, 1.0
+            v.cam_rot = scenes.look_rotation(scenes.spherical_position(1.0, *aim))
+            a, b = (parity.render_gpu(gpu_ctx, gpu_tables, v, None, aov=False, area=h)[0]
+                    for h in (small, large))
+            r = np.abs(a - b)[..., :3].max(-1) / np.maximum(a[..., :3].max(-1), 1e-3)
+            assert (a[..., :3].max(-1) > 0).mean() > 0.5
+            assert np.percentile(r, 97) < 1e-5, float(np.percentile(r, 97))
+    finally:
+        bh.bh_release_area(small)
+        bh.bh_release_area(large)
+        bh.bh_trim(gpu_ctx)
