@@ -317,7 +317,8 @@ struct PointU {
 __device__ __forceinline__ PointU columns_U(const TablesDev& T, float e2, float e) {
   float x = fdiv(1.0f, 1.0f + 6.0f * e2);
   // (1 + 6 e^3) / (1 + e^2) written so that it cannot overflow for nearly radial rays
-  return PointU{clampf(x * T.u_last, 0.0f, T.u_last * kBelowOne), 6.0f * e + fdiv(1.0f - 6.0f * e, 1.0f + e2)};
+  return PointU{clampf(x * T.u_last, 0.0f, T.u_last * kBelowOne),
+                6.0f * e + fdiv(1.0f - 6.0f * e, 1.0f + e2)};
 }
 __device__ __forceinline__ TablePoint point_U(const TablesDev& T, const PointU& c, float phi) {
   float y = phi * (1.0f / 3.0f) * c.row;

@@ -214,7 +214,7 @@ __global__ void __launch_bounds__(256)
   }
 }
 
-// ---- the U chain and the output, per T x T output tile -------------------------------------------
+// ---- the U chain and the output, per T x T output tile ------------------------------------------
 //
 // A 64 x 64 tile reads level-1 pixels 32 t - 1 .. 32 t + 32 (34 per axis), level-2 pixels 18 per
 // axis, then 10, 6, 4 and 3 at level 6.  Levels 2 .. 6 together are 485 pixels, so each thread
@@ -459,8 +459,9 @@ static void up(const float4* in, void* out, const float4* P, const float4* U, co
 // waves (640 x 360 display: 11.4 against 13.3 us; 1280 x 720: 17.4 against 14.7).  With the
 // encoding's arithmetic, images of more than one round of workgroups (two 64 x 64 tiles reside on
 // a CU) overlap better in small ones, 32 x 32 of 4 waves: display, us, small against large: 1920 x
-// 1080 (510 tiles) 26.6 and 23.7, 1920 x 1200 (570) 29.7 and 30.1, 2560 x 1440 38.3 and 40.2, 3840 x
-// 2160 70.9 and 73.4 (3839 x 2158 78.5 and 77.2), 5120 x 2880 124 and 131, 7680 x 4320 280 and 295.
+// 1080 (510 tiles) 26.6 and 23.7, 1920 x 1200 (570) 29.7 and 30.1, 2560 x 1440 38.3 and 40.2, 3840
+// x 2160 70.9 and 73.4 (3839 x 2158 78.5 and 77.2), 5120 x 2880 124 and 131, 7680 x 4320 280 and
+// 295.
 constexpr int kUpFewTiles = 128, kUpManyTiles = 512;
 
 static hipError_t launch_bloom_up(const float4* in, void* out, const float4* P, const float4* U,

@@ -595,7 +595,8 @@ __device__ __forceinline__ void area_add(const AreaQuad<BANDS>& q, float weight,
   const float wb = q.fx * y0, we = q.fx * y1, wa = y0 - wb, wc = y1 - we;
   s.x = fmaf(we, q.e.x, fmaf(wc, q.c.x, fmaf(wb, q.b.x, fmaf(wa, q.a.x, s.x))));
   s.y = fmaf(we, q.e.y, fmaf(wc, q.c.y, fmaf(wb, q.b.y, fmaf(wa, q.a.y, s.y))));
-  if constexpr (BANDS) s.z = fmaf(we, q.e.z, fmaf(wc, q.c.z, fmaf(wb, q.b.z, fmaf(wa, q.a.z, s.z))));
+  if constexpr (BANDS)
+    s.z = fmaf(we, q.e.z, fmaf(wc, q.c.z, fmaf(wb, q.b.z, fmaf(wa, q.a.z, s.z))));
 }
 
 // The footprint of d' on the face of its centre, shared by the star gather and the area filter:
@@ -772,8 +773,8 @@ __device__ __forceinline__ float3 cshift_lookup(const float4* __restrict__ tab, 
 }
 
 // The view record of a kernel that takes it as its first argument (launch_plain checks that it
-// does), to be read again from the argument segment where it is used: fields kept since the kernel's start would hold scalar
-// registers across the whole trace (8 to 28 of them spilled into vector registers, and two of
+// does), to be read again from the argument segment where it is used: fields kept since the
+// kernel's start would hold scalar registers across the whole trace (8 to 28 of them spilled into vector registers, and two of
 // those to memory; without: 1080p frame 29.0 -> 28.0 us, 8K 324 -> 307, animated 52.5 -> 49.4).
 __device__ __forceinline__ const ViewDev& reread(const ViewDev&) {
   typedef const __attribute__((address_space(4))) ViewDev* Args;
@@ -921,172 +922,171 @@ __device__ __forceinline__ void render_pixel(const ViewDev& v0, const TablesDev&
   int mip = 255;
   const ViewDev& w = LATE ? reread(v0) : v0;
   if (COUNT || w.aov || __ballot(trans > 0.0f && !captured) != 0ull) {
-  // ---- stars (Sections 3.3.2, 3.4.1)
-  // hardware sine and cosine (argument in turns): the escape direction only places star
-  // light, where their ~1e-6 rad error is a thousandth of a pixel
-  const float turns = tr.dprime * 0.159154943091895336f;
-  const float sdp = __builtin_amdgcn_sinf(turns), cdp = __builtin_amdgcn_cosf(turns);
-  float dp0 = captured ? 0.0f : cdp * w.rhat[0] + sdp * ey0;
-  float dp1 = captured ? 0.0f : cdp * w.rhat[1] + sdp * ey1;
-  float dp2 = captured ? 0.0f : cdp * w.rhat[2] + sdp * ey2;
-  int cap = captured ? 1 : 0;
-  cap |= __builtin_amdgcn_mov_dpp(cap, 0xB1, 0xF, 0xF, true);
-  cap |= __builtin_amdgcn_mov_dpp(cap, 0x4E, 0xF, 0xF, true);
-  float dw0 = quad_diff<1>(dp0), dw1 = quad_diff<1>(dp1), dw2 = quad_diff<1>(dp2);
-  float dh0 = quad_diff<2>(dp0), dh1 = quad_diff<2>(dp1), dh2 = quad_diff<2>(dp2);
-  if (cap) bits |= BH_STAR_ZEROED_BIT;
-  ShiftPlane sp{0, 0.0f};
-  if constexpr (AREA >= 2) sp = cshift_plane(dcam);
-  if (w.has_stars && !cap) {
-    const StarsDev& S = w.stars;
-    const FaceFootprint ff = face_footprint(dp0, dp1, dp2, dw0, dw1, dw2, dh0, dh1, dh2);
-    const float U = ff.U, V = ff.V;
-    const float J00 = ff.J00, J01 = ff.J01, J10 = ff.J10, J11 = ff.J11;
-    const int face = ff.c.face;
-    float hu = fabsf(J00) + fabsf(J01), hv = fabsf(J10) + fabsf(J11);
-    float E0 = fmaxf(hu, hv) * (float)S.n0;
-    // smallest level with E0 / 2^L <= 8: from the exponent and mantissa of E0 / 8
-    int Lv = 0;
-    {
-      float q = E0 * 0.125f;
-      if (q > 1.0f) {
-        unsigned b = __float_as_uint(q);
-        int ex = (int)((b >> 23) & 255u) - 127;   // q = 1.m * 2^ex, q finite and > 1
-        Lv = ex + ((b & 0x7fffffu) != 0u ? 1 : 0);
-      }
-      if (!(q <= 3.0e38f)) Lv = S.levels - 1;      // infinite or NaN footprint
-      Lv = min(Lv, S.levels - 1);
-    }
-    mip = Lv;
-    float det = J00 * J11 - J01 * J10;
-    // band-colour star maps are read only by the band variants (AREA 2 and 3)
-    const bool bands = AREA >= 2 && S.bands;
-    float A = 0.0f, B = 0.0f, Cb = 0.0f;
-    // behind an opaque disc crossing (transmittance exactly 0) the stars add nothing: their
-    // light is scaled by trans below, so the gather is skipped (the level above is kept)
-    if (fabsf(det) >= 1e-20f && trans > 0.0f) {
-      float idet = fdiv(1.0f, det);
-      Footprint F;
-      // inverse face Jacobian
-      const float i00 = J11 * idet, i01 = -J01 * idet, i10 = -J10 * idet, i11 = J00 * idet;
-      const int nL = S.n0 >> Lv;
-      const float fn = (float)nL;
-      // clamp before the integer conversion (equal to floor-then-clamp for in-range values)
-      const float top = fn - 1.0f;
-      int x0 = (int)clampf(0.5f * (U - hu + 1.0f) * fn, 0.0f, top);
-      int x1 = (int)clampf(0.5f * (U + hu + 1.0f) * fn, 0.0f, top);
-      int y0 = (int)clampf(0.5f * (V - hv + 1.0f) * fn, 0.0f, top);
-      int y1 = (int)clampf(0.5f * (V + hv + 1.0f) * fn, 0.0f, top);
-      x1 = min(x1, x0 + 8);
-      y1 = min(y1, y0 + 8);
-      F.nL = nL;
-      const int wpr = ((nL + 31) >> 5) + 1;
-      F.wpr4 = 4 * wpr;
-      F.sh = x0 & 31;
-      F.ny = y1 - y0;
-      F.span = (1u << (x1 - x0 + 1)) - 1u;  // x1 - x0 <= 8
-      F.texel0 = S.level_off[Lv] + ((uint32_t)face * (uint32_t)nL + (uint32_t)y0) * (uint32_t)nL +
-                 (uint32_t)x0;
-      F.occ = S.occ + S.occ_off[Lv] +
-              2u * (((uint32_t)face * (uint32_t)nL + (uint32_t)y0) * (uint32_t)wpr +
-                    (uint32_t)(x0 >> 5));
-      // a level-L texel is tw = 2 / nL wide in face coordinates; the corner (x0, y0) lies at
-      // (cu, cv) from the centre direction (U, V)
-      const float tw = __builtin_ldexpf(S.tw0, Lv);  // nL = n0 / 2^L: 2 / nL exactly
-      const float cu = (float)x0 * tw - 1.0f - U, cv = (float)y0 * tw - 1.0f - V;
-      F.Wc = i00 * tw;
-      F.Wr = i01 * tw;
-      F.W0 = fmaf(i00, cu, i01 * cv);
-      F.Hc = i10 * tw;
-      F.Hr = i11 * tw;
-      F.H0 = fmaf(i10, cu, i11 * cv);
-      F.one = S.one;
-      if (COUNT) req += 12;  // level offsets and scale
-      if constexpr (AREA >= 2) {
-        if (bands) {
-          if (S.fp16)
-            gather<kTexBand16, COUNT, false>(S.tex, F, cnt, req, A, B, Cb);
-          else
-            gather<kTexBand32, COUNT, false>(S.tex, F, cnt, req, A, B, Cb);
+    // ---- stars (Sections 3.3.2, 3.4.1)
+    // hardware sine and cosine (argument in turns): the escape direction only places star
+    // light, where their ~1e-6 rad error is a thousandth of a pixel
+    const float turns = tr.dprime * 0.159154943091895336f;
+    const float sdp = __builtin_amdgcn_sinf(turns), cdp = __builtin_amdgcn_cosf(turns);
+    float dp0 = captured ? 0.0f : cdp * w.rhat[0] + sdp * ey0;
+    float dp1 = captured ? 0.0f : cdp * w.rhat[1] + sdp * ey1;
+    float dp2 = captured ? 0.0f : cdp * w.rhat[2] + sdp * ey2;
+    int cap = captured ? 1 : 0;
+    cap |= __builtin_amdgcn_mov_dpp(cap, 0xB1, 0xF, 0xF, true);
+    cap |= __builtin_amdgcn_mov_dpp(cap, 0x4E, 0xF, 0xF, true);
+    float dw0 = quad_diff<1>(dp0), dw1 = quad_diff<1>(dp1), dw2 = quad_diff<1>(dp2);
+    float dh0 = quad_diff<2>(dp0), dh1 = quad_diff<2>(dp1), dh2 = quad_diff<2>(dp2);
+    if (cap) bits |= BH_STAR_ZEROED_BIT;
+    ShiftPlane sp{0, 0.0f};
+    if constexpr (AREA >= 2) sp = cshift_plane(dcam);
+    if (w.has_stars && !cap) {
+      const StarsDev& S = w.stars;
+      const FaceFootprint ff = face_footprint(dp0, dp1, dp2, dw0, dw1, dw2, dh0, dh1, dh2);
+      const float U = ff.U, V = ff.V;
+      const float J00 = ff.J00, J01 = ff.J01, J10 = ff.J10, J11 = ff.J11;
+      const int face = ff.c.face;
+      float hu = fabsf(J00) + fabsf(J01), hv = fabsf(J10) + fabsf(J11);
+      float E0 = fmaxf(hu, hv) * (float)S.n0;
+      // smallest level with E0 / 2^L <= 8: from the exponent and mantissa of E0 / 8
+      int Lv = 0;
+      {
+        float q = E0 * 0.125f;
+        if (q > 1.0f) {
+          unsigned b = __float_as_uint(q);
+          int ex = (int)((b >> 23) & 255u) - 127;   // q = 1.m * 2^ex, q finite and > 1
+          Lv = ex + ((b & 0x7fffffu) != 0u ? 1 : 0);
         }
+        if (!(q <= 3.0e38f)) Lv = S.levels - 1;      // infinite or NaN footprint
+        Lv = min(Lv, S.levels - 1);
       }
-      if (!bands) {
-        if (S.fp16)
-          gather<kTexIT16, COUNT, AREA != 3>(S.tex, F, cnt, req, A, B, Cb);
-        else
-          gather<kTexIT32, COUNT, AREA != 3>(S.tex, F, cnt, req, A, B, Cb);
+      mip = Lv;
+      float det = J00 * J11 - J01 * J10;
+      // band-colour star maps are read only by the band variants (AREA 2 and 3)
+      const bool bands = AREA >= 2 && S.bands;
+      float A = 0.0f, B = 0.0f, Cb = 0.0f;
+      // behind an opaque disc crossing (transmittance exactly 0) the stars add nothing: their
+      // light is scaled by trans below, so the gather is skipped (the level above is kept)
+      if (fabsf(det) >= 1e-20f && trans > 0.0f) {
+        float idet = fdiv(1.0f, det);
+        Footprint F;
+        // inverse face Jacobian
+        const float i00 = J11 * idet, i01 = -J01 * idet, i10 = -J10 * idet, i11 = J00 * idet;
+        const int nL = S.n0 >> Lv;
+        const float fn = (float)nL;
+        // clamp before the integer conversion (equal to floor-then-clamp for in-range values)
+        const float top = fn - 1.0f;
+        int x0 = (int)clampf(0.5f * (U - hu + 1.0f) * fn, 0.0f, top);
+        int x1 = (int)clampf(0.5f * (U + hu + 1.0f) * fn, 0.0f, top);
+        int y0 = (int)clampf(0.5f * (V - hv + 1.0f) * fn, 0.0f, top);
+        int y1 = (int)clampf(0.5f * (V + hv + 1.0f) * fn, 0.0f, top);
+        x1 = min(x1, x0 + 8);
+        y1 = min(y1, y0 + 8);
+        F.nL = nL;
+        const int wpr = ((nL + 31) >> 5) + 1;
+        F.wpr4 = 4 * wpr;
+        F.sh = x0 & 31;
+        F.ny = y1 - y0;
+        F.span = (1u << (x1 - x0 + 1)) - 1u;  // x1 - x0 <= 8
+        F.texel0 = S.level_off[Lv] + ((uint32_t)face * (uint32_t)nL + (uint32_t)y0) * (uint32_t)nL +
+                   (uint32_t)x0;
+        F.occ = S.occ + S.occ_off[Lv] +
+                2u * (((uint32_t)face * (uint32_t)nL + (uint32_t)y0) * (uint32_t)wpr +
+                      (uint32_t)(x0 >> 5));
+        // a level-L texel is tw = 2 / nL wide in face coordinates; the corner (x0, y0) lies at
+        // (cu, cv) from the centre direction (U, V)
+        const float tw = __builtin_ldexpf(S.tw0, Lv);  // nL = n0 / 2^L: 2 / nL exactly
+        const float cu = (float)x0 * tw - 1.0f - U, cv = (float)y0 * tw - 1.0f - V;
+        F.Wc = i00 * tw;
+        F.Wr = i01 * tw;
+        F.W0 = fmaf(i00, cu, i01 * cv);
+        F.Hc = i10 * tw;
+        F.Hr = i11 * tw;
+        F.H0 = fmaf(i10, cu, i11 * cv);
+        F.one = S.one;
+        if (COUNT) req += 12;  // level offsets and scale
+        if constexpr (AREA >= 2) {
+          if (bands) {
+            if (S.fp16)
+              gather<kTexBand16, COUNT, false>(S.tex, F, cnt, req, A, B, Cb);
+            else
+              gather<kTexBand32, COUNT, false>(S.tex, F, cnt, req, A, B, Cb);
+          }
+        }
+        if (!bands) {
+          if (S.fp16)
+            gather<kTexIT16, COUNT, AREA != 3>(S.tex, F, cnt, req, A, B, Cb);
+          else
+            gather<kTexIT32, COUNT, AREA != 3>(S.tex, F, cnt, req, A, B, Cb);
+        }
+        const float iscale = S.scale[Lv];
+        A *= iscale;
+        B *= S.fp16 && !bands ? iscale * 1024.0f : iscale;
+        Cb *= iscale;
       }
-      const float iscale = S.scale[Lv];
-      A *= iscale;
-      B *= S.fp16 && !bands ? iscale * 1024.0f : iscale;
-      Cb *= iscale;
-    }
-    float cdx = dw1 * dh2 - dw2 * dh1, cdy = dw2 * dh0 - dw0 * dh2, cdz = dw0 * dh1 - dw1 * dh0;
-    // Omega / Omega' = |q_w x q_h| / |d'_w x d'_h| with the same quad differences of the
-    // camera-frame direction q = (q^w, q^h, -f) inq.  The row partner shares q^h and the
-    // column partner q^w, so with a = quad difference of inq along the row and b along the
-    // column, q_w = (dq0, q^h a, -f a) and q_h = (q^w b, dq1, -f b), whose cross product is
-    // (f a (dq1 - q^h b), f b (dq0 - q^w a), dq0 dq1 - q^w q^h a b).
-    const float qa = quad_diff<1>(inq), qb = quad_diff<2>(inq);
-    const float dq0 = quad_diff<1>(q0), dq1 = quad_diff<2>(q1);
-    const float cq0 = w.f * qa * (dq1 - qh * qb), cq1 = w.f * qb * (dq0 - qw * qa);
-    const float cq2 = dq0 * dq1 - (qw * qh) * (qa * qb);
-    const float om2 = cq0 * cq0 + cq1 * cq1 + cq2 * cq2;
-    const float omp2 = cdx * cdx + cdy * cdy + cdz * cdz;
-    if (bands) {
-      // light of any colour: band sum and chromaticity, shifted by C(r, g, D_cam)
-      const float Ssum = A + B + Cb;
-      if (Ssum > 0.0f && omp2 > 0.0f) {
-        const float iS = fdiv(1.0f, Ssum);
-        const float3 C = cshift_lookup(S.ctab, A * iS, B * iS, sp);
-        const float sc = trans * w.k_star * fsqrt(om2) * __builtin_amdgcn_rsqf(omp2) * Ssum;
-        cr += sc * C.x;
-        cg += sc * C.y;
-        cb += sc * C.z;
-      }
-    } else if (A > 0.0f && omp2 > 0.0f) {
-      float Tpix = fdiv(B, A);
-      float4 Lr = band_lookup(L, dcam * Tpix);
-      float4 Ln = band_lookup(L, Tpix);
-      if (COUNT) req += 64;
-      float sc = trans * w.k_star * fsqrt(om2) * __builtin_amdgcn_rsqf(omp2) * fdiv(A, Ln.w);
-      cr += sc * Lr.x;
-      cg += sc * Lr.y;
-      cb += sc * Lr.z;
-    }
-  }
-
-
-  // ---- area sources: the footprint's mean radiance, one Doppler shift per pixel as for
-  // stars, no lensing amplification (Section 3.4.1).  The face footprint is formed again: kept
-  // across the star gather it would spill.
-  if ((AREA == 1 || AREA == 2) && w.area.tex && !cap && trans > 0.0f) {
-    const FaceFootprint ff = face_footprint(dp0, dp1, dp2, dw0, dw1, dw2, dh0, dh1, dh2);
-    float A, B, Cc;
-    if (AREA == 2 && w.area.bands) {
-      // light of any colour: band sum S and chromaticity (r, g), shifted by C(r, g, D_cam)
-      area_filter<true, false>(w.area, ff, A, B, Cc);
-      const float S = A + B + Cc;
-      if (S > 0.0f) {
-        const float iS = fdiv(1.0f, S);
-        const float3 C = cshift_lookup(w.area.ctab, A * iS, B * iS, sp);
-        const float sc = trans * w.area.k_area * S;
-        cr += sc * C.x;
-        cg += sc * C.y;
-        cb += sc * C.z;
-      }
-    } else {
-      area_filter<false, AREA == 1>(w.area, ff, A, B, Cc);
-      if (A > 0.0f) {
-        const float Tpix = fdiv(B, A);
-        const float4 Lr = band_lookup(L, dcam * Tpix), Ln = band_lookup(L, Tpix);
-        const float sc = trans * w.area.k_area * fdiv(A, Ln.w);
+      float cdx = dw1 * dh2 - dw2 * dh1, cdy = dw2 * dh0 - dw0 * dh2, cdz = dw0 * dh1 - dw1 * dh0;
+      // Omega / Omega' = |q_w x q_h| / |d'_w x d'_h| with the same quad differences of the
+      // camera-frame direction q = (q^w, q^h, -f) inq.  The row partner shares q^h and the
+      // column partner q^w, so with a = quad difference of inq along the row and b along the
+      // column, q_w = (dq0, q^h a, -f a) and q_h = (q^w b, dq1, -f b), whose cross product is
+      // (f a (dq1 - q^h b), f b (dq0 - q^w a), dq0 dq1 - q^w q^h a b).
+      const float qa = quad_diff<1>(inq), qb = quad_diff<2>(inq);
+      const float dq0 = quad_diff<1>(q0), dq1 = quad_diff<2>(q1);
+      const float cq0 = w.f * qa * (dq1 - qh * qb), cq1 = w.f * qb * (dq0 - qw * qa);
+      const float cq2 = dq0 * dq1 - (qw * qh) * (qa * qb);
+      const float om2 = cq0 * cq0 + cq1 * cq1 + cq2 * cq2;
+      const float omp2 = cdx * cdx + cdy * cdy + cdz * cdz;
+      if (bands) {
+        // light of any colour: band sum and chromaticity, shifted by C(r, g, D_cam)
+        const float Ssum = A + B + Cb;
+        if (Ssum > 0.0f && omp2 > 0.0f) {
+          const float iS = fdiv(1.0f, Ssum);
+          const float3 C = cshift_lookup(S.ctab, A * iS, B * iS, sp);
+          const float sc = trans * w.k_star * fsqrt(om2) * __builtin_amdgcn_rsqf(omp2) * Ssum;
+          cr += sc * C.x;
+          cg += sc * C.y;
+          cb += sc * C.z;
+        }
+      } else if (A > 0.0f && omp2 > 0.0f) {
+        float Tpix = fdiv(B, A);
+        float4 Lr = band_lookup(L, dcam * Tpix);
+        float4 Ln = band_lookup(L, Tpix);
+        if (COUNT) req += 64;
+        float sc = trans * w.k_star * fsqrt(om2) * __builtin_amdgcn_rsqf(omp2) * fdiv(A, Ln.w);
         cr += sc * Lr.x;
         cg += sc * Lr.y;
         cb += sc * Lr.z;
       }
     }
-  }
+
+    // ---- area sources: the footprint's mean radiance, one Doppler shift per pixel as for
+    // stars, no lensing amplification (Section 3.4.1).  The face footprint is formed again: kept
+    // across the star gather it would spill.
+    if ((AREA == 1 || AREA == 2) && w.area.tex && !cap && trans > 0.0f) {
+      const FaceFootprint ff = face_footprint(dp0, dp1, dp2, dw0, dw1, dw2, dh0, dh1, dh2);
+      float A, B, Cc;
+      if (AREA == 2 && w.area.bands) {
+        // light of any colour: band sum S and chromaticity (r, g), shifted by C(r, g, D_cam)
+        area_filter<true, false>(w.area, ff, A, B, Cc);
+        const float S = A + B + Cc;
+        if (S > 0.0f) {
+          const float iS = fdiv(1.0f, S);
+          const float3 C = cshift_lookup(w.area.ctab, A * iS, B * iS, sp);
+          const float sc = trans * w.area.k_area * S;
+          cr += sc * C.x;
+          cg += sc * C.y;
+          cb += sc * C.z;
+        }
+      } else {
+        area_filter<false, AREA == 1>(w.area, ff, A, B, Cc);
+        if (A > 0.0f) {
+          const float Tpix = fdiv(B, A);
+          const float4 Lr = band_lookup(L, dcam * Tpix), Ln = band_lookup(L, Tpix);
+          const float sc = trans * w.area.k_area * fdiv(A, Ln.w);
+          cr += sc * Lr.x;
+          cg += sc * Lr.y;
+          cb += sc * Lr.z;
+        }
+      }
+    }
   }
 
   if (COUNT) {
@@ -1159,8 +1159,10 @@ static inline int xcd_grid(int tiles_x, int tiles_y) {
 // Resident waves per SIMD the one-launch and per-tile kernels are held to (the register
 // budget the compiler keeps to): 8, and 5 for the area-source variants, whose probe loop
 // spilled 20 vector registers at 8 waves and 9 at 6 (nebula frame 1599 x 899: 43.5 us at 6 waves,
-// 42.4 at 5, one probe in flight; at 7 waves 48.5, and the any-colour frame 139 us for 109).  Band
-// star maps without area maps fit 8 (64 VGPRs).
+// 42.4 at 5, one probe in flight; two in flight 38.9 and 33.7, 4K 97.2 and 99.2; at 7 waves 48.5,
+// and the any-colour frame 139 us for 109).  With particles too: 64.6 us at 6 waves and 59.8 at 5
+// at 1599 x 899, 75.8 and 76.6 at 1080p, 205 and 222 at 4K.  Band star maps without area maps fit
+// 8 (64 VGPRs).
 template <int FEAT>
 constexpr int kMinWaves = (FEAT & kFeatArea) ? 5 : 8;
 
@@ -1236,10 +1238,10 @@ __device__ __forceinline__ void render_flat_tile(const ViewDev* __restrict__ vie
 // size.  Claiming tiles from an atomic counter costs more than it evens out, since one
 // address takes an atomic every 17 ns: claims of 16 blocks with short ones at the end, then in
 // turn, us: 24 uneven views 865 and 862, four 1080p frames 262 and 153, one 176 and 59, one 512 x
-// 512 frame 159 and 40.  Held to 7 resident waves per SIMD: the loop over tiles keeps ~14 more vector
-// registers live than one tile does, so at 8 waves it would spill; with area code to 5, as the
-// other launches are (at 7 it spilled 46 and four 1599 x 899 nebula views took 1003 us, 727 at 5).
-// The host sizes the grid to the same.
+// 512 frame 159 and 40.  Held to 7 resident waves per SIMD: the loop over tiles keeps ~14 more
+// vector registers live than one tile does, so at 8 waves it would spill; with area code to 5, as
+// the other launches are (at 7 it spilled 46; four 1599 x 899 nebula views, claimed, 1003 us and
+// 727 at 5).  The host sizes the grid to the same.
 constexpr int kBatchThreads = 256;
 
 template <int FEAT>

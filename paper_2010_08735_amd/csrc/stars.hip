@@ -1011,7 +1011,7 @@ hipError_t launch_star_build(const StarBuild& B, int* count, int64_t n, int band
   return bands ? build<true>(B, count, n, s) : build<false>(B, count, n, s);
 }
 
-// ---- reading a map back ---------------------------------------------------------------------------
+// ---- reading a map back --------------------------------------------------------------------------
 
 __global__ void k_star_unpack(const void* __restrict__ in, int64_t count, float scale, int fp16,
                               float4* __restrict__ out) {
