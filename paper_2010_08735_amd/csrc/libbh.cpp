@@ -1155,15 +1155,19 @@ extern "C" bh_status bh_color_shift_table_download(bh_ctx* c, float* host) {
   HIPCHK(hipSetDevice(c->device));
   bh_status st = ensure_cshift(c, nullptr);
   if (st) return st;
-  // plane by plane (D outermost on the device, innermost for the caller)
-  constexpr size_t plane = (size_t)kCshiftN * kCshiftN;
-  std::unique_ptr<float4[]> nodes(new (std::nothrow) float4[plane]);
+  // D is outermost on the device and innermost for the caller: some planes at a time
+  constexpr size_t plane = (size_t)kCshiftN * kCshiftN, at_once = 16;
+  static_assert(kCshiftN % at_once == 0, "whole groups of planes");
+  std::unique_ptr<float4[]> nodes(new (std::nothrow) float4[plane * at_once]);
   if (!nodes) return fail(BH_ENOMEM, "no host memory for the colour-shift table");
-  for (size_t k = 0; k < kCshiftN; ++k) {
-    HIPCHK(hipMemcpy(nodes.get(), c->ctab + k * plane, sizeof(float4) * plane,
+  for (size_t k = 0; k < kCshiftN; k += at_once) {
+    HIPCHK(hipMemcpy(nodes.get(), c->ctab + k * plane, sizeof(float4) * plane * at_once,
                      hipMemcpyDeviceToHost));
-    for (size_t ij = 0; ij < plane; ++ij)
-      memcpy(host + 4 * (ij * kCshiftN + k), &nodes[ij], sizeof(float4));
+    for (size_t ij = 0; ij < plane; ++ij) {
+      float* out = host + 4 * (ij * kCshiftN + k);
+      for (size_t q = 0; q < at_once; ++q)
+        memcpy(out + 4 * q, &nodes[q * plane + ij], sizeof(float4));
+    }
   }
   return BH_OK;
 }
