@@ -454,15 +454,17 @@ static void up(const float4* in, void* out, const float4* P, const float4* U, co
                      P, U, B, exposure);
 }
 
-// Output tiles.  64 x 64 tiles of 16 waves read the least around each tile, but a small image
-// has too few of them to fill the chip: below kUpFewTiles (about 960 x 540) 32 x 32 tiles of 8
-// waves (640 x 360 display: 11.4 against 13.3 us; 1280 x 720: 17.4 against 14.7).  With the
-// encoding's arithmetic, images of more than one round of workgroups (two 64 x 64 tiles reside on
-// a CU) overlap better in small ones, 32 x 32 of 4 waves: display, us, small against large: 1920 x
-// 1080 (510 tiles) 26.6 and 23.7, 1920 x 1200 (570) 29.7 and 30.1, 2560 x 1440 38.3 and 40.2, 3840
-// x 2160 70.9 and 73.4 (3839 x 2158 78.5 and 77.2), 5120 x 2880 124 and 131, 7680 x 4320 280 and
-// 295.
-constexpr int kUpFewTiles = 128, kUpManyTiles = 512;
+// Output tiles.  64 x 64 tiles read the least around each tile, but a small image has too few of
+// them to fill the chip: below kUpFewTiles (about 960 x 540) 32 x 32 tiles of 8 waves (640 x 360
+// display: 11.4 against 13.3 us; 1280 x 720: 17.4 against 14.7).  64 x 64 tiles of 8 waves reside
+// four on a CU and overlap their phases; with the encoding's arithmetic 16 waves a tile are
+// quicker while the image is one round of them, two on a CU (kUpRoundTiles).  Display, us, 16
+// waves and 8: 1920 x 1080 (510 tiles) 23.9 and 24.4, 1600 x 900 19.6 and 20.6; 1920 x 1200 (570) 30.1
+// and 29.0, 2560 x 1440 40.2 and 39.6, 3840 x 2160 73.4 and 70.4, 3839 x 2158 77.2 and 75.1, 7680 x
+// 4320 281 and 276.  Linear: 1920 x 1080 21.6 and 21.3, 1920 x 1200 27.6 and 25.2, 3839 x 2158 86.1
+// and 86.2, 5120 x 2880 148 and 141.  (32 x 32 tiles of 4 waves: 3839 x 2158 display 78.8, 5120 x
+// 2880 125 against 120.)
+constexpr int kUpFewTiles = 128, kUpRoundTiles = 512;
 
 static hipError_t launch_bloom_up(const float4* in, void* out, const float4* P, const float4* U,
                                   const BloomDev& B, bool display, float exposure,
@@ -472,10 +474,10 @@ static hipError_t launch_bloom_up(const float4* in, void* out, const float4* P, 
     display ? up<32, 512, true>(in, out, P, U, B, exposure, s)
             : up<32, 512, false>(in, out, P, U, B, exposure, s);
   } else if (display) {
-    tiles > kUpManyTiles ? up<32, 256, true>(in, out, P, U, B, exposure, s)
-                         : up<64, 1024, true>(in, out, P, U, B, exposure, s);
+    tiles > kUpRoundTiles ? up<64, 512, true>(in, out, P, U, B, exposure, s)
+                          : up<64, 1024, true>(in, out, P, U, B, exposure, s);
   } else {
-    up<64, 1024, false>(in, out, P, U, B, exposure, s);
+    up<64, 512, false>(in, out, P, U, B, exposure, s);
   }
   return hipGetLastError();
 }
