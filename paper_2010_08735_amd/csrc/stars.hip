@@ -23,7 +23,7 @@
 // finds the maxima and the tiles' topmost texels, from which k_star_tail forms the remaining
 // levels; a second pass merges again (the stars are few against the texels) and writes the
 // stored texels and the occupancy bits, each byte once.
-// 10^6 stars on 6 x 2048^2: 351 us of kernels (count 19, scatter 41, tiles 118 and 149, tail 13),
+// 10^6 stars on 6 x 2048^2: 351 us of kernels (count 19, scatter 41, tiles 119 and 152, tail 13),
 // where linking the stars through a texel-sized head array and passing every level through
 // FP32 texels in memory took 1550 us, 60 launches and 0.9 GB of scratch.  The map's own 277 MB
 // are 45 us; the tile passes wait on their chains of LDS and FP64 latency (a wave lives for 13
@@ -498,10 +498,12 @@ constexpr int kStash = 512;
 // once for each of its stars), sort them first, through memory: counts per texel and their
 // prefix sums in LDS, a scatter of the star indices, and each star's rank among the indices of its
 // texel, one lane per star.  The second pass over the tiles counts again and finds the order in
-// memory.  Then a texel's sum is one walk.  All kernels for 10^6 stars, where every
-// texel looked through a list in memory once for each of its stars, and now: 6 x 32^2 229 and 1.1
-// ms, 64^2 19.3 and 0.44; 256^2 589 and 195 us, 512^2 235 and 181, 1024^2 243 and 237; on 2048^2
-// with half of the stars in a cluster of 0.02 rad 46 and 3.0 ms (one CU's work, almost all of it).
+// memory.  Then a texel's sum is one walk, in LDS where the values fit.  All kernels for 10^6
+// stars, where every texel looked through a list in memory once for each of its stars, and now:
+// 6 x 32^2 229 and 0.88 ms, 64^2 19.5 and 0.40; 256^2 593 and 195 us, 512^2 235 and 175, 1024^2
+// 239 and 232; on 2048^2 with half of the stars in a cluster of 0.02 rad 46 and 3.1 ms (one CU's
+// work, almost all of it); 10^7 stars on 4096^2, where the denser third of the tiles just passes
+// kStash, 2.45 and 2.55 ms.
 constexpr int kListed = 8;
 
 // PACK: write the tile's stored texels and occupancy bits; otherwise only its levels' maxima
@@ -512,9 +514,16 @@ __global__ void __launch_bounds__(kTileThreads, 6) k_star_tiles(StarBuild B) {
   constexpr int P = M::kN - 2;
   __shared__ int head[1 << (2 * kMaxTileLog)];
   __shared__ M mip[kMipTexels];
-  __shared__ M stash[kStash];
-  __shared__ int stash_id[kStash], stash_next[kStash];
-  __shared__ short stash_at[kStash], parents[kStash];
+  // kStash stars with their indices, links and texels, and their parents; or, when the tile's stars
+  // are sorted, the values of as many as fit
+  constexpr int kEach = sizeof(M) + 2 * sizeof(int) + 2 * sizeof(short);
+  constexpr int kStaged = kStash * kEach / sizeof(M);
+  __shared__ __align__(16) char stars[kStash * kEach];
+  M* const stash = (M*)stars;
+  int* const stash_id = (int*)(stash + kStash);
+  int* const stash_next = stash_id + kStash;
+  short* const stash_at = (short*)(stash_next + kStash);
+  short* const parents = stash_at + kStash;
   __shared__ unsigned seen[32];           // parents already listed
   __shared__ int own, listed;             // stars of this tile, parents with a child
   __shared__ int part[kTileThreads / 64];
@@ -709,17 +718,31 @@ __global__ void __launch_bounds__(kTileThreads, 6) k_star_tiles(StarBuild B) {
   };
   const bool dense = mine > most;
   const int* sorted = nullptr;
-  if (dense) sorted = sort_tile();
+  const auto star = [&](int e) {
+    if (B.val) return value_at<BANDS>(B, base + e);
+    return star_value<BANDS>(B, e, place_star<BANDS>(B.dirs, B.inten, e, n0));
+  };
+  const bool staged = dense && mine <= kStaged;
+  if (dense) {
+    sorted = sort_tile();
+    if (staged) {
+      for (int p = t; p < mine; p += kTileThreads) stash[p] = star(sorted[p]);
+      __syncthreads();
+    }
+  }
   // level-0 texel from the sorted stars
   const auto merge_sorted = [&](int at) {
     constexpr int kAhead = 4;  // stars whose values are in flight
     Sums<BANDS> sum;
     int j = at ? head[at - 1] : 0;
     const int end = head[at];
-    const auto star = [&](int e) {
-      if (B.val) return value_at<BANDS>(B, base + e);
-      return star_value<BANDS>(B, e, place_star<BANDS>(B.dirs, B.inten, e, n0));
-    };
+    if (staged) {
+      for (; j < end; ++j) {
+        const M m = stash[j];
+        sum.add(m, (double)m.v[P], (double)m.v[P + 1]);
+      }
+      return sum.texel();
+    }
     for (; j + kAhead <= end; j += kAhead) {
       M m[kAhead];
 #pragma unroll
@@ -948,16 +971,16 @@ __global__ void __launch_bounds__(kTileThreads) k_star_tail(StarBuild B) {
 
 // Tiles of 64 texels an edge from 1024 texels a face, else 32: a map of few tiles needs the
 // smaller ones to spread over the chip (6 x 256^2: 384 workgroups instead of 96).  Smaller still
-// while they hold more than twice kStash on average, which too few workgroups would sort, down to
-// bins of four tiles, each of which looks through its bin.  Splitting to half of kStash
-// instead, so that the lists do, costs more rounds of workgroups than it saves: 10^6 stars on 6 x
-// 256^2 349 against 226 us, on 1024^2 299 against 276.
+// while they hold more than four times kStash on average, which too few workgroups would sort,
+// down to bins of four tiles, each of which looks through its bin.  Splitting further costs more
+// rounds of workgroups than it saves: past 2 kStash, 3 10^6 stars on 6 x 1024^2 571 against 433
+// us; past kStash / 2, 10^6 on 256^2 349 against 226.
 int star_tile_log(int n0, int64_t n) {
   int lg = 0;
   while ((2 << lg) <= n0) ++lg;
   int tl = n0 >= 1024 ? kMaxTileLog : std::min(lg, kMaxTileLog - 1);
   const auto tiles = [&](int l) { return (int64_t)6 * (n0 >> l) * (n0 >> l); };
-  while (tl > 0 && n > 2 * kStash * tiles(tl) && tiles(tl - 1) <= 4 * kMaxBins) --tl;
+  while (tl > 0 && n > 4 * kStash * tiles(tl) && tiles(tl - 1) <= 4 * kMaxBins) --tl;
   return tl;
 }
 
@@ -1011,7 +1034,7 @@ hipError_t launch_star_build(const StarBuild& B, int* count, int64_t n, int band
   return bands ? build<true>(B, count, n, s) : build<false>(B, count, n, s);
 }
 
-// ---- reading a map back --------------------------------------------------------------------------
+// ---- reading a map back ---------------------------------------------------------------------
 
 __global__ void k_star_unpack(const void* __restrict__ in, int64_t count, float scale, int fp16,
                               float4* __restrict__ out) {
