@@ -142,22 +142,24 @@ constexpr int kMaxBins = 1536;
 
 // Hash of the field, stars per bin and whether a band value is negative, infinite or NaN, which
 // fails the whole build (unless `count` and `bad` are null).  One 64-bit atomic per workgroup:
-// one per wave queued 15 600 of them on the same address, 192 us for 10^6 stars.
+// one per wave queued 15 600 of them on the same address, 192 us for 10^6 stars.  Each thread takes
+// `per` stars, fewer in a small field, so that it spreads over the chip.
 template <bool BANDS>
 __global__ void __launch_bounds__(kSortThreads)
     k_star_count(const float* __restrict__ dirs, const float* __restrict__ inten,
-                 const float* __restrict__ temp, int64_t n, int n0, int bl, int bins,
+                 const float* __restrict__ temp, int64_t n, int per, int n0, int bl, int bins,
                  unsigned long long* __restrict__ acc, int* __restrict__ bad,
                  int* __restrict__ count) {
   __shared__ int hist[kMaxBins];
   __shared__ unsigned long long wsum[kSortThreads / 64];
-  for (int b = threadIdx.x; b < bins; b += kSortThreads) hist[b] = 0;
+  if (count)
+    for (int b = threadIdx.x; b < bins; b += kSortThreads) hist[b] = 0;
   __syncthreads();
-  const int64_t first = (int64_t)blockIdx.x * kSortStars + threadIdx.x;
+  const int64_t first = (int64_t)blockIdx.x * kSortThreads * per + threadIdx.x;
   uint64_t h = 0;
   bool any_bad = false;
 #pragma unroll 4
-  for (int q = 0; q < kSortPer; ++q) {
+  for (int q = 0; q < per; ++q) {
     const int64_t s = first + q * kSortThreads;
     if (s >= n) continue;
     h += star_hash<BANDS>(dirs, inten, temp, s);
@@ -1002,13 +1004,14 @@ hipError_t launch_star_count(const float* dirs, const float* inten, const float*
                              hipStream_t s) {
   if (n <= 0) return hipSuccess;
   const int bl = star_bin_log(n0, n), nb = n0 >> bl;
-  const dim3 grid(blocks_for(n, kSortStars));
+  const int per = (int)std::min<int64_t>(n / (256 * kSortThreads) + 1, kSortPer);
+  const dim3 grid(blocks_for(n, kSortThreads * per));
   if (bands)
     hipLaunchKernelGGL(k_star_count<true>, grid, dim3(kSortThreads), 0, s, dirs, inten, temp, n,
-                       n0, bl, 6 * nb * nb, acc, bad, count);
+                       per, n0, bl, 6 * nb * nb, acc, bad, count);
   else
     hipLaunchKernelGGL(k_star_count<false>, grid, dim3(kSortThreads), 0, s, dirs, inten, temp, n,
-                       n0, bl, 6 * nb * nb, acc, bad, count);
+                       per, n0, bl, 6 * nb * nb, acc, bad, count);
   return hipGetLastError();
 }
 
