@@ -7,8 +7,8 @@ import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2010_08735_amd", "csrc")
-SCENARIOS = ["reuse", "refused_wait", "allocation_failure", "full_pool", "peers",
-             "budget", "threads"]
+SCENARIOS = ["reuse", "refused_wait", "allocation_failure", "full_pool", "larger_cycle",
+             "peers", "budget", "threads"]
 FLAVOURS = {"plain": ["-O2"],
             "asan_ubsan": ["-O1", "-g", "-fsanitize=address,undefined",
                            "-fno-sanitize-recover=undefined"],
