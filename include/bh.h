@@ -348,8 +348,8 @@ bh_status bh_render_batch(bh_ctx* ctx, const bh_tables* t, const bh_view* views,
 
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc): bh_render_batch without any allocation.
- * The launch's view records and tile runs live in a fixed device array of the library
- * (512 x 336 B = 168 KiB, one per GPU, held until the process ends), so n is at
+ * The launch's view records, tile runs and work counter live in a fixed device array of
+ * the library (256 B + 512 x 336 B = 168 KiB, one per GPU, held until the process ends), so n is at
  * most BH_NOALLOC_MAX_VIEWS (BH_EINVAL above); the records are uploaded through pinned host
  * memory that bh_create sets up, and the kernels are launched directly (no graph is
  * built).  Same kernels as bh_render_batch with the same tile configuration and launch
@@ -372,7 +372,7 @@ bh_status bh_tile_config_get(int32_t index, bh_tile_config* out);
  * bh_serve_start (-1: the built-in default, 8x8 tiles of one pixel per thread, index 3) */
 bh_status bh_set_tile_config(bh_ctx* ctx, int32_t index);
 /* Select the launch form of the batched calls: 1 = persistent workgroups whose waves
- * take the tiles in turn, 0 = one workgroup per tile (the default). */
+ * are dealt tiles in turn and claim the rest, 0 = one workgroup per tile (the default). */
 bh_status bh_set_batch_form(bh_ctx* ctx, int32_t persistent);
 /* Time every tile configuration with both batched launch forms (persistent workgroups,
  * or one workgroup per tile) on the given views and

@@ -53,7 +53,7 @@ hipError_t launch_area_build_bands(const float* rgbx, int n0, float4* tex, int* 
                                    hipStream_t s);
 hipError_t launch_cshift_build(const CshiftRule& q, double4* spec, float4* tab, hipStream_t s);
 hipError_t launch_render_batch(int cfg, int persistent, int feat, const ViewDev* views,
-                               const TileRun* runs, int nruns, int ntiles,
+                               const TileRun* runs, int nruns, int ntiles, int* counter,
                                const TablesDev& T, const LutDev& L, int grid, hipStream_t s);
 hipError_t launch_trace_rays(const TablesDev& T, const float* rays, int64_t n, float4* out,
                              float4* out_time, hipStream_t s);
@@ -234,6 +234,7 @@ struct bh_ctx {
   // batched launches
   ViewDev* b_views = nullptr;
   TileRun* b_runs = nullptr;
+  int* b_counter = nullptr;
   size_t b_cap = 0;  // views and runs held by b_views / b_runs
   Staging b_stage[2];
   int b_next_stage = 0;
@@ -368,12 +369,15 @@ extern "C" bh_status bh_create(int device, uint64_t budget, bh_ctx** out) {
   if (st) return st;
   hipError_t e = launch_band_lut(c->lut, c->lut_n, c->lut_x0, c->lut_dx, nullptr);
   if (e == hipSuccess) e = hipDeviceSynchronize();
-  if (e != hipSuccess) {
+  if (e == hipSuccess) {
+    st = dev_alloc(c.get(), sizeof(int) * 64, (void**)&c->b_counter);
+  } else {
     st = fail(BH_EDEVICE, std::string("band table: ") + hipGetErrorString(e));
   }
   if (!st) st = noalloc_setup(c.get());
   if (st) {
     dev_free(c.get(), c->lut, sizeof(float4) * c->lut_n);
+    dev_free(c.get(), c->b_counter, c->b_counter ? sizeof(int) * 64 : 0);
     if (c->na_stage.host) (void)hipHostFree(c->na_stage.host);
     if (c->na_stage.done) (void)hipEventDestroy(c->na_stage.done);
     return st;
@@ -429,6 +433,7 @@ extern "C" void bh_destroy(bh_ctx* c) {
   c->pool.drop();
   dev_free(c, c->lut, 0);
   dev_free(c, c->ctab, 0);
+  dev_free(c, c->b_counter, 0);
   dev_free(c, c->b_views, 0);
   dev_free(c, c->b_runs, 0);
   for (auto& s : c->b_stage) {
@@ -1436,8 +1441,8 @@ static int batch_grid(const bh_ctx* c, int feat, int64_t ntiles) {
 static bh_status enqueue_batch(bh_ctx* c, int cfg, int pers, const TablesDev& T,
                                const std::vector<ViewDev>& vds,
                                const std::vector<TileRun>& runs, int ntiles, ViewDev* dviews,
-                               TileRun* druns, Staging& stg, hipStream_t s, bool use_graph,
-                               hipStream_t cs = nullptr,
+                               TileRun* druns, int* counter, Staging& stg, hipStream_t s,
+                               bool use_graph, hipStream_t cs = nullptr,
                                hipEvent_t slot_free = nullptr, hipEvent_t copied = nullptr) {
   size_t bv = sizeof(ViewDev) * vds.size(), br = sizeof(TileRun) * runs.size();
   bh_status st = ensure_staging(stg, bv + br);
@@ -1461,11 +1466,11 @@ static bh_status enqueue_batch(bh_ctx* c, int cfg, int pers, const TablesDev& T,
   int grid = batch_grid(c, feat, ntiles);
   LutDev L = lut_dev(c);
   if (!use_graph) {
-    HIPCHK(launch_render_batch(cfg, pers, feat, dviews, druns, nruns, ntiles, T, L, grid,
-                               s));
+    HIPCHK(launch_render_batch(cfg, pers, feat, dviews, druns, nruns, ntiles, counter, T, L,
+                               grid, s));
     return BH_OK;
   }
-  bh_ctx::GraphKey key{(cfg * 2 + pers) * 8 + feat, ntiles, nruns, grid, (uintptr_t)dviews,
+  bh_ctx::GraphKey key{(cfg * 2 + pers) * 8 + feat, ntiles, nruns, grid, (uintptr_t)counter,
                        (const void*)T.D, (const void*)T.U, (const void*)T.Dt, (const void*)T.Ut,
                        T.d_n, T.u_ne, T.u_nphi};
   auto it = c->graphs.find(key);
@@ -1474,8 +1479,8 @@ static bh_status enqueue_batch(bh_ctx* c, int cfg, int pers, const TablesDev& T,
     HIPCHK(hipStreamCreateWithFlags(&cap, hipStreamNonBlocking));
     hipGraph_t graph;
     HIPCHK(hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal));
-    hipError_t e = launch_render_batch(cfg, pers, feat, dviews, druns, nruns, ntiles, T, L,
-                                       grid, cap);
+    hipError_t e = launch_render_batch(cfg, pers, feat, dviews, druns, nruns, ntiles, counter,
+                                       T, L, grid, cap);
     hipError_t e2 = hipStreamEndCapture(cap, &graph);
     (void)hipStreamDestroy(cap);
     if (e != hipSuccess || e2 != hipSuccess)
@@ -1556,7 +1561,7 @@ extern "C" bh_status bh_render_batch(bh_ctx* c, const bh_tables* t, const bh_vie
   if (!c->b_last) HIPCHK(hipEventCreateWithFlags(&c->b_last, hipEventDisableTiming));
   else HIPCHK(hipStreamWaitEvent(s, c->b_last, 0));
   st = enqueue_batch(c, c->tile_cfg, c->persistent, tables_dev(t), vds, runs, (int)ntiles,
-                     c->b_views, c->b_runs, stg, s, true);
+                     c->b_views, c->b_runs, c->b_counter, stg, s, true);
   if (st) return st;
   HIPCHK(hipEventRecord(c->b_last, s));
   return BH_OK;
@@ -1602,7 +1607,8 @@ extern "C" bh_status bh_render_batch_noalloc(bh_ctx* c, const bh_tables* t, cons
       return fail(BH_EINVAL, "batch too large: more than 2^32 - 1 pixels in its tiles");
   }
   hipStream_t s = (hipStream_t)stream;
-  ViewDev* dviews = (ViewDev*)c->scratch;
+  int* dcounter = (int*)c->scratch;
+  ViewDev* dviews = (ViewDev*)((char*)c->scratch + 256);
   TileRun* druns = (TileRun*)(dviews + BH_NOALLOC_MAX_VIEWS);
   HIPCHK(hipMemcpyAsync(dviews, hv, sizeof(ViewDev) * n, hipMemcpyHostToDevice, s));
   HIPCHK(hipMemcpyAsync(druns, hr, sizeof(TileRun) * n, hipMemcpyHostToDevice, s));
@@ -1610,7 +1616,7 @@ extern "C" bh_status bh_render_batch_noalloc(bh_ctx* c, const bh_tables* t, cons
   stg.used = true;
   int feat = 0;
   for (int i = 0; i < n; ++i) feat |= view_features(hv[i]);
-  HIPCHK(launch_render_batch(cfg, c->persistent, feat, dviews, druns, n, (int)ntiles,
+  HIPCHK(launch_render_batch(cfg, c->persistent, feat, dviews, druns, n, (int)ntiles, dcounter,
                              tables_dev(t), lut_dev(c), batch_grid(c, feat, ntiles), s));
   return BH_OK;
 }
@@ -1789,8 +1795,8 @@ extern "C" bh_status bh_band_eval(bh_ctx* c, const float* temps, int64_t n, floa
 // ---- serving ---------------------------------------------------------------------------------
 // The policy (admission by budget, continuous batching, failure and cancellation) is the
 // scheduler of bh_sched.h, run on its own thread; this is its HIP backend.  Launches go to
-// the serving stream through maxin + 1 slots of device records (view blocks, tile
-// runs), uploaded on a copy stream after the slot's previous launch; a launch is
+// the serving stream through maxin + 1 slots of device records (view blocks, tile runs,
+// a claim counter), uploaded on a copy stream after the slot's previous launch; a launch is
 // in flight until an event recorded after it completes.  Library images come from a
 // stream-ordered memory pool on the serving stream, inside the context's HBM budget.
 struct ServePayload {
@@ -1814,6 +1820,7 @@ struct ServeBackend {
   std::vector<Staging> stg;
   std::vector<ViewDev*> dviews;
   std::vector<TileRun*> druns;
+  std::vector<int*> dcounter;
   std::vector<size_t> rcap;
   std::vector<hipEvent_t> slot_free, copied, evpool;
   bool dev_ok = true;
@@ -1826,12 +1833,13 @@ struct ServeBackend {
     stg.resize(slots);
     dviews.assign(slots, nullptr);
     druns.assign(slots, nullptr);
+    dcounter.assign(slots, nullptr);
     rcap.assign(slots, 0);
     slot_free.assign(slots, nullptr);
     copied.assign(slots, nullptr);
   }
 
-  // streams, image pool, per-slot events
+  // streams, image pool, per-slot counters and events
   hipError_t init() {
     hipError_t e = hipStreamCreateWithFlags(&stream, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&copy_stream, hipStreamNonBlocking);
@@ -1847,7 +1855,8 @@ struct ServeBackend {
       e = hipMemPoolSetAttribute(img_pool, hipMemPoolAttrReleaseThreshold, &keep);
     }
     for (int k = 0; k < slots && e == hipSuccess; ++k) {
-      e = hipEventCreateWithFlags(&slot_free[k], hipEventDisableTiming);
+      e = raw_alloc(c, &dcounter[k], sizeof(int) * 16);
+      if (e == hipSuccess) e = hipEventCreateWithFlags(&slot_free[k], hipEventDisableTiming);
       if (e == hipSuccess) e = hipEventCreateWithFlags(&copied[k], hipEventDisableTiming);
     }
     return e;
@@ -1865,6 +1874,7 @@ struct ServeBackend {
       if (copied[k]) (void)hipEventDestroy(copied[k]);
       if (dviews[k]) (void)hipFree(dviews[k]);
       if (druns[k]) (void)hipFree(druns[k]);
+      if (dcounter[k]) (void)hipFree(dcounter[k]);
       if (stg[k].host) (void)hipHostFree(stg[k].host);
       if (stg[k].done) (void)hipEventDestroy(stg[k].done);
     }
@@ -1949,7 +1959,7 @@ struct ServeBackend {
       rcap[slot] = cap;
     }
     bh_status st = enqueue_batch(c, cfg, pers, tables_dev(pieces.front().r->payload.tables), vds,
-                                 runs, (int)ntiles, dviews[slot], druns[slot],
+                                 runs, (int)ntiles, dviews[slot], druns[slot], dcounter[slot],
                                  stg[slot], stream, false, copy_stream, slot_free[slot],
                                  copied[slot]);
     if (st == BH_OK && hipEventRecord(slot_free[slot], stream) != hipSuccess) st = BH_EDEVICE;

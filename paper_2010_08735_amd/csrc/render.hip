@@ -774,8 +774,9 @@ __device__ __forceinline__ float3 cshift_lookup(const float4* __restrict__ tab, 
 
 // The view record of a kernel that takes it as its first argument (launch_plain checks that it
 // does), to be read again from the argument segment where it is used: fields kept since the
-// kernel's start would hold scalar registers across the whole trace (8 to 28 of them spilled into vector registers, and two of
-// those to memory; without: 1080p frame 29.0 -> 28.0 us, 8K 324 -> 307, animated 52.5 -> 49.4).
+// kernel's start would hold scalar registers across the whole trace (8 to 28 of them spilled into
+// vector registers, and two of those to memory; without: 1080p frame 29.0 -> 28.0 us, 8K 324 ->
+// 307, animated 52.5 -> 49.4).
 __device__ __forceinline__ const ViewDev& reread(const ViewDev&) {
   typedef const __attribute__((address_space(4))) ViewDev* Args;
   Args p = (Args)__builtin_amdgcn_kernarg_segment_ptr();
@@ -1231,18 +1232,22 @@ __device__ __forceinline__ void render_flat_tile(const ViewDev* __restrict__ vie
                                         (tile / r.tiles_x) * TH);
 }
 
-// Persistent launch over the tiles of many views.  Every wave works on its own: wave j renders
-// the flat tiles j, j + waves, ..., every 8x8 block of each, so no tile waits on a barrier, the
-// workgroup shape (4 waves) is the same for every tile configuration, and neighbouring tiles,
-// which cost alike, go to different waves.  No wave has more than its share, rounded up, at any
-// size.  Claiming tiles from an atomic counter costs more than it evens out, since one
-// address takes an atomic every 17 ns: claims of 16 blocks with short ones at the end, then in
-// turn, us: 24 uneven views 865 and 862, four 1080p frames 262 and 153, one 176 and 59, one 512 x
-// 512 frame 159 and 40.  Held to 7 resident waves per SIMD: the loop over tiles keeps ~14 more
-// vector registers live than one tile does, so at 8 waves it would spill; with area code to 5, as
-// the other launches are (at 7 it spilled 46; four 1599 x 899 nebula views, claimed, 1003 us and
-// 727 at 5).  The host sizes the grid to the same.
-constexpr int kBatchThreads = 256;
+// Persistent launch over the tiles of many views.  Every wave works on its own and renders every
+// 8x8 block of its tiles, so no tile waits on a barrier and the workgroup shape (4 waves) is the
+// same for every tile configuration.  Wave j is dealt the tiles j, j + waves, ..., so that
+// neighbouring tiles, which cost alike, go to different waves and no launch leaves waves without
+// any.  Up to kDealtBlocks blocks a wave all tiles are dealt.  Beyond, where the sums of uneven
+// tiles drift apart, the second half is claimed from an atomic counter, about kClaimBlocks blocks
+// at a time: one address takes an atomic every 17 ns, which claims of all tiles ran into.  Tiles of
+// 16 blocks are too coarse to deal more than half of.  A wave leaves at its first tile past the
+// last; the counter only grows, so every wave reaches that exit.  us, all claimed (with single
+// tiles at the end), all dealt, and so: 64 uneven views of 86 Mpixels 1340, 1480, 1240; 24 of 31
+// Mpixels 625, 585, 585; 24 of 52 Mpixels 865, 862, 842; eight 1080p frames 372, 272, 277; one 176,
+// 59, 63; one 512 x 512 frame 159, 40, 38.  Held to 7 resident waves per SIMD: the loop over tiles
+// keeps ~14 more vector registers live than one tile does, so at 8 waves it would spill; with area
+// code to 5, as the other launches are (at 7 it spilled 46; four 1599 x 899 nebula views, claimed,
+// 1003 us and 727 at 5).  The host sizes the grid to the same.
+constexpr int kBatchThreads = 256, kDealtBlocks = 64, kClaimBlocks = 16;
 
 template <int FEAT>
 constexpr int kBatchWaves = batch_waves(FEAT);
@@ -1250,26 +1255,45 @@ constexpr int kBatchWaves = batch_waves(FEAT);
 template <int TW, int TH, int PPT, int FEAT>
 __global__ void __launch_bounds__(kBatchThreads, kBatchWaves<FEAT>)
     k_render_batch(const ViewDev* __restrict__ views, const TileRun* __restrict__ runs,
-                   int nruns, int ntiles, TablesDev T, LutDev L) {
+                   int nruns, int ntiles, int* __restrict__ counter, TablesDev T, LutDev L) {
   using C = TileCfg<TW, TH, 1>;
   constexpr int kBlocks = C::kBX * C::kBY;                // 8x8 blocks per tile
   const int lane = threadIdx.x & 63;
   const int q = lane >> 2;
   const int ox = 2 * (q & 3) + (lane & 1), oy = 2 * (q >> 2) + ((lane >> 1) & 1);
   const int waves = (int)(gridDim.x * (kBatchThreads / 64));
-  const int first = (int)(blockIdx.x * (kBatchThreads / 64) + threadIdx.x / 64);
+  constexpr int kClaim = kBlocks >= kClaimBlocks ? 1 : kClaimBlocks / kBlocks;  // tiles
+  const int share = (ntiles + waves - 1) / waves;
+  const bool claims = kBlocks >= kClaimBlocks || share * kBlocks > kDealtBlocks;
+  const int dealt = claims ? max(ntiles / waves / 2, 1) : share;  // tiles a wave
+  const int wave = __builtin_amdgcn_readfirstlane(
+      (int)(blockIdx.x * (kBatchThreads / 64) + threadIdx.x / 64));
+  for (int r = 0;; ++r) {
+    int it0, it1;
+    if (r < dealt) {
+      it0 = r * waves + wave;
+      it1 = it0 + 1;
+    } else {
+      if (!claims) break;
+      int c = 0;
+      if (lane == 0) c = atomicAdd(counter, 1);
+      it0 = dealt * waves + __builtin_amdgcn_readfirstlane(c) * kClaim;
+      it1 = min(it0 + kClaim, ntiles);
+    }
+    if (it0 >= ntiles) break;
 #pragma unroll 1
-  for (int it = __builtin_amdgcn_readfirstlane(first); it < ntiles; it += waves) {
-    const TileRun r = find_run(runs, nruns, it);
-    const int tile = r.tile0 + (it - r.start);
-    const ViewDev& v = views[r.view];
-    const int tx0 = (tile % r.tiles_x) * TW, ty0 = (tile / r.tiles_x) * TH;
+    for (int it = it0; it < it1; ++it) {
+      const TileRun run = find_run(runs, nruns, it);
+      const int tile = run.tile0 + (it - run.start);
+      const ViewDev& v = views[run.view];
+      const int tx0 = (tile % run.tiles_x) * TW, ty0 = (tile / run.tiles_x) * TH;
 #pragma unroll 1
-    for (int blk = 0; blk < kBlocks; ++blk) {
-      const int bx = tx0 + 8 * (blk % C::kBX), by = ty0 + 8 * (blk / C::kBX);
-      if (bx >= v.width || by >= v.height) continue;    // block outside the image
-      render_pixel<false, (FEAT & kFeatParticles) != 0, false, kAreaOf<FEAT>>(
-          v, T, L, bx + ox, by + oy, nullptr);
+      for (int blk = 0; blk < kBlocks; ++blk) {
+        const int bx = tx0 + 8 * (blk % C::kBX), by = ty0 + 8 * (blk / C::kBX);
+        if (bx >= v.width || by >= v.height) continue;    // block outside the image
+        render_pixel<false, (FEAT & kFeatParticles) != 0, false, kAreaOf<FEAT>>(
+            v, T, L, bx + ox, by + oy, nullptr);
+      }
     }
   }
 }
@@ -1289,6 +1313,8 @@ __global__ void __launch_bounds__((TW / 8) * (TH / 8) * 64 / PPT, kMinWaves<FEAT
   if (it >= ntiles) return;
   render_flat_tile<TW, TH, PPT, FEAT>(views, runs, nruns, it, T, L);
 }
+
+__global__ void k_reset_counter(int* c) { *c = 0; }
 
 // Measurement variant of the plain launch (16x16 tiles): marks the star-map texels that
 // the footprints visit.
@@ -1342,13 +1368,16 @@ __global__ void __launch_bounds__(256)
 }
 
 // ---- scratch of the allocation-free batched launch -------------------------------------------
-// Device memory of bh_render_batch_noalloc: up to kNoAllocViews view records and as many tile
-// runs.  A file-scope device array: each GPU the library runs on holds its own copy until the
-// process ends, and every call on that GPU shares it (it keeps the last call's contents).  In host
-// code `scratch` only names the symbol: its device address comes from scratch_address(), once per
-// device.
+// Device memory of bh_render_batch_noalloc: the persistent form's claim counter (first 256
+// bytes), then up to kNoAllocViews view records and as many tile runs.  A file-scope device
+// array: each GPU the library runs on holds its own copy until the process ends, and every
+// call on that GPU shares it (it keeps the last call's contents; the counter is reset by a
+// kernel before each persistent launch).  In host code `scratch` only names the symbol: its
+// device address comes from scratch_address(), once per device.
 constexpr int kNoAllocViews = BH_NOALLOC_MAX_VIEWS;
-constexpr size_t kNoAllocBytes = (size_t)kNoAllocViews * (sizeof(ViewDev) + sizeof(TileRun));
+constexpr size_t kNoAllocHead = 256;
+constexpr size_t kNoAllocBytes =
+    kNoAllocHead + (size_t)kNoAllocViews * (sizeof(ViewDev) + sizeof(TileRun));
 static_assert(sizeof(ViewDev) % 16 == 0, "view records keep the tile runs 16-byte aligned");
 static __device__ __align__(256) unsigned char scratch[kNoAllocBytes];
 
@@ -1364,8 +1393,8 @@ struct TileEntry {
   // indexed by the features the views may use: kFeatParticles | kFeatArea | kFeatBands
   // (kFeatBands alone: band star maps without area maps)
   void (*plain[8])(const ViewDev&, const TablesDev&, const LutDev&, hipStream_t);
-  void (*batch[8])(const ViewDev*, const TileRun*, int, int, const TablesDev&, const LutDev&,
-                   int grid, hipStream_t);
+  void (*batch[8])(const ViewDev*, const TileRun*, int, int, int*, const TablesDev&,
+                   const LutDev&, int grid, hipStream_t);
   void (*list[8])(const ViewDev*, const TileRun*, int, int, const TablesDev&, const LutDev&,
                   hipStream_t);
 };
@@ -1390,9 +1419,11 @@ static void launch_plain(const ViewDev& v, const TablesDev& T, const LutDev& L, 
 
 template <int TW, int TH, int PPT, int FEAT>
 static void launch_batch(const ViewDev* views, const TileRun* runs, int nruns, int ntiles,
-                         const TablesDev& T, const LutDev& L, int grid, hipStream_t s) {
+                         int* counter, const TablesDev& T, const LutDev& L, int grid,
+                         hipStream_t s) {
+  hipLaunchKernelGGL(k_reset_counter, dim3(1), dim3(1), 0, s, counter);
   hipLaunchKernelGGL((k_render_batch<TW, TH, PPT, FEAT>), dim3(grid), dim3(kBatchThreads), 0, s,
-                     views, runs, nruns, ntiles, T, L);
+                     views, runs, nruns, ntiles, counter, T, L);
 }
 
 template <int TW, int TH, int PPT, int FEAT>
@@ -1430,15 +1461,15 @@ hipError_t launch_render(int cfg, const ViewDev& v, const TablesDev& T, const Lu
   return hipGetLastError();
 }
 
-// persistent != 0: `grid` persistent workgroups, whose waves take the tiles in turn;
+// persistent != 0: `grid` persistent workgroups, dealt and claiming tiles;
 // otherwise one workgroup per tile.
 hipError_t launch_render_batch(int cfg, int persistent, int feat, const ViewDev* views,
-                               const TileRun* runs, int nruns, int ntiles,
+                               const TileRun* runs, int nruns, int ntiles, int* counter,
                                const TablesDev& T, const LutDev& L, int grid, hipStream_t s) {
   if (ntiles <= 0) return hipSuccess;
   const int a = feat & (kFeatParticles | kFeatArea | kFeatBands);
   if (persistent)
-    kTiles[cfg].batch[a](views, runs, nruns, ntiles, T, L, grid, s);
+    kTiles[cfg].batch[a](views, runs, nruns, ntiles, counter, T, L, grid, s);
   else
     kTiles[cfg].list[a](views, runs, nruns, ntiles, T, L, s);
   return hipGetLastError();
