@@ -9,9 +9,10 @@
 // by size.  Past kKeepMost a block makes room when it was not asked for during the last kStale
 // calls, so that sizes of the past do not fill the pool for good; builds that need more in all
 // than is kept still find what is.  (Room made for every block: the maps of 10^7 stars on 6 x
-// 4096^2, 1 GiB each, and their scratch put each other out, 3.19 ms a build for 2.77.)  Sizes are rounded up to eight steps an octave so that nearly equal
-// builds share blocks.  Kept blocks are freed with the pool's owner, and all pools of a device
-// (Peers) free theirs when an allocation on it fails, before it is tried again.
+// 4096^2, 1 GiB each, and their scratch put each other out, 3.19 ms a build for 2.77.)  Sizes are
+// rounded up to eight steps an octave so that nearly equal builds share blocks.  Kept blocks are
+// freed with the pool's owner, and all pools of a device (Peers) free theirs when an allocation on
+// it fails, before it is tried again.
 #pragma once
 
 #include <cstddef>

@@ -223,9 +223,9 @@ __global__ void __launch_bounds__(256)
 // only the levels it owns elements of, and two output rows at a time come from the same three
 // rows of U_1.  With every level's elements spread over all threads and one output row at a
 // time, the display form issued 829 vector instructions a wave for 4 pixels a lane: 18.4 us at
-// 1920 x 1080, now 16.2 (whole pass 26.5 -> 23.7; linear 3839 x 2158 93.7 -> 90.3).  At 1920 x
-// 1080 every workgroup is resident at once, so the phases add up instead of overlapping: about
-// 3 us each for the image's loads, the chain and the encoding.
+// 1920 x 1080, now 16.2 (whole pass 26.5 -> 23.7; linear 3839 x 2158 93.7 -> 86.2).  At 1920 x
+// 1080 every workgroup is resident at once, so the phases (the image's loads, the chain, the
+// encoding) add up instead of overlapping.
 struct Region {
   int lox, hix, loy, hiy;
 };
@@ -459,11 +459,11 @@ static void up(const float4* in, void* out, const float4* P, const float4* U, co
 // display: 11.4 against 13.3 us; 1280 x 720: 17.4 against 14.7).  64 x 64 tiles of 8 waves reside
 // four on a CU and overlap their phases; with the encoding's arithmetic 16 waves a tile are
 // quicker while the image is one round of them, two on a CU (kUpRoundTiles).  Display, us, 16
-// waves and 8: 1920 x 1080 (510 tiles) 23.9 and 24.4, 1600 x 900 19.6 and 20.6; 1920 x 1200 (570) 30.1
-// and 29.0, 2560 x 1440 40.2 and 39.6, 3840 x 2160 73.4 and 70.4, 3839 x 2158 77.2 and 75.1, 7680 x
-// 4320 281 and 276.  Linear: 1920 x 1080 21.6 and 21.3, 1920 x 1200 27.6 and 25.2, 3839 x 2158 86.1
-// and 86.2, 5120 x 2880 148 and 141.  (32 x 32 tiles of 4 waves: 3839 x 2158 display 78.8, 5120 x
-// 2880 125 against 120.)
+// waves and 8: 1920 x 1080 (510 tiles) 23.9 and 24.4, 1600 x 900 19.6 and 20.6; 1920 x 1200 (570)
+// 30.1 and 29.0, 2560 x 1440 40.2 and 39.6, 3840 x 2160 73.4 and 70.4, 3839 x 2158 77.2 and 75.1,
+// 7680 x 4320 281 and 276.  Linear: 1920 x 1080 21.6 and 21.3, 1920 x 1200 27.6 and 25.2, 3839 x
+// 2158 86.1 and 86.2, 5120 x 2880 148 and 141.  (32 x 32 tiles of 4 waves: 3839 x 2158 display
+// 78.8, 5120 x 2880 125 against 120.)
 constexpr int kUpFewTiles = 128, kUpRoundTiles = 512;
 
 static hipError_t launch_bloom_up(const float4* in, void* out, const float4* P, const float4* U,

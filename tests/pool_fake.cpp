@@ -157,8 +157,8 @@ static void full_pool() {
   CHECK(m.live.empty());
 }
 
-// Builds that need more in all than is kept: what is kept is found every time, and is not put out by
-// the rest.
+// Builds that need more in all than is kept: what is kept is found every time, and is not put out
+// by the rest.
 static void larger_cycle() {
   Memory m;
   Pool::Peers peers;

@@ -52,8 +52,8 @@ int main() {
                   p[(k + 2) % 3] = P.pb + ta * jb;
                   const AreaAt at = area_at(P, i);
                   const int f = face_by_definition(p), kf = f / 2;
-                  ties += std::fabs(p[0]) == std::fabs(p[1]) || std::fabs(p[1]) == std::fabs(p[2]) ||
-                          std::fabs(p[0]) == std::fabs(p[2]);
+                  const float q[] = {std::fabs(p[0]), std::fabs(p[1]), std::fabs(p[2])};
+                  ties += q[0] == q[1] || q[1] == q[2] || q[0] == q[2];
                   ++checked;
                   const float m = std::fabs(p[kf]);
                   if (at.face != f || std::fabs(at.u - p[(kf + 1) % 3] / m) > 1e-6f ||
