@@ -509,9 +509,9 @@ constexpr int kStash = 512;
 constexpr int kListed = 8;
 
 // PACK: write the tile's stored texels and occupancy bits; otherwise only its levels' maxima
-// and its topmost texel (level tl) for the tail.
+// and its topmost texel (level tl) for the tail.  LDS fits three workgroups a CU (two with bands).
 template <bool BANDS, bool PACK>
-__global__ void __launch_bounds__(kTileThreads, 6) k_star_tiles(StarBuild B) {
+__global__ void __launch_bounds__(kTileThreads, BANDS ? 4 : 6) k_star_tiles(StarBuild B) {
   using M = Master<BANDS>;
   constexpr int P = M::kN - 2;
   __shared__ int head[1 << (2 * kMaxTileLog)];
