@@ -86,7 +86,8 @@ typedef struct {
   int32_t u_nphi;     /* intersection table rows along phi (paper: 32)                   */
   int32_t precision;  /* BH_TAB_*                                                        */
   double fp64_band;   /* half-width of the FP64 band around u = 2/3 (0.05)               */
-  double step;        /* integration step in phi (RK4; 0 selects 2e-3)                   */
+  double step;        /* integration step in phi (RK4; 0 selects 2e-3), in (1e-7, 0.05];
+                       * the time is inverse to it (1 ms at 2e-3, half a second at 3e-6)  */
 } bh_table_params;
 
 /* Integrate the orbit equation u'' = 3/2 u^2 - u on the device for every table column
